@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -50,6 +51,25 @@ std::vector<double> metric(const std::vector<double>& c, bool per, double period
     m[i] = 2.0 / (cp - cm);
   }
   return m;
+}
+
+// Row table of the two-step kernel from the y weights w (PairPlan::wy16).
+std::vector<double> scatter_weights(const std::vector<double>& w, int n, bool per) {
+  std::vector<double> t(static_cast<size_t>(n) * 16, 0.0);
+  for (int r = 0; r < n; ++r) {
+    double* o = &t[static_cast<size_t>(r) * 16];
+    for (int k = 0; k < kWeightsPerNode; ++k) o[k] = w[static_cast<size_t>(r) * kWeightsPerNode + k];
+    for (int s = 0; s < 2; ++s)
+      for (int k = 0; k < kTaps; ++k) {
+        int i = r - (s == 0 ? k - 2 : k - 1);  // the output whose tap k is row r
+        if (per)
+          i = (i % n + n) % n;
+        else if (i < 0 || i >= n)
+          continue;
+        o[8 + s * kTaps + k] = w[static_cast<size_t>(i) * kWeightsPerNode + s * kTaps + k];
+      }
+  }
+  return t;
 }
 
 // Trapezoid measure of each node (diagnostics).
@@ -146,11 +166,14 @@ int band_of(long long nunits, int ny, long long nb) {
 // one piece per unit: on a 4060^2 grid in FP64 the default 512 blocks leave
 // a last band of 7 rows and 74 pieces in the busiest range.
 constexpr long long kPieceWork = 4;  // fitted to step times at 1101^2 - 4060^2
-long long busiest_block_work(long long nunits, int ny, long long nb) {
+// The search stops at `limit` (a count already known to be worse), from the
+// last range down, since the short last band is where the pieces are.
+long long busiest_block_work(long long nunits, int ny, long long nb, long long piece_work,
+                             long long limit) {
   const int band = band_of(nunits, ny, nb);
   const long long total = nunits * ny, band_rows = nunits * band;
   long long worst = 0;
-  for (long long L = 0; L < nb; ++L) {
+  for (long long L = nb - 1; L >= 0 && worst < limit; --L) {
     long long beg = total * L / nb;
     const long long end = total * (L + 1) / nb;
     long long work = end - beg;
@@ -160,11 +183,40 @@ long long busiest_block_work(long long nunits, int ny, long long nb) {
       const long long y0 = r0 + rem % hb;
       const long long y1 = std::min(r0 + hb, y0 + (end - beg));
       beg += y1 - y0;
-      work += kPieceWork;
+      work += piece_work;
     }
     worst = std::max(worst, work);
   }
   return worst;
+}
+
+// Sets p's split of nunits x ny unit-rows to about nb blocks (a multiple of 8; unless forced, fewer
+// where that makes the busiest block's work at least 3% less) and returns
+// the block count.
+template <typename Plan>  // StepParams or PairPlan
+int set_blocks(Plan& p, int ny, long long nb, bool forced, long long piece_work) {
+  const long long rows = static_cast<long long>(p.nunits) * ny;
+  nb = std::max<long long>(8, nb / 8 * 8);
+  nb = std::min<long long>(nb, std::max<long long>(8, rows / 8 * 8));
+  if (!forced) {
+    const long long w0 = busiest_block_work(p.nunits, ny, nb, piece_work, LLONG_MAX);
+    long long best = nb, wbest = w0;
+    for (long long c = nb - 8; c >= std::max<long long>(8, nb - nb / 4); c -= 8) {
+      // No count below this one can do better: its equal share alone is more.
+      if ((static_cast<long long>(p.nunits) * ny + c - 1) / c + piece_work >= wbest) break;
+      const long long w = busiest_block_work(p.nunits, ny, c, piece_work, wbest);
+      if (w < wbest) {
+        wbest = w;
+        best = c;
+      }
+    }
+    if (wbest * 100 < w0 * 97) nb = best;
+  }
+  p.nblocks = static_cast<int>(nb);
+  // The blocks of neighbouring units in a band march the same rows at the
+  // same time, so the halo lines they share are fetched once.
+  p.band = band_of(p.nunits, ny, nb);
+  return static_cast<int>(nb);
 }
 
 // One block per resident slot (CUs x blocks per CU), so every block runs in
@@ -191,25 +243,81 @@ int plan_blocks(StepParams& p, int storage, int cus) {
   long long nb = rows >= 8 * slots ? slots : (rows >= 4LL * cus ? cus : rows / 4);
   const char* forced = std::getenv("T2S2_BLOCKS");
   if (forced) nb = std::atoll(forced);
-  nb = std::max<long long>(8, nb / 8 * 8);
-  nb = std::min<long long>(nb, std::max<long long>(8, rows / 8 * 8));
-  if (!forced) {
-    const long long w0 = busiest_block_work(p.nunits, p.ny, nb);
-    long long best = nb, wbest = w0;
-    for (long long c = nb - 8; c >= std::max<long long>(8, nb - nb / 4); c -= 8) {
-      const long long w = busiest_block_work(p.nunits, p.ny, c);
-      if (w < wbest) {
-        wbest = w;
-        best = c;
-      }
+  return set_blocks(p, p.ny, nb, forced != nullptr, kPieceWork);
+}
+
+// Rows that a piece costs the two-step kernel beyond its own: eight above
+// and eight below it are read again, and the second wave starts ten
+// iterations after the first.
+constexpr long long kPairPieceWork = 25;
+// Time of a row of the frame's pieces (the wall paths) over a main row's:
+// along the x walls, where every row takes them, and along the y walls.
+// (Cavity 2049^2: 115.9 us per step at 1.5 / 1.5, 116.2 at 2 / 2, 118.4 at
+// 3 / 2.5; 4097^2: 375.8 at 2 / 1.5, 381.7 at 3 / 2.)
+constexpr double kPairEdgeCost = 2.0, kPairTopCost = 1.5;
+// The two-step kernel takes meshes whose busiest block marches at least this
+// many rows (piece work included); on smaller ones the rows read again cost
+// more than the saved pass.  FP64, us per step, single steps / two-step:
+// Taylor-Green 1101^2 (50 rows) 52.1 / 54.7, 1400^2 (66) 79 / 56; cavity
+// 1025^2 (53) 55.1 / 52.6, 2049^2 (125) 151 / 117.
+constexpr long long kPairMinWork = 52;
+
+// The two-step kernel's plan: the frame of a walled mesh and the main strips
+// and rows inside it, over one block per resident slot, so that a frame
+// piece and a main block's share take about the same time.  Returns the grid,
+// 0 if the mesh does not take the kernel.  T2S2_PAIR_BLOCKS=n forces it with n
+// main blocks (a hook for checking small meshes and ragged splits against
+// single steps).
+int plan_pair(const StepParams& p, PairPlan& plan, int cus) {
+  const bool walls = !p.per_x || !p.per_y;
+  const int per_cu = pair_blocks_per_cu(p.has_force != 0, walls);
+  if (per_cu < 1) return 0;
+  const long long slots = static_cast<long long>(cus) * per_cu / 8 * 8;
+  const char* forced = std::getenv("T2S2_PAIR_BLOCKS");
+  // Columns: the main strips keep 8 columns clear of a wall.
+  plan.x0 = p.per_x ? 0 : kPairOut;
+  plan.nunits = p.per_x ? (p.nx + kPairOut - 1) / kPairOut
+                     : std::max(0, (p.nx - kPairOut - 2 * kHalo) / kPairOut);
+  const int right = p.nx - plan.x0 - plan.nunits * kPairOut;  // columns right of the main strips
+  plan.edge = p.per_x ? 0 : 1 + (right > 0 ? (right + kPairOut - 1) / kPairOut : 0);
+  // Frame pieces of hx rows along the x walls and hy rows along the y
+  // walls; returns the rows a main block marches over nb main blocks.
+  auto split = [&](long long hx, long long hy, long long& nb) {
+    plan.chunks = static_cast<int>((p.ny + hx - 1) / hx);
+    plan.y0 = p.per_y ? 0 : static_cast<int>(std::max<long long>(2 * kHalo, hy));
+    plan.rows = p.per_y ? p.ny : p.ny - 2 * plan.y0;
+    if (plan.rows < 1) {  // few rows: the bottom pieces take them all
+      plan.y0 = p.ny;
+      plan.rows = 0;
     }
-    if (wbest * 100 < w0 * 97) nb = best;
+    const int pieces = plan.edge * plan.chunks + (p.per_y ? 0 : 2 * plan.nunits);
+    plan.frame = (pieces + 7) / 8 * 8;
+    nb = slots - plan.frame;
+    const long long rows = static_cast<long long>(plan.nunits) * plan.rows;
+    return nb < 8 ? -1 : (rows + nb - 1) / nb + kPairPieceWork;
+  };
+  long long nb = slots;
+  if (forced) {
+    split(17, 17, nb);
+    nb = std::atoll(forced);
+  } else {
+    long long work = 0;
+    for (long long t = kPairMinWork;; ++t) {
+      if (t > p.ny + kPairPieceWork) return 0;
+      auto rows = [&](double cost) {
+        return std::max<long long>(2 * kHalo, static_cast<long long>(t / cost) - kPairPieceWork);
+      };
+      work = split(rows(kPairEdgeCost), rows(kPairTopCost), nb);
+      if (work >= 0 && work <= t) break;
+    }
+    if (work < kPairMinWork) return 0;
   }
-  p.nblocks = static_cast<int>(nb);
-  // The blocks of neighbouring units in a band march the same rows at the
-  // same time, so the halo lines they share are fetched once.
-  p.band = band_of(p.nunits, p.ny, nb);
-  return static_cast<int>(nb);
+  if (static_cast<long long>(plan.nunits) * plan.rows == 0) {
+    plan.nblocks = 0;
+    plan.band = 1;
+    return forced ? plan.frame : 0;
+  }
+  return plan.frame + set_blocks(plan, plan.rows, nb, forced != nullptr, kPairPieceWork);
 }
 
 }  // namespace
@@ -248,9 +356,9 @@ struct t2s2_ctx {
   int nx = 0, ny = 0;
   long long pitch = 0;
   double dt = 0, tau = 0, omega = 0;
-  std::vector<double> wx, wy, jx, jy;
+  std::vector<double> wx, wy, wy16, jx, jy;
   std::vector<float> wx32, wy32;
-  size_t off_wx = 0, off_wy = 0, off_wx32 = 0, off_wy32 = 0, off_jx = 0, off_jy = 0,
+  size_t off_wx = 0, off_wy = 0, off_wy16 = 0, off_wx32 = 0, off_wy32 = 0, off_jx = 0, off_jy = 0,
          off_part = 0, off_res = 0, ws_bytes = 0;
   void* state[2] = {nullptr, nullptr};
   char* ws = nullptr;
@@ -266,6 +374,9 @@ struct t2s2_ctx {
   // and tile_step_kernel; equal to sp unless sp.single.
   StepParams sp_gen{};
   int grid_gen = 0;
+  // Plan of the two-step kernel; grid_pair 0: this context does not take it.
+  PairPlan pair{};
+  int grid_pair = 0;
   // adjoint
   AdjParams adj{};
   bool adj_bound = false;
@@ -491,6 +602,7 @@ int t2s2_create(const t2s2_config* cfg, const double* x, int nx, const double* y
 
   c->wx = stencil_weights(metric(xs, cfg->periodic_x, cfg->period_x), cfg->periodic_x, cfg->eta, dt);
   c->wy = stencil_weights(metric(ys, cfg->periodic_y, cfg->period_y), cfg->periodic_y, cfg->eta, dt);
+  c->wy16 = scatter_weights(c->wy, ny, cfg->periodic_y);
   c->wx32.assign(c->wx.begin(), c->wx.end());
   c->wy32.assign(c->wy.begin(), c->wy.end());
   c->jx = measure(xs, cfg->periodic_x, cfg->period_x);
@@ -510,6 +622,8 @@ int t2s2_create(const t2s2_config* cfg, const double* x, int nx, const double* y
   off = align256(off + c->wx.size() * sizeof(double));
   c->off_wy = off;
   off = align256(off + c->wy.size() * sizeof(double));
+  c->off_wy16 = off;
+  off = align256(off + c->wy16.size() * sizeof(double));
   c->off_wx32 = off;
   off = align256(off + c->wx32.size() * sizeof(float));
   c->off_wy32 = off;
@@ -565,6 +679,7 @@ int t2s2_bind(t2s2_ctx* c, void* state_a, void* state_b, void* workspace, void* 
     size_t bytes;
   } up[] = {{c->off_wx, c->wx.data(), c->wx.size() * sizeof(double)},
             {c->off_wy, c->wy.data(), c->wy.size() * sizeof(double)},
+            {c->off_wy16, c->wy16.data(), c->wy16.size() * sizeof(double)},
             {c->off_wx32, c->wx32.data(), c->wx32.size() * sizeof(float)},
             {c->off_wy32, c->wy32.data(), c->wy32.size() * sizeof(float)},
             {c->off_jx, c->jx.data(), c->jx.size() * sizeof(double)},
@@ -577,6 +692,7 @@ int t2s2_bind(t2s2_ctx* c, void* state_a, void* state_b, void* workspace, void* 
   if (e != hipSuccess) return hip_fail(e, "bind: synchronize");
   c->sp.wx = reinterpret_cast<const double*>(c->ws + c->off_wx);
   c->sp.wy = reinterpret_cast<const double*>(c->ws + c->off_wy);
+  c->pair.wy16 = reinterpret_cast<const double*>(c->ws + c->off_wy16);
   c->sp.wx32 = reinterpret_cast<const float*>(c->ws + c->off_wx32);
   c->sp.wy32 = reinterpret_cast<const float*>(c->ws + c->off_wy32);
   c->ap.jx = reinterpret_cast<const double*>(c->ws + c->off_jx);
@@ -608,11 +724,41 @@ int t2s2_bind(t2s2_ctx* c, void* state_a, void* state_b, void* workspace, void* 
       static_cast<long long>(c->sp.nunits) * c->ny < static_cast<long long>(kTileMaxMarchRows) * c->grid)
     c->sp.tile = 1;
   if (!c->sp.single) c->sp_gen = c->sp;
+  c->grid_pair = 0;
+  if (c->cfg.storage == T2S2_F64 && c->sp.scheme == 1 && !c->sp.single &&
+      !std::getenv("T2S2_BLOCKS")) {
+    c->grid_pair = plan_pair(c->sp, c->pair, cus);
+  }
   if (c->grid < 1 || c->grid_gen < 1) return fail(T2S2_ERR_HIP, "bind: step kernel cannot be resident");
   c->bound = true;
   c->cur = 0;
   c->steps = 0;
   return T2S2_OK;
+}
+
+// Launches nsteps steps from buffer cur, which ends as the buffer that holds
+// the result.  Where the two-step kernel applies, four steps at a time go as
+// two launches of it, which end in the buffer they began in, as four single
+// steps do.
+static hipError_t launch_steps(t2s2_ctx* c, int64_t nsteps, int& cur, int64_t* taken) {
+  const int64_t pairs = c->grid_pair > 0 ? 2 * (nsteps / 4) : 0;
+  for (int64_t k = 0; k < pairs; ++k) {
+    c->sp.src = c->state[cur];
+    c->sp.dst = c->state[1 - cur];
+    const hipError_t e = launch_pair_step(c->sp, c->pair, c->grid_pair, c->stream);
+    if (e != hipSuccess) return e;
+    cur = 1 - cur;
+    if (taken) *taken += 2;
+  }
+  for (int64_t k = 2 * pairs; k < nsteps; ++k) {
+    c->sp.src = c->state[cur];
+    c->sp.dst = c->state[1 - cur];
+    const hipError_t e = launch_step(c->cfg.storage, c->sp, c->grid, c->stream);
+    if (e != hipSuccess) return e;
+    cur = 1 - cur;
+    if (taken) ++*taken;
+  }
+  return hipSuccess;
 }
 
 int t2s2_init_macro(t2s2_ctx* c, const double* rho, const double* ux, const double* uy,
@@ -646,14 +792,8 @@ int t2s2_step(t2s2_ctx* c, int64_t nsteps) {
   if (!c) return fail(T2S2_ERR_INVALID_ARG, "NULL context");
   if (!c->bound) return fail(T2S2_ERR_NOT_BOUND, "context not bound");
   if (nsteps < 0) return fail(T2S2_ERR_INVALID_ARG, "nsteps < 0");
-  for (int64_t k = 0; k < nsteps; ++k) {
-    c->sp.src = c->state[c->cur];
-    c->sp.dst = c->state[1 - c->cur];
-    hipError_t e = launch_step(c->cfg.storage, c->sp, c->grid, c->stream);
-    if (e != hipSuccess) return hip_fail(e, "step");
-    c->cur = 1 - c->cur;
-    ++c->steps;
-  }
+  const hipError_t e = launch_steps(c, nsteps, c->cur, &c->steps);
+  if (e != hipSuccess) return hip_fail(e, "step");
   return T2S2_OK;
 }
 
@@ -671,14 +811,7 @@ int t2s2_graph_capture(t2s2_ctx* c, int steps_per_graph) {
   // Record the launches of steps_per_graph steps; nothing executes, so the
   // host-side buffer index is advanced on a copy only.
   int cur = c->cur;
-  hipError_t le = hipSuccess;
-  for (int k = 0; k < steps_per_graph && le == hipSuccess; ++k) {
-    StepParams sp = c->sp;
-    sp.src = c->state[cur];
-    sp.dst = c->state[1 - cur];
-    le = launch_step(c->cfg.storage, sp, c->grid, c->stream);
-    cur = 1 - cur;
-  }
+  const hipError_t le = launch_steps(c, steps_per_graph, cur, nullptr);
   hipGraph_t g = nullptr;
   e = hipStreamEndCapture(c->stream, &g);
   if (le != hipSuccess || e != hipSuccess) {

@@ -22,6 +22,20 @@ __host__ __device__ constexpr double w_of(int q) {
   return q == 0 ? 4.0 / 9.0 : (q < 5 ? 1.0 / 9.0 : 1.0 / 36.0);
 }
 
+// a b + c.  FP64: in one rounding, so that every kernel rounds a node's
+// values the same way (of a sum of two products the compiler may fuse
+// either).  FP32: left to the compiler, whose choice is the same in every
+// kernel of the reduced forms.
+__device__ inline double fma_of(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ inline float fma_of(float a, float b, float c) { return a * b + c; }
+
+// a b + c with c in the arithmetic type and a, b FP64 parameters: FP64 in
+// one rounding, FP32 with the product rounded first.
+__device__ inline double add_scaled(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ inline float add_scaled(double a, double b, float c) {
+  return c + static_cast<float>(a * b);
+}
+
 template <typename S>
 struct Cvt;
 template <>
@@ -316,7 +330,11 @@ __host__ __device__ constexpr int wclass(int q) { return q == 0 ? 0 : (q < 5 ? 1
 // moment sums.  FP64 arithmetic divides in FP64.  FP32 arithmetic rounds
 // the sums to FP32 and multiplies by the hardware reciprocal of rho refined
 // by one Newton step.
+// (FP64: no contraction here and in eq_brackets; x and y enter sums, and
+// whether the compiler fuses their products into those differs between
+// kernels.)
 __device__ inline void velocity(double s, double jx, double jy, double& r, double& x, double& y) {
+#pragma clang fp contract(off)
   r = 1.0 + s;
   const double ir = recip(r);
   x = jx * ir;
@@ -333,14 +351,27 @@ __device__ inline void velocity(double s, double jx, double jy, float& r, float&
 // Brackets X_q of the equilibrium, f^eq_q - w_q = w_q (drho + rho X_q) with
 // X_q = 3 e_q + 9/2 e_q^2 - 3/2 |u|^2 and e_q = xi_q . u (eq 3.2, c_s^2 =
 // 1/3).  Opposite directions share 9/2 e^2 - 3/2 |u|^2.
-template <typename Real>
-__device__ inline void eq_brackets(Real x, Real y, Real X[kQ]) {
-  const Real uu = Real(1.5) * (x * x + y * y);
+__device__ inline void eq_brackets(double x, double y, double X[kQ]) {
+#pragma clang fp contract(off)
+  const double uu = 1.5 * fma_of(x, x, y * y);
   X[0] = -uu;
-  auto pair = [&](Real e, int qp, int qm) {
-    const Real T = (Real(4.5) * e) * e - uu;
-    X[qp] = T + Real(3) * e;
-    X[qm] = T - Real(3) * e;
+  auto pair = [&](double e, int qp, int qm) {
+    const double T = fma_of(4.5 * e, e, -uu);
+    X[qp] = fma_of(3.0, e, T);
+    X[qm] = fma_of(-3.0, e, T);
+  };
+  pair(x, 1, 3);
+  pair(y, 2, 4);
+  pair(x + y, 5, 7);
+  pair(y - x, 6, 8);
+}
+__device__ inline void eq_brackets(float x, float y, float X[kQ]) {
+  const float uu = float(1.5) * (x * x + y * y);
+  X[0] = -uu;
+  auto pair = [&](float e, int qp, int qm) {
+    const float T = (float(4.5) * e) * e - uu;
+    X[qp] = T + float(3) * e;
+    X[qm] = T - float(3) * e;
   };
   pair(x, 1, 3);
   pair(y, 2, 4);
@@ -356,25 +387,24 @@ __device__ inline void nee_shift(double rho, double uxf, double uyf, double uxb,
   const Real r = static_cast<Real>(rho);
   const Real xf = static_cast<Real>(uxf), yf = static_cast<Real>(uyf);
   const Real xb = static_cast<Real>(uxb), yb = static_cast<Real>(uyb);
-  const Real uuf = Real(1.5) * (xf * xf + yf * yf), uub = Real(1.5) * (xb * xb + yb * yb);
+  const Real uuf = Real(1.5) * fma_of(xf, xf, yf * yf);
+  const Real uub = Real(1.5) * fma_of(xb, xb, yb * yb);
 #pragma unroll
   for (int q = 0; q < kQ; ++q) {
     const Real ef = Real(ex_of(q)) * xf + Real(ey_of(q)) * yf;
     const Real eb = Real(ex_of(q)) * xb + Real(ey_of(q)) * yb;
-    const Real Xf = ef * (Real(3) + Real(4.5) * ef) - uuf;
-    const Real Xb = eb * (Real(3) + Real(4.5) * eb) - uub;
+    const Real Xf = fma_of(ef, Real(3) + Real(4.5) * ef, -uuf);
+    const Real Xb = fma_of(eb, Real(3) + Real(4.5) * eb, -uub);
     out[q] = Real(w_of(q)) * r * (Xb - Xf);
   }
 }
 
-// f^eq(rho, u_b) - f^eq(rho, u_f) of eq 3.10 for q >= 1 from the brackets
-// Xf of the fluid node's velocity (eq_brackets) and Xb of the wall's
-// (StepParams::xb): w_q rho (Xb_q - Xf_q).  out[0] is not formed.
+// The wall node's R_q of eq 3.10: R_q + f^eq_q(rho, u_b) - f^eq_q(rho, u_f)
+// from the brackets Xf of the fluid node's velocity (eq_brackets) and Xb of
+// the wall's (StepParams::xb), R_q + w_q rho (Xb_q - Xf_q), wr = w_q rho.
 template <typename Real>
-__device__ inline void nee_shift_x(Real rho, const Real (&Xf)[kQ], const Real* Xb, Real out[kQ]) {
-  const Real r1 = Real(w_of(1)) * rho, r2 = Real(w_of(5)) * rho;
-#pragma unroll
-  for (int q = 1; q < kQ; ++q) out[q] = (wclass(q) == 1 ? r1 : r2) * (Xb[q] - Xf[q]);
+__device__ __forceinline__ Real nee_r(Real wr, Real Xf, Real Xb, Real Rf) {
+  return fma_of(wr, Xb - Xf, Rf);
 }
 
 // The wall whose node (i + dx, j + dy) is extrapolated from the fluid node

@@ -58,6 +58,10 @@ __host__ __device__ constexpr int step_threads(int storage, int scheme) {
   return kBlockThreads * strips_per_block(storage, scheme);
 }
 
+// Columns of output of a strip of the two-step kernel (8 columns of halo
+// each side).
+constexpr int kPairOut = kLanes - 4 * kHalo;
+
 struct StepParams {
   const void* src;
   void* dst;
@@ -123,6 +127,21 @@ struct StepParams {
   Coef<float> c32;
 };
 
+// Plan of the two-step kernel (its own argument: StepParams goes with every
+// launch of the single-step kernels, whose time on small meshes grows with
+// its size).  The main pieces cover nunits strips from column x0 and rows
+// rows from row y0, cut into nblocks ranges and bands like StepParams'; the
+// frame of a walled mesh around them takes the grid's first `frame` blocks,
+// chunks pieces of each of the `edge` strips along the x walls, then the
+// bottom and top of each main strip.
+struct PairPlan {
+  int x0, y0, rows, nunits, nblocks, band, frame, edge, chunks;
+  // [ny][16]: row r's own y weights, then those with which the values of row
+  // r enter the outputs around it (taps k = 0..3 of the outputs r+2 .. r-1
+  // for a positive y velocity, of r+1 .. r-2 for a negative one).
+  const double* wy16;
+};
+
 struct AuxParams {
   int nx, ny;
   long long pitch, plane;
@@ -180,6 +199,10 @@ constexpr int kAdjMaxBlocks = 1024;
 // Launchers (t2s2_kernels.hip).  Return hipError_t of the launch.
 hipError_t launch_step(int storage, const StepParams& p, int grid, hipStream_t s);
 hipError_t launch_step_save_s(int storage, const StepParams& p, int grid, hipStream_t s);
+// Two time steps from p.src to p.dst (t2s2_pair.hip): FP64 storage, scheme 1
+// with A > 0, strips of kPairOut columns.
+hipError_t launch_pair_step(const StepParams& p, const PairPlan& plan, int grid, hipStream_t s);
+int pair_blocks_per_cu(bool force, bool walls);
 // Resident step-kernel blocks per CU for this variant (-1 on error); scheme
 // 0 is the single-stencil (A = 0) kernel, 4 the family (scheme 3) with
 // collision weights other than (1/2, 0, 1/2).

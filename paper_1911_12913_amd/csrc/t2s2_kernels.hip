@@ -25,6 +25,7 @@
 
 #include "t2s2_device.h"
 #include "t2s2_internal.h"
+#include "t2s2_step.h"
 
 namespace t2s2 {
 namespace {
@@ -32,167 +33,6 @@ namespace {
 // ---------------------------------------------------------------------------
 // Fused step.
 // ---------------------------------------------------------------------------
-// The row weights are the same for the whole wave: read them through the
-// constant address space at a wave-uniform index so they become scalar loads
-// (counted by lgkmcnt).  A vector load here would be waited for with the
-// in-order vmcnt counter and so drain the row prefetches in flight.
-template <typename Real>
-__device__ inline void row_weights(const Real* table, int row, Real out[kWeightsPerNode]) {
-  using CPtr = const __attribute__((address_space(4))) Real*;
-  const int r = __builtin_amdgcn_readfirstlane(row);
-  CPtr w = (CPtr)(table) + r * kWeightsPerNode;
-#pragma unroll
-  for (int k = 0; k < kWeightsPerNode; ++k) out[k] = w[k];
-}
-
-
-// Element at a 32-bit byte offset from a plane base: the row offset is
-// formed once per row in 32 bits and shared by the nine planes.  Every
-// population plane is under 4 GiB (checked when the context is created).
-template <typename T>
-__device__ inline const T* at_byte(const T* base, unsigned boff) {
-  return reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + boff);
-}
-template <typename T>
-__device__ inline T* at_byte(T* base, unsigned boff) {
-  return reinterpret_cast<T*>(reinterpret_cast<char*>(base) + boff);
-}
-
-// The nine new values of one interior node at byte offset boff of each
-// plane: rounded to nearest even, or, for the stochastic forms, by
-// round_node_sr with the node's offset as its position.  FP64 rows (448
-// bytes per wave) go out as non-temporal (streaming) stores: the state is
-// not read again in this launch, and they reach HBM faster than write-back
-// stores.  The narrower FP32 and 16-bit rows (224 and 112 bytes, not
-// line-aligned) merge better in L2 and use ordinary stores (measured: FP32
-// 5% faster so).
-template <typename Store>
-__device__ inline void store_node(Store* dst, long long plane, unsigned boff,
-                                  const typename Cvt<Store>::R (&out)[kQ]) {
-  constexpr bool kNt = std::is_same<Store, double>::value;
-  Store r[kQ];
-  if constexpr (kStochastic<Store>) {
-    round_node_sr(out, boff, r);
-  } else {
-#pragma unroll
-    for (int q = 0; q < kQ; ++q) r[q] = Cvt<Store>::st(out[q]);
-  }
-  store_planes<kNt>(dst, plane * sizeof(Store), boff, r);
-}
-
-// Row index brought into [0, n) by whole periods; the rows a piece touches
-// lie within a few rows of the grid, so this loops at most a few times.
-__device__ inline int wrap_near(int i, int n) {
-  while (i < 0) i += n;
-  while (i >= n) i -= n;
-  return i;
-}
-
-// acc + sum_k w[k] v(lane + offset_k) for the 4 taps of the mixed difference
-// along x: offsets (-2,-1,0,+1) for a positive velocity component (sx = 0),
-// (-1,0,+1,+2) for a negative one (sx = 1); the neighbours come from the
-// centre values of the other lanes.
-template <int sx, typename Real>
-__device__ inline Real x_taps(const Real* w, Real centre, Real acc) {
-  const Real m1 = from_below(centre), p1 = from_above(centre);
-  if (sx == 0) {
-    const Real m2 = from_below(m1);
-    acc += w[0] * m2;
-    acc += w[1] * m1;
-    acc += w[2] * centre;
-    acc += w[3] * p1;
-  } else {
-    const Real p2 = from_above(p1);
-    acc += w[4] * m1;
-    acc += w[5] * centre;
-    acc += w[6] * p1;
-    acc += w[7] * p2;
-  }
-  return acc;
-}
-
-// Guo force term (eq 3.12) of direction q from E = (f^eq_q - w_q) / w_q:
-// F_q = 3 (F . (xi_q - u)) f^eq_q with f^eq_q = w_q (1 + E).
-template <typename Real>
-__device__ inline Real force_term(int q, const StepParams& p, Real ux, Real uy, Real E) {
-  const Real fu = static_cast<Real>(p.Fx) * (Real(ex_of(q)) - ux) +
-                  static_cast<Real>(p.Fy) * (Real(ey_of(q)) - uy);
-  return Real(3.0 * w_of(q)) * fu * (Real(1) + E);
-}
-
-// Wall nodes of the new state (eq 3.10),
-//   f~_b = f~_f + f^eq(rho_f, u_b) - f^eq(rho_f, u_f),
-// from the moments of the stored new state at the nearest interior node f
-// (diagonal at the corners), u_f with the force shift of eq 3.3.  Run by a
-// strip's threads after its piece [y0, y1) has been marched and the block
-// has passed a barrier: the sources are the nodes next to a wall among the
-// piece's outputs (columns [x0, x1)), which this block has just stored, so
-// the loads see them (the coherence point is L2; the buffer was not read
-// earlier in the launch).  Each wall node has exactly one source node, and
-// each source node is output by exactly one piece.
-template <typename Store>
-__device__ inline void piece_walls(const StepParams& p, Store* dst, int x0, int x1, int y0,
-                                   int y1, int tid, int nthreads) {
-  using Real = typename Cvt<Store>::R;
-  const int nx = p.nx, ny = p.ny;
-  // Interior output columns and rows of this strip-piece.
-  const int cx0 = p.per_x ? x0 : max(x0, 1), cx1 = p.per_x ? x1 : min(x1, nx - 1);
-  const int ry0 = p.per_y ? y0 : max(y0, 1), ry1 = p.per_y ? y1 : min(y1, ny - 1);
-  if (cx0 >= cx1 || ry0 >= ry1) return;
-  // Sources: (a) the rows next to the bottom and top walls, every column;
-  // (b) the columns next to the left and right walls, the other rows.
-  const bool rb = !p.per_y && ry0 <= 1 && 1 < ry1;
-  const bool rt = !p.per_y && ry0 <= ny - 2 && ny - 2 < ry1;
-  const bool cl = !p.per_x && cx0 <= 1 && 1 < cx1;
-  const bool cr = !p.per_x && cx0 <= nx - 2 && nx - 2 < cx1;
-  const int ncol = cx1 - cx0;
-  const int nrow_a = (rb ? 1 : 0) + (rt ? 1 : 0);
-  const int nrows_b = (ry1 - ry0) - nrow_a;  // rows not already in (a)
-  const int nsrc = nrow_a * ncol + ((cl ? 1 : 0) + (cr ? 1 : 0)) * nrows_b;
-#pragma unroll 1
-  for (int k = tid; k < nsrc; k += nthreads) {
-    int i, j;
-    if (k < nrow_a * ncol) {
-      j = (k < ncol && rb) ? 1 : ny - 2;
-      i = cx0 + k % ncol;
-    } else {
-      const int kb = k - nrow_a * ncol;
-      i = (kb < nrows_b && cl) ? 1 : nx - 2;
-      // The (kb mod nrows_b)-th row of [ry0, ry1) other than rows 1 and
-      // ny - 2 when those are in (a): row 1 is then ry0, row ny - 2 is ry1 - 1.
-      j = ry0 + (rb ? 1 : 0) + kb % nrows_b;
-    }
-    const long long fb = static_cast<long long>(j) * p.pitch + i;
-    Real v[kQ];
-#pragma unroll
-    for (int q = 0; q < kQ; ++q) v[q] = Cvt<Store>::ld(dst[q * p.plane + fb]);
-    double s, jx, jy;
-    moment_sums(v, s, jx, jy);
-    const double rho = 1.0 + s;
-    const double ir = recip(rho);
-    const double ux = jx * ir + p.half_dt * p.Fx;
-    const double uy = jy * ir + p.half_dt * p.Fy;
-    const bool wl = !p.per_x && i == 1, wr = !p.per_x && i == nx - 2;
-    const bool wb = !p.per_y && j == 1, wt = !p.per_y && j == ny - 2;
-#pragma unroll 1
-    for (int dy = -1; dy <= 1; ++dy) {
-      if ((dy == -1 && !wb) || (dy == 1 && !wt)) continue;
-#pragma unroll 1
-      for (int dx = -1; dx <= 1; ++dx) {
-        if ((dx == -1 && !wl) || (dx == 1 && !wr)) continue;
-        if (dx == 0 && dy == 0) continue;
-        double ub, vb;
-        wall_velocity(p, i + dx, j + dy, ub, vb);
-        Real sh[kQ];
-        nee_shift(rho, ux, uy, ub, vb, sh);
-        const long long wo = static_cast<long long>(j + dy) * p.pitch + (i + dx);
-#pragma unroll
-        for (int q = 0; q < kQ; ++q) dst[q * p.plane + wo] = Cvt<Store>::st(v[q] + sh[q]);
-      }
-    }
-  }
-}
-
 // Resident waves per SIMD the register allocation must allow: the FP64 rings
 // (68 KB per block) admit two blocks per CU; the FP32 rings admit four, which
 // the FP32 / FP16 variants without a force reach without spilling (the force
@@ -397,8 +237,8 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, kScheme), (kMinWave
         Real rho, ux, uy;
         velocity(s, jx, jy, rho, ux, uy);
         if (kForce) {
-          ux += static_cast<Real>(p.half_dt * p.Fx);
-          uy += static_cast<Real>(p.half_dt * p.Fy);
+          ux = add_scaled(p.half_dt, p.Fx, ux);
+          uy = add_scaled(p.half_dt, p.Fy, uy);
         }
         const Real d = static_cast<Real>(s);
         Real X[kQ];
@@ -409,14 +249,14 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, kScheme), (kMinWave
         for (int q = 0; q < kQ; ++q) {
           // E = (f^eq_q - w_q) / w_q; P and Q take their f^eq coefficient
           // times w_q per weight class.
-          const Real E = d + rho * X[q];
-          Real Pq = k.cPg * g[q] + k.kP[wclass(q)] * E;
-          Real Qq = k.cQg * g[q] + k.kQ[wclass(q)] * E;
+          const Real E = fma_of(rho, X[q], d);
+          Real Pq = fma_of(k.cPg, g[q], k.kP[wclass(q)] * E);
+          Real Qq = fma_of(k.cQg, g[q], k.kQ[wclass(q)] * E);
           Real Fq = Real(0);
           if (kForce) {
             Fq = force_term(q, p, ux, uy, E);
-            Pq += static_cast<Real>(p.cPF) * Fq;
-            Qq += static_cast<Real>(p.cQF) * Fq;
+            Pq = fma_of(static_cast<Real>(p.cPF), Fq, Pq);
+            Qq = fma_of(static_cast<Real>(p.cQF), Fq, Qq);
           }
           slotP[q * kLanes + lane] = kScheme == 2 ? Qq : Pq;
           if (kScheme == 2 && !kFnRegs && q > 0) slotP[(kQ + q - 1) * kLanes + lane] = Pq;
@@ -424,15 +264,15 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, kScheme), (kMinWave
           if (kFamily) {
             slotP[(kQ + q) * kLanes + lane] = Qq;
             if (q > 0) {
-              Real Uq = k.cU * g[q] + k.kU[wclass(q)] * E;  // f^n
-              if (kForce) Uq += static_cast<Real>(p.cUF) * Fq;
+              Real Uq = fma_of(k.cU, g[q], k.kU[wclass(q)] * E);  // f^n
+              if (kForce) Uq = fma_of(static_cast<Real>(p.cUF), Fq, Uq);
               slotP[(2 * kQ + q - 1) * kLanes + lane] = Uq;
             }
           }
           qnew[q] = Qq;
           if constexpr (gen_bbar) {  // Q2 = f^n + B-0 dt Omega(f^n)
-            Real Q2 = k.cQ2g * g[q] + k.kQ2[wclass(q)] * E;
-            if (kForce) Q2 += static_cast<Real>(p.cQ2F) * Fq;
+            Real Q2 = fma_of(k.cQ2g, g[q], k.kQ2[wclass(q)] * E);
+            if (kForce) Q2 = fma_of(static_cast<Real>(p.cQ2F), Fq, Q2);
             qnew[q] = Q2;
           }
         }
@@ -452,10 +292,10 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, kScheme), (kMinWave
           Real wyr[kWeightsPerNode];
           row_weights(weights_y<Real>(p), rm, wyr);
           // One base pointer per ring row r-2 .. r+2 at this lane.
-          const Real* rb[5];
+          LdsPtr<Real> rb[5];
 #pragma unroll
           for (int o = 0; o < 5; ++o)
-            rb[o] = ringP + ((r + o - 2) & (kRing - 1)) * kNP * kLanes + lane;
+            rb[o] = (LdsPtr<Real>)(ringP + ((r + o - 2) & (kRing - 1)) * kNP * kLanes + lane);
           const auto& k = coef<Real>(p);
           // A prediction along the characteristics from ring planes
           // [base, base + 9): S = centre + fac L(centre); then f at the
@@ -476,38 +316,38 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, kScheme), (kMinWave
               if (ey_of(q) != 0) {
                 const int sy = ey_of(q) > 0 ? 0 : 1;
 #pragma unroll
-                for (int k2 = 0; k2 < kTaps; ++k2) acc += wyr[sy * kTaps + k2] * rb[k2 + sy][pq];
+                for (int k2 = 0; k2 < kTaps; ++k2) acc = fma_of(wyr[sy * kTaps + k2], rb[k2 + sy][pq], acc);
               }
-              S[q] = q == 0 ? centre : centre + fac * acc;
+              S[q] = q == 0 ? centre : fma_of(fac, acc, centre);
             }
             double s, jx, jy;
             moment_sums(S, s, jx, jy);
             velocity(s, jx, jy, rho, ux, uy);
             if (kForce) {
-              ux += static_cast<Real>(hf * p.Fx);
-              uy += static_cast<Real>(hf * p.Fy);
+              ux = add_scaled(hf, p.Fx, ux);
+              uy = add_scaled(hf, p.Fy, uy);
             }
             const Real d = static_cast<Real>(s);
             eq_brackets(ux, uy, X);
             R[0] = Real(0);
 #pragma unroll
             for (int q = 1; q < kQ; ++q) {
-              const Real E = d + rho * X[q];
-              Real Rq = cs * S[q] + ke[wclass(q)] * E;
-              if (kForce) Rq += static_cast<Real>(cf) * force_term(q, p, ux, uy, E);
+              const Real E = fma_of(rho, X[q], d);
+              Real Rq = fma_of(cs, S[q], ke[wclass(q)] * E);
+              if (kForce) Rq = fma_of(static_cast<Real>(cf), force_term(q, p, ux, uy, E), Rq);
               R[q] = Rq;
             }
             if (want_v) {
               // Omega(f*) dt = w (f^eq* - f*) + dt F*, in deviations from w.
 #pragma unroll
               for (int q = 0; q < kQ; ++q) {
-                const Real E = d + rho * X[q];
+                const Real E = fma_of(rho, X[q], d);
                 Real Fq = Real(0);
                 if (kForce) Fq = force_term(q, p, ux, uy, E);
-                Real Rq = cs * S[q] + ke[wclass(q)] * E;
-                if (kForce) Rq += static_cast<Real>(cf) * Fq;
+                Real Rq = fma_of(cs, S[q], ke[wclass(q)] * E);
+                if (kForce) Rq = fma_of(static_cast<Real>(cf), Fq, Rq);
                 Real Vq = k.kV[wclass(q)] * E - k.cV * Rq;
-                if (kForce) Vq += static_cast<Real>(p.cVF) * Fq;
+                if (kForce) Vq = fma_of(static_cast<Real>(p.cVF), Fq, Vq);
                 V[q] = Vq;
               }
             }
@@ -570,16 +410,14 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, kScheme), (kMinWave
                   // The shift from the brackets of u_f, formed above, and
                   // of the wall's velocity.
                   const Real* Xb = wall_brackets<Real>(p, wall_side_of(dx, dy));
-                  Real sh[kQ], sh2[kQ];
-                  nee_shift_x(rho, X, Xb, sh);
-#pragma unroll
-                  for (int q = 0; q < kQ; ++q) sh2[q] = Real(0);
-                  if constexpr (kFamily) nee_shift_x(rho2, X2, Xb, sh2);
+                  const Real r1 = Real(w_of(1)) * rho, r2 = Real(w_of(5)) * rho;
+                  const Real r1b = Real(w_of(1)) * rho2, r2b = Real(w_of(5)) * rho2;
                   Real* slotW = dy == 1 ? topR : ringR + ((r + dy) & (kRing - 1)) * (kQ - 1) * kLanes;
 #pragma unroll
                   for (int q = 1; q < kQ; ++q)
                     slotW[(q - 1) * kLanes + lane + dx] =
-                        t_of(q, r + dy, lane + dx, R[q] + sh[q], R2[q] + sh2[q]);
+                        t_of(q, r + dy, lane + dx, nee_r(wclass(q) == 1 ? r1 : r2, X[q], Xb[q], R[q]),
+                             kFamily ? nee_r(wclass(q) == 1 ? r1b : r2b, X2[q], Xb[q], R2[q]) : R2[q]);
                 }
               }
             }
@@ -596,11 +434,11 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, kScheme), (kMinWave
         if (row_ok) {
           Real wyr[kWeightsPerNode];
           row_weights(weights_y<Real>(p), o, wyr);
-          const Real* rb[5];
+          LdsPtr<Real> rb[5];
 #pragma unroll
           for (int k = 0; k < 5; ++k) {
-            rb[k] = ringR + ((o + k - 2) & (kRing - 1)) * (kQ - 1) * kLanes + lane;
-            if (kWalls && !p.per_y && o + k - 2 == ny - 1) rb[k] = topR + lane;
+            rb[k] = (LdsPtr<Real>)(ringR + ((o + k - 2) & (kRing - 1)) * (kQ - 1) * kLanes + lane);
+            if (kWalls && !p.per_y && o + k - 2 == ny - 1) rb[k] = (LdsPtr<Real>)(topR + lane);
           }
           Real out[kQ];
           // V of this row: formed in this iteration's phase 2 by waves 2
@@ -614,13 +452,13 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, kScheme), (kMinWave
             const Real centre = rb[2][pq];
             Real acc = kScheme == 2 ? Real(0) : qold[q];
             if constexpr (gen_bbar) acc += v_now ? vnew[q] : vold[q];
-            if (ex_of(q) > 0) acc = x_taps<0>(wxr, centre, acc);
-            if (ex_of(q) < 0) acc = x_taps<1>(wxr, centre, acc);
+            const int sy = ey_of(q) > 0 ? 0 : 1;
+            Real rows[kTaps] = {};
             if (ey_of(q) != 0) {
-              const int sy = ey_of(q) > 0 ? 0 : 1;
 #pragma unroll
-              for (int k = 0; k < kTaps; ++k) acc += wyr[sy * kTaps + k] * rb[k + sy][pq];
+              for (int k = 0; k < kTaps; ++k) rows[k] = rb[k + sy][pq];
             }
+            acc = full_taps(q, wxr, wyr, centre, acc, rows);
             out[q] = kScheme == 2 ? qold[q] + Real(0.5) * acc : acc;
           }
           if constexpr (gen_bbar) {
@@ -633,17 +471,17 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, kScheme), (kMinWave
             Real rho, ux, uy;
             velocity(s, jx, jy, rho, ux, uy);
             if (kForce) {
-              ux += static_cast<Real>(p.b2dt * p.Fx);
-              uy += static_cast<Real>(p.b2dt * p.Fy);
+              ux = add_scaled(p.b2dt, p.Fx, ux);
+              uy = add_scaled(p.b2dt, p.Fy, uy);
             }
             const Real d = static_cast<Real>(s);
             Real X[kQ];
             eq_brackets(ux, uy, X);
 #pragma unroll
             for (int q = 0; q < kQ; ++q) {
-              const Real E = d + rho * X[q];
+              const Real E = fma_of(rho, X[q], d);
               Real o = k.aY * out[q] + k.kA[wclass(q)] * E;
-              if (kForce) o += static_cast<Real>(p.aF) * force_term(q, p, ux, uy, E);
+              if (kForce) o = fma_of(static_cast<Real>(p.aF), force_term(q, p, ux, uy, E), o);
               out[q] = o;
             }
           }
@@ -747,25 +585,30 @@ __global__ __launch_bounds__(kTileWaves * kLanes) void tile_step_kernel(StepPara
       Real rho, ux, uy;
       velocity(s, jx, jy, rho, ux, uy);
       if (kForce) {
-        ux += static_cast<Real>(p.half_dt * p.Fx);
-        uy += static_cast<Real>(p.half_dt * p.Fy);
+        ux = add_scaled(p.half_dt, p.Fx, ux);
+        uy = add_scaled(p.half_dt, p.Fy, uy);
       }
       const Real d = static_cast<Real>(s);
       Real X[kQ];
       eq_brackets(ux, uy, X);
       Real* row = tP + j * kQ * kLanes;
+      Real E[kQ], Fq[kQ];
 #pragma unroll
       for (int q = 0; q < kQ; ++q) {
-        const Real E = d + rho * X[q];
-        Real Pq = k.cPg * g[q] + k.kP[wclass(q)] * E;
-        Real Qq = k.cQg * g[q] + k.kQ[wclass(q)] * E;
+        E[q] = fma_of(rho, X[q], d);
+        Real Pq = fma_of(k.cPg, g[q], k.kP[wclass(q)] * E[q]);
         if (kForce) {
-          const Real Fq = force_term(q, p, ux, uy, E);
-          Pq += static_cast<Real>(p.cPF) * Fq;
-          Qq += static_cast<Real>(p.cQF) * Fq;
+          Fq[q] = force_term(q, p, ux, uy, E[q]);
+          Pq = fma_of(static_cast<Real>(p.cPF), Fq[q], Pq);
         }
         row[q * kLanes + lane] = Pq;
-        if (j == jout) qout[q] = Qq;
+      }
+      if (j == jout) {  // uniform per wave
+#pragma unroll
+        for (int q = 0; q < kQ; ++q) {
+          qout[q] = fma_of(k.cQg, g[q], k.kQ[wclass(q)] * E[q]);
+          if (kForce) qout[q] = fma_of(static_cast<Real>(p.cQF), Fq[q], qout[q]);
+        }
       }
     }
   }
@@ -795,9 +638,9 @@ __global__ __launch_bounds__(kTileWaves * kLanes) void tile_step_kernel(StepPara
       if (ey_of(q) != 0) {
         const int sy = ey_of(q) > 0 ? 0 : 1;
 #pragma unroll
-        for (int k2 = 0; k2 < kTaps; ++k2) acc += wyr[sy * kTaps + k2] * rb[k2 + sy][pq];
+        for (int k2 = 0; k2 < kTaps; ++k2) acc = fma_of(wyr[sy * kTaps + k2], rb[k2 + sy][pq], acc);
       }
-      S[q] = q == 0 ? centre : centre + k.A * acc;
+      S[q] = q == 0 ? centre : fma_of(k.A, acc, centre);
     }
     if (kSaveS && lane_o && col_interior && r >= y0 && r < y1) {
       Real* sv = static_cast<Real*>(p.save_s);
@@ -812,8 +655,8 @@ __global__ __launch_bounds__(kTileWaves * kLanes) void tile_step_kernel(StepPara
     Real rho, ux, uy;
     velocity(s, jx, jy, rho, ux, uy);
     if (kForce) {
-      ux += static_cast<Real>(p.half_h * p.Fx);
-      uy += static_cast<Real>(p.half_h * p.Fy);
+      ux = add_scaled(p.half_h, p.Fx, ux);
+      uy = add_scaled(p.half_h, p.Fy, uy);
     }
     const Real d = static_cast<Real>(s);
     Real X[kQ];
@@ -821,9 +664,9 @@ __global__ __launch_bounds__(kTileWaves * kLanes) void tile_step_kernel(StepPara
     R[0] = Real(0);
 #pragma unroll
     for (int q = 1; q < kQ; ++q) {
-      const Real E = d + rho * X[q];
-      Real Rq = k.cRs * S[q] + k.kR[wclass(q)] * E;
-      if (kForce) Rq += static_cast<Real>(p.cRF) * force_term(q, p, ux, uy, E);
+      const Real E = fma_of(rho, X[q], d);
+      Real Rq = fma_of(k.cRs, S[q], k.kR[wclass(q)] * E);
+      if (kForce) Rq = fma_of(static_cast<Real>(p.cRF), force_term(q, p, ux, uy, E), Rq);
       R[q] = Rq;
     }
     if (lane_r && col_interior) {
@@ -842,11 +685,12 @@ __global__ __launch_bounds__(kTileWaves * kLanes) void tile_step_kernel(StepPara
           for (int dx = -1; dx <= 1; ++dx) {
             if ((dx == -1 && !src_xl) || (dx == 1 && !src_xr)) continue;
             if (dx == 0 && dy == 0) continue;
-            Real sh[kQ];
-            nee_shift_x(rho, X, wall_brackets<Real>(p, wall_side_of(dx, dy)), sh);
+            const Real* Xb = wall_brackets<Real>(p, wall_side_of(dx, dy));
+            const Real r1 = Real(w_of(1)) * rho, r2 = Real(w_of(5)) * rho;
             Real* slotW = tR + (m + dy) * (kQ - 1) * kLanes;
 #pragma unroll
-            for (int q = 1; q < kQ; ++q) slotW[(q - 1) * kLanes + lane + dx] = R[q] + sh[q];
+            for (int q = 1; q < kQ; ++q)
+              slotW[(q - 1) * kLanes + lane + dx] = nee_r(wclass(q) == 1 ? r1 : r2, X[q], Xb[q], R[q]);
           }
         }
       }
@@ -871,14 +715,13 @@ __global__ __launch_bounds__(kTileWaves * kLanes) void tile_step_kernel(StepPara
         const int pq = (q - 1) * kLanes;
         const Real centre = rb[2][pq];
         Real acc = qout[q];
-        if (ex_of(q) > 0) acc = x_taps<0>(wxr, centre, acc);
-        if (ex_of(q) < 0) acc = x_taps<1>(wxr, centre, acc);
+        const int sy = ey_of(q) > 0 ? 0 : 1;
+        Real rows[kTaps] = {};
         if (ey_of(q) != 0) {
-          const int sy = ey_of(q) > 0 ? 0 : 1;
 #pragma unroll
-          for (int k2 = 0; k2 < kTaps; ++k2) acc += wyr[sy * kTaps + k2] * rb[k2 + sy][pq];
+          for (int k2 = 0; k2 < kTaps; ++k2) rows[k2] = rb[k2 + sy][pq];
         }
-        out[q] = acc;
+        out[q] = full_taps(q, wxr, wyr, centre, acc, rows);
       }
       if (lane_o && col_interior) {
         const unsigned boff =
@@ -1012,8 +855,8 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, 0), (kMinWaves<Stor
         Real rho, ux, uy;
         velocity(s, jx, jy, rho, ux, uy);
         if (kForce) {
-          ux += static_cast<Real>(p.half_dt * p.Fx);
-          uy += static_cast<Real>(p.half_dt * p.Fy);
+          ux = add_scaled(p.half_dt, p.Fx, ux);
+          uy = add_scaled(p.half_dt, p.Fy, uy);
         }
         const Real d = static_cast<Real>(s);
         Real X[kQ];
@@ -1022,13 +865,13 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, 0), (kMinWaves<Stor
         Real R[kQ];
 #pragma unroll
         for (int q = 0; q < kQ; ++q) {
-          const Real E = d + rho * X[q];
-          Real Rq = k.cPg * g[q] + k.kP[wclass(q)] * E;
-          Real Qq = k.cQg * g[q] + k.kQ[wclass(q)] * E;
+          const Real E = fma_of(rho, X[q], d);
+          Real Rq = fma_of(k.cPg, g[q], k.kP[wclass(q)] * E);
+          Real Qq = fma_of(k.cQg, g[q], k.kQ[wclass(q)] * E);
           if (kForce) {
             const Real Fq = force_term(q, p, ux, uy, E);
-            Rq += static_cast<Real>(p.cPF) * Fq;
-            Qq += static_cast<Real>(p.cQF) * Fq;
+            Rq = fma_of(static_cast<Real>(p.cPF), Fq, Rq);
+            Qq = fma_of(static_cast<Real>(p.cQF), Fq, Qq);
           }
           R[q] = Rq;
           qnew[q] = Qq;
@@ -1057,11 +900,12 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, 0), (kMinWaves<Stor
                 // A source in the strip's edge lane has its wall node outside
                 // the strip; no output of this strip reads it.
                 if (lane + dx < 0 || lane + dx >= kLanes) continue;
-                Real sh[kQ];
-                nee_shift_x(rho2, X2, wall_brackets<Real>(p, wall_side_of(dx, dy)), sh);
+                const Real* Xb = wall_brackets<Real>(p, wall_side_of(dx, dy));
+                const Real r1 = Real(w_of(1)) * rho2, r2 = Real(w_of(5)) * rho2;
                 Real* slotW = ringR + ((pr + dy) & (kRing1 - 1)) * (kQ - 1) * kLanes;
 #pragma unroll
-                for (int q = 1; q < kQ; ++q) slotW[(q - 1) * kLanes + lane + dx] = R[q] + sh[q];
+                for (int q = 1; q < kQ; ++q)
+                  slotW[(q - 1) * kLanes + lane + dx] = nee_r(wclass(q) == 1 ? r1 : r2, X2[q], Xb[q], R[q]);
               }
             }
           }
@@ -1088,14 +932,13 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, 0), (kMinWaves<Stor
             const int pq = (q - 1) * kLanes;
             const Real centre = rb[2][pq];
             Real acc = qold[q];
-            if (ex_of(q) > 0) acc = x_taps<0>(wxr, centre, acc);
-            if (ex_of(q) < 0) acc = x_taps<1>(wxr, centre, acc);
+            const int sy = ey_of(q) > 0 ? 0 : 1;
+            Real rows[kTaps] = {};
             if (ey_of(q) != 0) {
-              const int sy = ey_of(q) > 0 ? 0 : 1;
 #pragma unroll
-              for (int k = 0; k < kTaps; ++k) acc += wyr[sy * kTaps + k] * rb[k + sy][pq];
+              for (int k = 0; k < kTaps; ++k) rows[k] = rb[k + sy][pq];
             }
-            out[q] = acc;
+            out[q] = full_taps(q, wxr, wyr, centre, acc, rows);
           }
           if (lane_o && col_interior) {
             const unsigned boff =

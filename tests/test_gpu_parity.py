@@ -929,3 +929,54 @@ def test_tile_kernel_is_bitwise_the_march(kind, storage, monkeypatch):
     assert np.array_equal(g_tile, g_march)
     if storage == "f64":
         _compare(case, g_tile, d, u, v, oracle.run(case, phi0, 60))
+
+
+# --------------------------- two steps per launch (FP64, scheme 1, A > 0)
+
+def _pair_case(kind):
+    if kind == "tgv97x33":  # three 48-column strips across the seam, the last ragged
+        return W.tgv_case(97, 33, u0=0.02, nu=0.05, cfl=0.7, eta=0.05)
+    if kind == "tgv5x7":  # wraps several times within a strip and a piece
+        return W.tgv_case(5, 7, u0=0.02, nu=0.05, cfl=0.7, eta=0.05)
+    if kind == "tgv_forced":
+        case = W.tgv_case(150, 70, u0=0.02, nu=0.05, cfl=0.7, eta=0.05)
+        case.force = (1e-3, -2e-3)
+        return case
+    if kind == "cavity5":  # nothing but frame
+        return W.cavity_case(4, lid=0.1, re=100.0, cfl=0.5, eta=0.1, noise=1e-4, seed=5)
+    if kind == "cavity50":  # a right edge strip of two columns
+        return W.cavity_case(49, lid=0.1, re=400.0, cfl=0.9, eta=0.1, noise=1e-6, seed=0)
+    if kind == "cavity145":  # one main strip; every wall moving
+        case = W.cavity_case(144, lid=0.1, re=400.0, cfl=0.8, eta=0.1, noise=1e-5, seed=4)
+        case.u_wall[:] = np.array([[0.002, 0.03], [-0.001, -0.02], [0.025, 0.003], [0.1, -0.002]])
+        return case
+    if kind == "channel":  # force, walls on y only
+        return W.poiseuille_case(dt_over_y1=0.9, eta=0.1)
+    c = W.couette_case(70, 30)  # walls on x only
+    return W.Case(name="couette_x", x=c.y, y=c.x, periodic_x=False, periodic_y=True,
+                  period_x=0.0, period_y=1.0, nu=c.nu, cfl=c.cfl, eta=c.eta,
+                  u_wall=np.array([[0, 0], [0.003, 0.02], [0, 0], [0, 0.0]]),
+                  rho0=np.ones((70, 31)), ux0=np.zeros((70, 31)), uy0=np.zeros((70, 31)))
+
+
+@pytest.mark.parametrize("kind", ["tgv97x33", "tgv5x7", "tgv_forced", "cavity5", "cavity50",
+                                  "cavity145", "channel", "couette_x"])
+def test_two_step_kernel_is_bitwise_single_steps(kind, monkeypatch):
+    """The kernel that takes two time steps per launch (chosen on large FP64
+    meshes, forced here with T2S2_PAIR_BLOCKS), at several block counts,
+    gives bitwise the state of single steps of the march, after a number of
+    steps that is and one that is not a multiple of four (the rest are single
+    steps), and matches the oracle."""
+    case = _pair_case(kind)
+    phi0 = oracle.init(case) + W.random_state((9, case.ny, case.nx), 1e-5, 8)
+    for n in (4, 11):
+        monkeypatch.delenv("T2S2_PAIR_BLOCKS", raising=False)
+        monkeypatch.setenv("T2S2_BLOCKS", "8")
+        _, g_single, *_ = _gpu_run(case, phi0, n)
+        monkeypatch.delenv("T2S2_BLOCKS")
+        for blocks in ("8", "24", "64"):
+            monkeypatch.setenv("T2S2_PAIR_BLOCKS", blocks)
+            ctx, g, d, u, v = _gpu_run(case, phi0, n)
+            assert ctx.current == n % 2 and ctx.steps_taken == n
+            assert np.array_equal(g, g_single)
+        _compare(case, g, d, u, v, oracle.run(case, phi0, n))
