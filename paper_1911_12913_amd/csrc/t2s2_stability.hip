@@ -26,11 +26,24 @@
 // the exponentials).  The advection symbol multiplies from the left (it
 // acts on the population it advects).
 //
-// One wave per map point walks the k grid; the matrices live in LDS.  The
-// spectral radius is lim ||G^m||^(1/m), taken at m = 2^J by J normalised
-// squarings (the log of each normalisation is accumulated), in FP64.
+// The spectral radius is lim ||G^m||^(1/m), taken at m = 2^J by J squarings
+// in FP64, the matrix scaled by powers of two (exact) as it goes.
+//
+// A block is one wave that takes every nchunks-th mode of one map point, 21
+// modes at a time: three lanes per mode, three rows of its matrix in the
+// registers of each, and a copy of the matrix in LDS whose elements the three
+// lanes read together, so each 16-byte LDS read feeds 12 multiply-adds per
+// lane and the squaring is bound by the FP64 units.  A mode stops as soon as
+// it cannot be the largest: rho(G) <= ||G^n||_F^(1/n) for every n, so once
+// that bound at n = 2^s lies below a radius already found at this point
+// (|k| = 0 goes first, and other blocks' results are read), the rest of its
+// squarings cannot change the maximum.  Measured, 30 squarings x 561
+// modes, one wave per point and every squaring before -> now: the step's
+// models 23.3 -> 0.80 ms (256 points), 24.5 -> 1.85 ms (1024); eq 4.7, whose
+// elimination takes the whole wave per mode, 27.0 -> 2.4 and 28.4 -> 6.9 ms.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 
 #include "t2s2_device.h"
@@ -55,6 +68,7 @@ __device__ inline cplx cdiv(cplx a, cplx b) {
 }
 
 constexpr int kN = 9, kN2 = 81;
+constexpr int kWantedBlocks = 2560;
 
 // Gamma_ij = d f^eq_i / d f_j at rho = 1, velocity u (eq 3.2, c_s^2 = 1/3):
 // f^eq depends on f through rho = sum f and m = sum xi f.
@@ -67,18 +81,8 @@ __device__ inline double gamma_ij(int i, int j, double ux, double uy) {
   return d_rho + d_mx * ex_of(j) + d_my * ey_of(j);
 }
 
-// dx * symbol of xi_q . D, mixed difference with upwind weight eta.
-__device__ inline cplx symbol_q(int q, double thx, double thy, double eta) {
-  cplx s{0.0, 0.0};
-  const double th[2] = {thx * ex_of(q), thy * ey_of(q)};
-  for (int a = 0; a < 2; ++a) {
-    const double t = th[a];
-    s.im += (1.0 - eta) * sin(t);
-    s.re += 0.5 * eta * (3.0 - 4.0 * cos(t) + cos(2.0 * t));
-    s.im += 0.5 * eta * (4.0 * sin(t) - sin(2.0 * t));
-  }
-  return s;
-}
+constexpr int kLanesPerMode = 3, kModes = kLanes / kLanesPerMode;  // 21 modes per wave
+constexpr int kRowsPerLane = kN / kLanesPerMode;
 
 // One pass over the (up to two) matrix elements e = lane, lane + 64 of a
 // 9 x 9 matrix.
@@ -88,13 +92,166 @@ __device__ inline void for_elems(int lane, F f) {
   if (lane + 64 < kN2) f((lane + 64) / kN, (lane + 64) % kN);
 }
 
+// dx * symbol of xi_q . D, mixed difference with upwind weight eta, from the
+// sines and cosines of the mode's angles.
+__device__ inline cplx symbol_q(int q, const double (&sn)[2], const double (&cs)[2], double eta) {
+  cplx s{0.0, 0.0};
+  const int e[2] = {ex_of(q), ey_of(q)};
+  for (int a = 0; a < 2; ++a) {
+    const double si = e[a] * sn[a], co = e[a] == 0 ? 1.0 : cs[a];
+    const double s2 = 2.0 * si * co, c2 = 1.0 - 2.0 * si * si;
+    s.im += (1.0 - eta) * si;
+    s.re += 0.5 * eta * (3.0 - 4.0 * co + c2);
+    s.im += 0.5 * eta * (4.0 * si - s2);
+  }
+  return s;
+}
+
+// Eq 4.7: G = lhs^{-1} rhs by Gauss-Jordan elimination with partial
+// pivoting, the whole wave on one mode; G is left in T.
+__device__ inline void solve_paper(const StabArgs& a, int lane, const double* gam,
+                                   const cplx* sym, double w, double r, cplx* X, cplx* T) {
+  const double b2 = a.b2bar, bt = a.b2tilde;
+  for_elems(lane, [&](int i, int j) {
+    const double d = i == j ? 1.0 : 0.0, g = gam[i * kN + j];
+    const cplx rs = cscale(sym[i], r);
+    X[i * kN + j] = cadd({(1 + w * b2) * d + w * (0.5 - 2 * b2) * g, 0.0},
+                         cscale(rs, bt * d + (0.5 - bt) * g));
+    T[i * kN + j] = csub({(1 - w * (1 - b2)) * d + w * (1.5 - 2 * b2) * g, 0.0},
+                         cscale(rs, (1 - bt) * d - (0.5 - bt) * g));
+  });
+  __syncthreads();
+  for (int c = 0; c < kN; ++c) {
+    int piv = c;
+    double pmax = cabs2(X[c * kN + c]);
+    for (int i = c + 1; i < kN; ++i) {
+      const double v = cabs2(X[i * kN + c]);
+      if (v > pmax) {
+        pmax = v;
+        piv = i;
+      }
+    }
+    __syncthreads();
+    if (lane < kN && piv != c) {
+      const cplx x0 = X[c * kN + lane], t0 = T[c * kN + lane];
+      X[c * kN + lane] = X[piv * kN + lane];
+      T[c * kN + lane] = T[piv * kN + lane];
+      X[piv * kN + lane] = x0;
+      T[piv * kN + lane] = t0;
+    }
+    __syncthreads();
+    const cplx p = X[c * kN + c];
+    __syncthreads();
+    if (lane < kN) {
+      X[c * kN + lane] = cdiv(X[c * kN + lane], p);
+      T[c * kN + lane] = cdiv(T[c * kN + lane], p);
+    }
+    __syncthreads();
+    cplx fac[2], xr[2], tr[2];
+    int n = 0;
+    for_elems(lane, [&](int i, int j) {
+      fac[n] = X[i * kN + c];
+      xr[n] = X[c * kN + j];
+      tr[n] = T[c * kN + j];
+      ++n;
+    });
+    __syncthreads();
+    n = 0;
+    for_elems(lane, [&](int i, int j) {
+      if (i != c) {
+        X[i * kN + j] = csub(X[i * kN + j], cmul(fac[n], xr[n]));
+        T[i * kN + j] = csub(T[i * kN + j], cmul(fac[n], tr[n]));
+      }
+      ++n;
+    });
+    __syncthreads();
+  }
+}
+
+using Rows = cplx[kRowsPerLane][kN];
+
+// The lane's rows of a matrix to its mode's LDS copy, for the other lanes.
+// (The fences keep the compiler from moving other lanes' reads across; the
+// block is one wave, so they cost nothing else.)
+__device__ __forceinline__ void publish(cplx* m, int row0, const Rows& x) {
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kRowsPerLane; ++r) {
+#pragma unroll
+    for (int j = 0; j < kN; ++j) m[(row0 + r) * kN + j] = x[r][j];
+  }
+  __syncthreads();
+}
+
+// The lane's rows of Gamma M, M in LDS.
+__device__ __forceinline__ void gamma_times(const double* gam, const cplx* m, int row0, Rows& out) {
+#pragma unroll
+  for (int r = 0; r < kRowsPerLane; ++r) {
+#pragma unroll
+    for (int j = 0; j < kN; ++j) out[r][j] = {0.0, 0.0};
+  }
+#pragma unroll 1
+  for (int k = 0; k < kN; ++k) {
+    double g[kRowsPerLane];
+#pragma unroll
+    for (int r = 0; r < kRowsPerLane; ++r) g[r] = gam[(row0 + r) * kN + k];
+#pragma unroll
+    for (int j = 0; j < kN; ++j) {
+      const cplx b = m[k * kN + j];
+#pragma unroll
+      for (int r = 0; r < kRowsPerLane; ++r) {
+        out[r][j].re = fma(g[r], b.re, out[r][j].re);
+        out[r][j].im = fma(g[r], b.im, out[r][j].im);
+      }
+    }
+  }
+}
+
+// The lane's rows of X M, X the lane's rows of M and M in LDS.
+__device__ __forceinline__ void square(const cplx* m, const Rows& x, Rows& out) {
+#pragma unroll
+  for (int r = 0; r < kRowsPerLane; ++r) {
+#pragma unroll
+    for (int j = 0; j < kN; ++j) out[r][j] = {0.0, 0.0};
+  }
+#pragma unroll
+  for (int k = 0; k < kN; ++k) {
+#pragma unroll
+    for (int j = 0; j < kN; ++j) {
+      const cplx b = m[k * kN + j];
+#pragma unroll
+      for (int r = 0; r < kRowsPerLane; ++r) {
+        out[r][j].re = fma(x[r][k].re, b.re, out[r][j].re);
+        out[r][j].im = fma(x[r][k].re, b.im, out[r][j].im);
+        out[r][j].re = fma(-x[r][k].im, b.im, out[r][j].re);
+        out[r][j].im = fma(x[r][k].im, b.re, out[r][j].im);
+      }
+    }
+  }
+}
+
+__device__ __forceinline__ double max3(double v, int base) {
+  return fmax(fmax(__shfl(v, base), __shfl(v, base + 1)), __shfl(v, base + 2));
+}
+
+__global__ void stability_clear(double* radius, int n) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n) radius[i] = 0.0;
+}
+
+template <bool kPaper>
 __global__ __launch_bounds__(64) void stability_kernel(StabArgs a, const double* omega_p,
-                                                        const double* r_p, double* radius) {
+                                                        const double* r_p, double* radius,
+                                                        int nchunks) {
   __shared__ double gam[kN2];
-  __shared__ cplx X[kN2], T[kN2], T2[kN2], U[kN2];
-  __shared__ cplx sym[kN];
+  __shared__ cplx mats[kModes * kN2];
+  __shared__ cplx solve[kPaper ? 2 * kN2 + kN : 1];
   const int lane = threadIdx.x;
-  const int point = blockIdx.x;
+  const int point = blockIdx.x / nchunks, chunk = blockIdx.x % nchunks;
+  // Lane 63 repeats lane 60's work.
+  const int grp = min(lane / kLanesPerMode, kModes - 1), base = grp * kLanesPerMode;
+  const int row0 = (lane - base) % kLanesPerMode * kRowsPerLane;
+  cplx* const mat = mats + grp * kN2;
   for (int e = lane; e < kN2; e += 64) gam[e] = gamma_ij(e / kN, e % kN, a.ux, a.uy);
   const double w = omega_p[point], r = r_p[point];
   // collision-map coefficients
@@ -106,190 +263,231 @@ __global__ __launch_bounds__(64) void stability_kernel(StabArgs a, const double*
   const double cFg = 2 / (2 + w), cFe = w / (2 + w);  // f from f~ (A = 0); R at h = dt
   __syncthreads();
 
-  double best = 0.0;
   const int nk = a.nkx * a.nky;
-  for (int kk = 0; kk < nk; ++kk) {
-    const double thx = a.thx0 + (kk / a.nky) * a.dthx;
-    const double thy = (kk % a.nky) * a.dthy;
-    if (lane < kN) sym[lane] = symbol_q(lane, thx, thy, a.eta);
-    __syncthreads();
+  const int k0 = a.nkx > a.nky ? (a.nky - 1) * a.nky : 0;  // the mode at |k| = 0
+  const int mine = chunk < nk ? (nk - 1 - chunk) / nchunks + 1 : 0;  // modes of this chunk
+  const int stride = mine % 7919 == 0 ? 7907 : 7919;  // prime to mine (< 2^17.1)
+  double best = 0.0;  // over this block's modes
+  for (int first = 0; first < mine + 1; first += kModes) {
+    const int item = first + grp;  // item 0: |k| = 0, then the chunk's modes
+    const bool active = item <= mine;
+    // The chunk's modes in a scattered order, so that the first of them
+    // already sample the whole grid for a large radius to compare with.
+    const int kk = item == 0 || !active ? k0 : chunk + (item - 1) * stride % mine * nchunks;
+    const double th[2] = {a.thx0 + (kk / a.nky) * a.dthx, (kk % a.nky) * a.dthy};
+    double sn[2], cs[2];
+    for (int k = 0; k < 2; ++k) sincos(th[k], &sn[k], &cs[k]);
+    cplx rs[kRowsPerLane];  // r * symbol of the lane's rows
+#pragma unroll
+    for (int i = 0; i < kRowsPerLane; ++i) rs[i] = cscale(symbol_q(row0 + i, sn, cs, a.eta), r);
+    auto delta = [&](int i, int j) { return row0 + i == j ? 1.0 : 0.0; };
+    auto gm = [&](int i, int j) { return gam[(row0 + i) * kN + j]; };
 
-    if (a.model == 0) {
-      // lhs in X, rhs in T; Gauss-Jordan with partial pivoting: T <- X^-1 T.
-      const double b2 = a.b2bar, bt = a.b2tilde;
-      for_elems(lane, [&](int i, int j) {
-        const double d = i == j ? 1.0 : 0.0, g = gam[i * kN + j];
-        const cplx rs = cscale(sym[i], r);
-        X[i * kN + j] = cadd({(1 + w * b2) * d + w * (0.5 - 2 * b2) * g, 0.0},
-                             cscale(rs, bt * d + (0.5 - bt) * g));
-        T[i * kN + j] = csub({(1 - w * (1 - b2)) * d + w * (1.5 - 2 * b2) * g, 0.0},
-                             cscale(rs, (1 - bt) * d - (0.5 - bt) * g));
-      });
-      __syncthreads();
-      for (int c = 0; c < kN; ++c) {
-        int piv = c;
-        double pmax = cabs2(X[c * kN + c]);
-        for (int i = c + 1; i < kN; ++i) {
-          const double v = cabs2(X[i * kN + c]);
-          if (v > pmax) {
-            pmax = v;
-            piv = i;
-          }
+    Rows X, Y;
+    if constexpr (kPaper) {
+      // One mode after the other, each by the whole wave.
+      cplx* const sym = solve + 2 * kN2;
+      for (int g = 0; g < kModes; ++g) {
+        __syncthreads();
+        if (grp == g && lane < 63) {
+#pragma unroll
+          for (int i = 0; i < kRowsPerLane; ++i) sym[row0 + i] = symbol_q(row0 + i, sn, cs, a.eta);
         }
         __syncthreads();
-        if (lane < kN && piv != c) {
-          const cplx x0 = X[c * kN + lane], t0 = T[c * kN + lane];
-          X[c * kN + lane] = X[piv * kN + lane];
-          T[c * kN + lane] = T[piv * kN + lane];
-          X[piv * kN + lane] = x0;
-          T[piv * kN + lane] = t0;
-        }
-        __syncthreads();
-        const cplx p = X[c * kN + c];
-        __syncthreads();
-        if (lane < kN) {
-          X[c * kN + lane] = cdiv(X[c * kN + lane], p);
-          T[c * kN + lane] = cdiv(T[c * kN + lane], p);
-        }
-        __syncthreads();
-        cplx fac[2], xr[2], tr[2];
-        int n = 0;
-        for_elems(lane, [&](int i, int j) {
-          fac[n] = X[i * kN + c];
-          xr[n] = X[c * kN + j];
-          tr[n] = T[c * kN + j];
-          ++n;
-        });
-        __syncthreads();
-        n = 0;
-        for_elems(lane, [&](int i, int j) {
-          if (i != c) {
-            X[i * kN + j] = csub(X[i * kN + j], cmul(fac[n], xr[n]));
-            T[i * kN + j] = csub(T[i * kN + j], cmul(fac[n], tr[n]));
-          }
-          ++n;
-        });
-        __syncthreads();
+        solve_paper(a, lane, gam, sym, w, r, solve, solve + kN2);
+        for_elems(lane, [&](int i, int j) { mats[g * kN2 + i * kN + j] = solve[kN2 + i * kN + j]; });
       }
-      // G in T; copy to X
-      for_elems(lane, [&](int i, int j) { X[i * kN + j] = T[i * kN + j]; });
       __syncthreads();
-    } else if (a.model == 3) {
-      // T = (I - A rS) J_P, T2 = (I - rS) J_Q; then
-      // X = J_Q - rS (b0 J_f + b1 J_R T + b2 J_R1 T2), J_R1 = cFg I + cFe Gamma.
-      for_elems(lane, [&](int i, int j) {
-        const double d = i == j ? 1.0 : 0.0, g = gam[i * kN + j];
-        T[i * kN + j] = cscale(csub({1.0, 0.0}, cscale(sym[i], A * r)), cPg * d + cPe * g);
-        T2[i * kN + j] = cscale(csub({1.0, 0.0}, cscale(sym[i], r)), cQg * d + cQe * g);
-      });
-      __syncthreads();
-      for_elems(lane, [&](int i, int j) {
-        cplx m1{0.0, 0.0}, m2{0.0, 0.0};
-        for (int k = 0; k < kN; ++k) {
-          const double dk = i == k ? 1.0 : 0.0, gk = gam[i * kN + k];
-          m1 = cadd(m1, cscale(T[k * kN + j], cRs * dk + cRe * gk));
-          m2 = cadd(m2, cscale(T2[k * kN + j], cFg * dk + cFe * gk));
-        }
-        const double d = i == j ? 1.0 : 0.0, g = gam[i * kN + j];
-        cplx m = cadd(cscale(m1, a.bt[1]), cscale(m2, a.bt[2]));
-        m = cadd(m, {a.bt[0] * (cFg * d + cFe * g), 0.0});
-        // The base: J_Q, or J_f with the collision weights' terms added below.
-        const double base = a.gen_bb ? cFg * d + cFe * g : cQg * d + cQe * g;
-        X[i * kN + j] = csub({base, 0.0}, cmul(cscale(sym[i], r), m));
-        U[i * kN + j] = m1;  // J_R (I - A rS) J_P, the Jacobian of f*
-      });
-      __syncthreads();
-      if (a.gen_bb) {
-        // X += w (Gamma - I) (B-0 J_f + B-1 U)
-        for_elems(lane, [&](int i, int j) {
-          cplx acc{0.0, 0.0};
-          for (int k = 0; k < kN; ++k) {
-            const double gik = gam[i * kN + k] - (i == k ? 1.0 : 0.0);
-            const double jf = cFg * (k == j ? 1.0 : 0.0) + cFe * gam[k * kN + j];
-            acc = cadd(acc, cscale(cadd({a.bb[0] * jf, 0.0}, cscale(U[k * kN + j], a.bb[1])), gik));
-          }
-          X[i * kN + j] = cadd(X[i * kN + j], cscale(acc, w));
-        });
-        __syncthreads();
-        // G = (aY I + aE Gamma) X
-        const double aY = (1 + 0.5 * w) / (1 + a.bb[2] * w);
-        const double aE = w * (a.bb[2] - 0.5) / (1 + a.bb[2] * w);
-        for_elems(lane, [&](int i, int j) {
-          cplx acc{0.0, 0.0};
-          for (int k = 0; k < kN; ++k)
-            acc = cadd(acc, cscale(X[k * kN + j], aY * (i == k ? 1.0 : 0.0) + aE * gam[i * kN + k]));
-          T[i * kN + j] = acc;
-        });
-        __syncthreads();
-        for_elems(lane, [&](int i, int j) { X[i * kN + j] = T[i * kN + j]; });
-        __syncthreads();
+#pragma unroll
+      for (int i = 0; i < kRowsPerLane; ++i) {
+#pragma unroll
+        for (int j = 0; j < kN; ++j) X[i][j] = mat[(row0 + i) * kN + j];
       }
     } else {
-      // T = (I - c rS) J, with (c, J) = (A, J_P) for model 1 and (1, J_Q) for model 2.
-      const double cs = a.model == 1 ? A : 1.0;
-      const double jg = a.model == 1 ? cPg : cQg, je = a.model == 1 ? cPe : cQe;
-      for_elems(lane, [&](int i, int j) {
-        const double J = jg * (i == j ? 1.0 : 0.0) + je * gam[i * kN + j];
-        const cplx f = csub({1.0, 0.0}, cscale(sym[i], cs * r));
-        T[i * kN + j] = cscale(f, J);
-      });
-      __syncthreads();
-      // X = J_Q - c2 rS (J_extra + J_R T)
-      for_elems(lane, [&](int i, int j) {
-        cplx m{0.0, 0.0};
-        for (int k = 0; k < kN; ++k) {
-          const double jr = cRs * (i == k ? 1.0 : 0.0) + cRe * gam[i * kN + k];
-          m = cadd(m, cscale(T[k * kN + j], jr));
+      // (I - c rS) J to LDS, then J_R times it: cRs T + cRe Gamma T.
+      auto predicted = [&](double c, double jg, double je, double ss, double se, Rows& out) {
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kRowsPerLane; ++i) {
+          const cplx f = csub({1.0, 0.0}, cscale(rs[i], c));
+#pragma unroll
+          for (int j = 0; j < kN; ++j)
+            mat[(row0 + i) * kN + j] = cscale(f, jg * delta(i, j) + je * gm(i, j));
         }
-        const double d = i == j ? 1.0 : 0.0, g = gam[i * kN + j];
-        if (a.model == 2) m = cadd(m, {cFg * d + cFe * g, 0.0});
-        const double c2 = a.model == 2 ? 0.5 * r : r;
-        X[i * kN + j] = csub({cQg * d + cQe * g, 0.0}, cmul(cscale(sym[i], c2), m));
-      });
-      __syncthreads();
+        __syncthreads();
+        gamma_times(gam, mat, row0, out);
+#pragma unroll
+        for (int i = 0; i < kRowsPerLane; ++i) {
+#pragma unroll
+          for (int j = 0; j < kN; ++j)
+            out[i][j] = cadd(cscale(mat[(row0 + i) * kN + j], ss), cscale(out[i][j], se));
+        }
+      };
+      if (a.model == 2)
+        predicted(1.0, cQg, cQe, cRs, cRe, Y);
+      else
+        predicted(A, cPg, cPe, cRs, cRe, Y);
+      if (a.model == 3) {
+        // X = base - rS (b0 J_f + b1 J_R (I - A rS) J_P + b2 J_R1 (I - rS) J_Q).
+        if (a.gen_bb) {
+          // The explicit collision terms, w (Gamma - I) (B-0 J_f + B-1 Y).
+          __syncthreads();
+#pragma unroll
+          for (int i = 0; i < kRowsPerLane; ++i) {
+#pragma unroll
+            for (int j = 0; j < kN; ++j)
+              mat[(row0 + i) * kN + j] =
+                  cadd({a.bb[0] * (cFg * delta(i, j) + cFe * gm(i, j)), 0.0},
+                       cscale(Y[i][j], a.bb[1]));
+          }
+          __syncthreads();
+          gamma_times(gam, mat, row0, X);
+#pragma unroll
+          for (int i = 0; i < kRowsPerLane; ++i) {
+#pragma unroll
+            for (int j = 0; j < kN; ++j)
+              X[i][j] = cscale(csub(X[i][j], mat[(row0 + i) * kN + j]), w);
+          }
+        } else {
+#pragma unroll
+          for (int i = 0; i < kRowsPerLane; ++i) {
+#pragma unroll
+            for (int j = 0; j < kN; ++j) X[i][j] = {0.0, 0.0};
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < kRowsPerLane; ++i) {
+#pragma unroll
+          for (int j = 0; j < kN; ++j) {
+            const double f = cFg * delta(i, j) + cFe * gm(i, j);
+            const double qm = a.gen_bb ? f : cQg * delta(i, j) + cQe * gm(i, j);
+            const cplx m = cadd(cscale(Y[i][j], a.bt[1]), {a.bt[0] * f, 0.0});
+            X[i][j] = cadd(X[i][j], csub({qm, 0.0}, cmul(rs[i], m)));
+          }
+        }
+        predicted(1.0, cQg, cQe, cFg, cFe, Y);
+#pragma unroll
+        for (int i = 0; i < kRowsPerLane; ++i) {
+#pragma unroll
+          for (int j = 0; j < kN; ++j)
+            X[i][j] = csub(X[i][j], cmul(rs[i], cscale(Y[i][j], a.bt[2])));
+        }
+        if (a.gen_bb) {
+          // G = (aY I + aE Gamma) X
+          const double aY = (1 + 0.5 * w) / (1 + a.bb[2] * w);
+          const double aE = w * (a.bb[2] - 0.5) / (1 + a.bb[2] * w);
+          publish(mat, row0, X);
+          gamma_times(gam, mat, row0, Y);
+#pragma unroll
+          for (int i = 0; i < kRowsPerLane; ++i) {
+#pragma unroll
+            for (int j = 0; j < kN; ++j)
+              X[i][j] = cadd(cscale(X[i][j], aY), cscale(Y[i][j], aE));
+          }
+        }
+      } else {
+        // X = J_Q - c2 rS (J_f (model 2) + J_R T)
+        const double c2 = a.model == 2 ? 0.5 : 1.0;
+#pragma unroll
+        for (int i = 0; i < kRowsPerLane; ++i) {
+#pragma unroll
+          for (int j = 0; j < kN; ++j) {
+            cplx m = Y[i][j];
+            if (a.model == 2) m.re += cFg * delta(i, j) + cFe * gm(i, j);
+            X[i][j] = csub({cQg * delta(i, j) + cQe * gm(i, j), 0.0},
+                           cmul(cscale(rs[i], c2), m));
+          }
+        }
+      }
     }
 
-    // Spectral radius by normalised squaring.
-    double c2 = 0.0;
-    for_elems(lane, [&](int i, int j) { c2 = fmax(c2, cabs2(X[i * kN + j])); });
-    c2 = wave_max(c2);
-    double ell = 0.5 * log(c2);  // log ||G||_max
-    bool zero = !(c2 > 0.0);
-    {
-      const double inv = zero ? 0.0 : 1.0 / sqrt(c2);
-      for_elems(lane, [&](int i, int j) { X[i * kN + j] = cscale(X[i * kN + j], inv); });
+    // Spectral radius by squaring: G^(2^s) = 2^e X.  dead: the radius counts
+    // as 0 (X is zero or not finite), or it cannot be the largest.
+    double known = best;
+    if (nchunks > 1)
+      known = fmax(known, __hip_atomic_load(radius + point, __ATOMIC_RELAXED,
+                                            __HIP_MEMORY_SCOPE_AGENT));
+    const double log_known = log(known);
+    double e = 0.0;
+    bool dead = !active;
+    double biggest = 0.0;  // max |x| of the scaled matrix
+    auto scale = [&](int s) {
+      double m2 = 0.0, f2 = 0.0;
+#pragma unroll
+      for (int i = 0; i < kRowsPerLane; ++i) {
+#pragma unroll
+        for (int j = 0; j < kN; ++j) {
+          const double v = cabs2(X[i][j]);
+          m2 = fmax(m2, v);
+          f2 += v;
+        }
+      }
+      m2 = max3(m2, base);
+      f2 = __shfl(f2, base) + __shfl(f2, base + 1) + __shfl(f2, base + 2);
+      if (!(m2 > 0.0) || !isfinite(m2)) {
+        dead = true;
+        return;
+      }
+      const int x = ilogb(m2) / 2;  // max |x| within a factor of 2 of 2^x
+      const double down = ldexp(1.0, -x);
+#pragma unroll
+      for (int i = 0; i < kRowsPerLane; ++i) {
+#pragma unroll
+        for (int j = 0; j < kN; ++j) X[i][j] = cscale(X[i][j], down);
+      }
+      e += x;
+      biggest = sqrt(m2) * down;
+      // ln rho <= ln ||G^(2^s)||_F / 2^s, f2 rounded up to a power of two
+      // (f2 is that of the matrix before the scaling by 2^x).
+      const double bound = (e - x + 0.5 * (ilogb(f2) + 1)) * 0.6931471805599453;
+      if (known > 0.0 && bound < ldexp(log_known - 1e-11, s)) dead = true;
+    };
+    scale(0);
+    for (int s = 1; s <= a.squarings; ++s) {
+      if (__all(dead)) break;
+      publish(mat, row0, X);
+      square(mat, X, Y);
+#pragma unroll
+      for (int i = 0; i < kRowsPerLane; ++i) {
+#pragma unroll
+        for (int j = 0; j < kN; ++j) X[i][j] = Y[i][j];
+      }
+      e *= 2.0;
+      if (!(s & 1) || s == a.squarings) scale(s);
     }
-    __syncthreads();
-    for (int s = 0; s < a.squarings && !zero; ++s) {
-      cplx v[2];
-      int n = 0;
-      double m2 = 0.0;
-      for_elems(lane, [&](int i, int j) {
-        cplx acc{0.0, 0.0};
-        for (int k = 0; k < kN; ++k) acc = cadd(acc, cmul(X[i * kN + k], X[k * kN + j]));
-        v[n++] = acc;
-        m2 = fmax(m2, cabs2(acc));
-      });
-      m2 = wave_max(m2);
-      __syncthreads();
-      zero = !(m2 > 0.0);
-      const double inv = zero ? 0.0 : 1.0 / sqrt(m2);
-      n = 0;
-      for_elems(lane, [&](int i, int j) { X[i * kN + j] = cscale(v[n++], inv); });
-      ell = 2.0 * ell + (zero ? 0.0 : 0.5 * log(m2));
-      __syncthreads();
-    }
-    const double rho = zero ? 0.0 : exp(ldexp(ell, -a.squarings));
-    best = fmax(best, rho);
+    double rho = 0.0;
+    if (!dead) rho = exp(ldexp(e * 0.6931471805599453 + log(biggest), -a.squarings));
+    best = fmax(best, wave_max(rho));
+    if (lane == 0 && nchunks > 1)
+      // A non-negative double orders like its bits.
+      atomicMax(reinterpret_cast<unsigned long long*>(radius + point),
+                __double_as_longlong(best));
   }
-  if (lane == 0) radius[point] = best;
+  if (lane == 0 && nchunks == 1) radius[point] = best;
 }
 
 }  // namespace
 
 hipError_t launch_stability(const StabArgs& a, const double* omega, const double* r, int npoints,
                             double* radius, hipStream_t s) {
-  hipLaunchKernelGGL(stability_kernel, dim3(npoints), dim3(64), 0, s, a, omega, r, radius);
+  // Blocks for the whole chip (27 KB of LDS: five waves per CU), two batches
+  // of modes each or more.  Several blocks to a point keep their maximum in
+  // the output, which is cleared first; an output that overlaps an input
+  // takes one block per point, which reads its point before it writes.
+  const int nk = a.nkx * a.nky;
+  const int most = std::max(1, nk / (2 * kModes));
+  auto overlaps = [&](const double* in) { return radius < in + npoints && in < radius + npoints; };
+  const int nchunks = overlaps(omega) || overlaps(r)
+                          ? 1
+                          : std::min(most, std::max(1, kWantedBlocks / npoints));
+  if (nchunks > 1)
+    hipLaunchKernelGGL(stability_clear, dim3((npoints + 255) / 256), dim3(256), 0, s, radius,
+                       npoints);
+  const dim3 g(static_cast<unsigned>(npoints) * nchunks);
+  if (a.model == 0)
+    hipLaunchKernelGGL(stability_kernel<true>, g, dim3(64), 0, s, a, omega, r, radius, nchunks);
+  else
+    hipLaunchKernelGGL(stability_kernel<false>, g, dim3(64), 0, s, a, omega, r, radius, nchunks);
   return hipGetLastError();
 }
 

@@ -104,3 +104,42 @@ def test_paper_family_largest_stable_region_on_gpu():
     print("    stable fractions: " + ", ".join(f"B2={k[0]},B~2={k[1]},eta={k[2]}: {v:.3f}"
                                                for k, v in area.items()), flush=True)
     assert area[(0.5, 0.5, 0.1)] == max(area.values())
+
+
+@pytest.mark.parametrize("squarings", [1, 2, 7, 30])
+@pytest.mark.parametrize("npoints,nk", [(1, 2), (1, 23), (3, 9), (70, 5)])
+def test_stability_map_is_the_largest_norm_root(squarings, npoints, nk):
+    """The map is, to rounding, the largest ||G^m||_max^(1/m) over every mode
+    of the grid at m = 2^squarings, for one and several blocks per point (and
+    with the output overlapping an input, which takes one), odd and even
+    numbers of squarings, fewer modes than a batch and many batches: modes
+    that are dropped early never hold the maximum.  1e-12: the squarings
+    double the relative error of ||G^m|| each, which the m-th root takes back,
+    and each squaring adds about 9 eps."""
+    rng = np.random.Generator(np.random.PCG64(5))
+    omegas, rs = rng.uniform(0.05, 8.0, npoints), rng.uniform(0.05, 1.5, npoints)
+    kw = dict(eta=0.1, u=(0.1, -0.05), A=0.5)
+    ref = []
+    for w, r in zip(omegas, rs):
+        G = np.stack([S.growth("fdlbm1", a, b, w, r, **kw)
+                      for a in np.linspace(-math.pi, math.pi, 2 * nk - 1)
+                      for b in np.linspace(0.0, math.pi, nk)])
+        ell = np.zeros(len(G))
+        for s in range(squarings + 1):
+            if s:
+                G, ell = G @ G, 2 * ell
+            n = np.abs(G).max(axis=(1, 2))
+            G, ell = G / n[:, None, None], ell + np.log(n)
+        ref.append(np.exp(ell / 2.0 ** squarings).max())
+    got = t2s2.stability_map("fdlbm1", omegas, rs, nk=nk, squarings=squarings, **kw).cpu().numpy()
+    assert np.abs(got / ref - 1).max() <= 1e-12
+    # In place: the output is the omega array.
+    w = torch.as_tensor(omegas, dtype=torch.float64, device="cuda")
+    r = torch.as_tensor(rs, dtype=torch.float64, device="cuda")
+    prm = t2s2.StabilityParams()
+    prm.model, prm.eta, prm.A, prm.nk, prm.full_kx = 1, kw["eta"], kw["A"], nk, 1
+    prm.u[0], prm.u[1], prm.squarings = kw["u"][0], kw["u"][1], squarings
+    lib = t2s2.load_library()
+    assert lib.t2s2_stability_map(prm, w.data_ptr(), r.data_ptr(), npoints, w.data_ptr(),
+                                  torch.cuda.current_stream().cuda_stream) == t2s2.OK
+    assert np.array_equal(w.cpu().numpy(), got)
