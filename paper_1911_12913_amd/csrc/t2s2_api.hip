@@ -262,6 +262,9 @@ constexpr double kPairEdgeCost = 2.0, kPairTopCost = 1.5;
 // 1025^2 (53) 55.1 / 52.6, 2049^2 (125) 151 / 117.
 constexpr long long kPairMinWork = 52;
 
+// Steps of one launch of the one-block kernel: about a millisecond.
+constexpr int64_t kMeshSteps = 256;
+
 // The two-step kernel's plan: the frame of a walled mesh and the main strips
 // and rows inside it, over one block per resident slot, so that a frame
 // piece and a main block's share take about the same time.  Returns the grid,
@@ -377,6 +380,8 @@ struct t2s2_ctx {
   // Plan of the two-step kernel; grid_pair 0: this context does not take it.
   PairPlan pair{};
   int grid_pair = 0;
+  // The mesh fits one block, which takes all steps of a call.
+  bool mesh_steps = false;
   // adjoint
   AdjParams adj{};
   bool adj_bound = false;
@@ -724,6 +729,15 @@ int t2s2_bind(t2s2_ctx* c, void* state_a, void* state_b, void* workspace, void* 
       static_cast<long long>(c->sp.nunits) * c->ny < static_cast<long long>(kTileMaxMarchRows) * c->grid)
     c->sp.tile = 1;
   if (!c->sp.single) c->sp_gen = c->sp;
+  // Meshes that fit one block take all steps of a call in it (us per step,
+  // FP64: forced channel 10 x 21 8.6 -> 2.6, Taylor-Green 32^2 6.3 -> 3.9;
+  // T2S2_TILE keeps the tile kernel).  The reduced forms do so on walled
+  // meshes, where the compiler fuses the FP32 products as in the tile kernel;
+  // on periodic ones it does not, and stochastic rounding would turn last-bit
+  // differences into whole units of the 16-bit forms.
+  c->mesh_steps = c->sp.tile && static_cast<long long>(c->nx) * c->ny <= kMeshNodes &&
+                  (c->cfg.storage == T2S2_F64 || !c->sp.per_x || !c->sp.per_y) &&
+                  !std::getenv("T2S2_TILE");
   c->grid_pair = 0;
   if (c->cfg.storage == T2S2_F64 && c->sp.scheme == 1 && !c->sp.single &&
       !std::getenv("T2S2_BLOCKS")) {
@@ -741,6 +755,25 @@ int t2s2_bind(t2s2_ctx* c, void* state_a, void* state_b, void* workspace, void* 
 // two launches of it, which end in the buffer they began in, as four single
 // steps do.
 static hipError_t launch_steps(t2s2_ctx* c, int64_t nsteps, int& cur, int64_t* taken) {
+  if (c->mesh_steps && nsteps > 1) {
+    // All of them in one block, at most kMeshSteps to a launch, which ends in
+    // the buffer that as many single steps end in.  (A step alone is faster
+    // over many CUs: 16.5 against 18.8 us with its read-back, cavity 31^2.)
+    for (int64_t left = nsteps; left > 0;) {
+      const int n = static_cast<int>(std::min<int64_t>(left, kMeshSteps));
+      c->sp.src = c->state[cur];
+      if (n & 1) cur = 1 - cur;
+      c->sp.dst = c->state[cur];
+      const hipError_t e = launch_mesh_steps(c->cfg.storage, c->sp, n, c->stream);
+      if (e != hipSuccess) {
+        if (n & 1) cur = 1 - cur;
+        return e;
+      }
+      left -= n;
+      if (taken) *taken += n;
+    }
+    return hipSuccess;
+  }
   const int64_t pairs = c->grid_pair > 0 ? 2 * (nsteps / 4) : 0;
   for (int64_t k = 0; k < pairs; ++k) {
     c->sp.src = c->state[cur];

@@ -203,6 +203,10 @@ hipError_t launch_step_save_s(int storage, const StepParams& p, int grid, hipStr
 // with A > 0, strips of kPairOut columns.
 hipError_t launch_pair_step(const StepParams& p, const PairPlan& plan, int grid, hipStream_t s);
 int pair_blocks_per_cu(bool force, bool walls);
+// nsteps time steps from p.src to p.dst (which may be one buffer) by one
+// block (t2s2_mesh.hip): scheme 1 with A > 0, at most kMeshNodes nodes.
+constexpr int kMeshNodes = 1024;
+hipError_t launch_mesh_steps(int storage, const StepParams& p, int nsteps, hipStream_t s);
 // Resident step-kernel blocks per CU for this variant (-1 on error); scheme
 // 0 is the single-stencil (A = 0) kernel, 4 the family (scheme 3) with
 // collision weights other than (1/2, 0, 1/2).

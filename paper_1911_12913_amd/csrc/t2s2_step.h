@@ -104,13 +104,13 @@ using LdsPtr = const __attribute__((address_space(3))) Real*;
 // two-step kernel, which adds each R row to the outputs around it, meets the
 // terms: the rows above, the row itself (the x taps first), the rows below.
 // FP32 takes the x taps first.
-template <typename Real>
-__device__ __forceinline__ Real full_taps(int q, const Real* wx, const Real* wy, Real centre,
-                                          Real acc, const Real (&row)[kTaps]) {
+// x(acc): acc plus the x taps.
+template <typename Real, typename X>
+__device__ __forceinline__ Real full_taps_of(int q, const Real* wy, Real acc,
+                                             const Real (&row)[kTaps], X x) {
   const int sy = ey_of(q) > 0 ? 0 : 1;
   if constexpr (sizeof(Real) == 4) {
-    if (ex_of(q) > 0) acc = x_taps<0>(wx, centre, acc);
-    if (ex_of(q) < 0) acc = x_taps<1>(wx, centre, acc);
+    acc = x(acc);
     if (ey_of(q) != 0) {
 #pragma unroll
       for (int k = 0; k < kTaps; ++k) acc += wy[sy * kTaps + k] * row[k];
@@ -124,14 +124,22 @@ __device__ __forceinline__ Real full_taps(int q, const Real* wx, const Real* wy,
     for (int k = 0; k < 2; ++k)
       if (k < above) acc = fma_of(wy[sy * kTaps + k], row[k], acc);
   }
-  if (ex_of(q) > 0) acc = x_taps<0>(wx, centre, acc);
-  if (ex_of(q) < 0) acc = x_taps<1>(wx, centre, acc);
+  acc = x(acc);
   if (ey_of(q) != 0) {
 #pragma unroll
     for (int k = 1; k < kTaps; ++k)
       if (k >= above) acc = fma_of(wy[sy * kTaps + k], row[k], acc);
   }
   return acc;
+}
+template <typename Real>
+__device__ __forceinline__ Real full_taps(int q, const Real* wx, const Real* wy, Real centre,
+                                          Real acc, const Real (&row)[kTaps]) {
+  return full_taps_of(q, wy, acc, row, [&](Real a) {
+    if (ex_of(q) > 0) a = x_taps<0>(wx, centre, a);
+    if (ex_of(q) < 0) a = x_taps<1>(wx, centre, a);
+    return a;
+  });
 }
 
 // Guo force term (eq 3.12) of direction q from E = (f^eq_q - w_q) / w_q:

@@ -980,3 +980,45 @@ def test_two_step_kernel_is_bitwise_single_steps(kind, monkeypatch):
             assert ctx.current == n % 2 and ctx.steps_taken == n
             assert np.array_equal(g, g_single)
         _compare(case, g, d, u, v, oracle.run(case, phi0, n))
+
+
+# ------------------- all steps of a call in one block (at most 1024 nodes)
+
+def _mesh_case(kind):
+    if kind == "tgv32":  # 1024 nodes, the largest
+        return W.tgv_case(32, 32, u0=0.02, nu=0.05, cfl=0.7, eta=0.05)
+    if kind == "tgv5x7":  # one wave, not full; the stencil wraps onto itself
+        return W.tgv_case(5, 7, u0=0.02, nu=0.05, cfl=0.7, eta=0.05)
+    if kind == "tgv_forced":  # 513 nodes: the first mesh of the larger block
+        case = W.tgv_case(27, 19, u0=0.02, nu=0.05, cfl=0.7, eta=0.05)
+        case.force = (1e-3, -2e-3)
+        return case
+    if kind == "cavity":  # 31 x 31, every wall moving
+        case = W.cavity_case(30, lid=0.1, re=400.0, cfl=0.8, eta=0.1, noise=1e-5, seed=4)
+        case.u_wall[:] = np.array([[0.002, 0.03], [-0.001, -0.02], [0.025, 0.003], [0.1, -0.002]])
+        return case
+    if kind == "cavity5":
+        return W.cavity_case(4, lid=0.1, re=100.0, cfl=0.5, eta=0.1, noise=1e-4, seed=5)
+    return W.poiseuille_case(dt_over_y1=0.9, eta=0.1)  # force, walls on y only
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "bf16", "f16", "bf16sr", "f16sr"])
+@pytest.mark.parametrize("kind", ["tgv32", "tgv5x7", "tgv_forced", "cavity", "cavity5",
+                                  "channel"])
+def test_one_block_steps_are_bitwise_the_tile_kernel(kind, storage, monkeypatch):
+    """On meshes of at most 1024 nodes one block takes all steps of a call
+    (T2S2_TILE selects the tile kernel, one launch per step): bitwise the same
+    state in every storage form, after an odd number of steps and, in two
+    launches, after more steps than one launch takes, in the buffer that
+    single steps end in.  (The reduced forms take it on walled meshes only:
+    on periodic ones both runs here are the tile kernel's.)"""
+    case = _mesh_case(kind)
+    phi0 = oracle.init(case) + W.random_state((9, case.ny, case.nx), 1e-5, 8)
+    monkeypatch.delenv("T2S2_BLOCKS", raising=False)
+    for n in (7, 300):
+        monkeypatch.setenv("T2S2_TILE", "1")
+        _, g_tile, *_ = _gpu_run(case, phi0, n, storage=storage)
+        monkeypatch.delenv("T2S2_TILE")
+        ctx, g, d, u, v = _gpu_run(case, phi0, n, storage=storage)
+        assert ctx.current == n % 2 and ctx.steps_taken == n
+        assert np.array_equal(g, g_tile)
