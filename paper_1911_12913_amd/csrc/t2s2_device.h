@@ -424,17 +424,16 @@ __device__ inline const float* wall_brackets<float>(const StepParams& p, int sid
   return p.xb32[side];
 }
 
+// Side (table row) of wall node (c, r): the side walls hold the corners.
+__device__ inline int wall_side_at(const StepParams& p, int c, int r) {
+  if (!p.per_x && c == 0) return 0;
+  if (!p.per_x && c == p.nx - 1) return 1;
+  return !p.per_y && r == 0 ? 2 : 3;
+}
+
 __device__ inline void wall_velocity(const StepParams& p, int c, int r, double& ub,
                                      double& vb) {
-  int side;
-  if (!p.per_x && c == 0)
-    side = 0;
-  else if (!p.per_x && c == p.nx - 1)
-    side = 1;
-  else if (!p.per_y && r == 0)
-    side = 2;
-  else
-    side = 3;
+  const int side = wall_side_at(p, c, r);
   ub = p.uw[side][0];
   vb = p.uw[side][1];
 }

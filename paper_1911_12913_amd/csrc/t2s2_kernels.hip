@@ -500,26 +500,31 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, kScheme), (kMinWave
       iteration(it + 1, gB, qB, qA, vB, vA);
     }
     __syncthreads();  // the next piece reuses the rings; the piece's stores are visible
-    if (kWalls) piece_walls(p, dst, x0, x1, y0, y1, threadIdx.x % kBlockThreads, kBlockThreads);
+    if (kWalls) piece_walls(p, dst, x0, x1, y0, y1, threadIdx.x % kBlockThreads, kBlockThreads, p.uw);
   }
 }
 
 // ---------------------------------------------------------------------------
-// Tile step for small meshes (T2S2-FDLBM1 family).  A block of eight waves
-// takes one strip (56 output columns) and kTileRows output rows as a whole
-// tile instead of marching down a range of rows: it loads the tile's rows
-// y0-4 .. y0+kTileRows+3 at once, forms P of all of them (LDS) and Q of its
-// output rows (registers), then S and R of rows y0-2 .. y0+kTileRows+1
-// (LDS), then the new state: three phases and two barriers, where a march
-// over a few rows runs four pipelined iterations of three phases each.  Each
-// node takes the expressions of step_kernel.  Wave w forms P of tile rows w
-// and w+8 (rows counted from y0-4) and keeps Q of the one that is an output
-// row (w+8 for w < 4, w otherwise), which it outputs in phase 3.  kSaveS
-// also stores S at the interior nodes, as in step_kernel.
+// Tile step for small meshes (T2S2-FDLBM1 family).  A block takes one strip
+// (56 output columns) and kTileRows output rows as a whole tile instead of
+// marching down a range of rows: it loads the tile's rows y0-4 ..
+// y0+kTileRows+3 at once, forms P of all of them (LDS) and Q of its output
+// rows (registers), then S and R of rows y0-2 .. y0+kTileRows+1 (LDS), then
+// the new state: three phases and two barriers, where a march over a few rows
+// runs four pipelined iterations of three phases each.  Each node takes the
+// expressions of step_kernel.  Wave w holds row y0 - 4 + w in every phase.
+// kSaveS also stores S at the interior nodes, as in step_kernel.
+//
+// A chain of latencies bounds it: of the 9.7 us of a 257^2 FP64 cavity step
+// an empty launch is 3.5, P 0.5, S and R 1.8, the new state and its way to
+// memory 2.7, the wall nodes 1.2.  Sixteen waves, one per row, cover each
+// other's latencies better than eight that take two rows of P and of S in
+// turn: 257^2 cavity FP64 9.86 -> 9.70 us, FP32 8.65 -> 7.70, bf16 with
+// stochastic rounding 8.26 -> 7.20; 64^2 periodic FP64 6.83 -> 6.63.
 // ---------------------------------------------------------------------------
 constexpr int kTileRows = 8;
-constexpr int kTileWaves = 8;
 constexpr int kTileIn = kTileRows + 2 * kHalo;   // rows of P
+constexpr int kTileWaves = kTileIn;               // one wave per row of P
 constexpr int kTileMid = kTileRows + kHalo;      // rows of R
 
 template <typename Store, bool kForce, bool kWalls, bool kSaveS = false>
@@ -527,6 +532,12 @@ __global__ __launch_bounds__(kTileWaves * kLanes) void tile_step_kernel(StepPara
   using Real = typename Cvt<Store>::R;
   __shared__ Real tP[kTileIn * kQ * kLanes];           // [row][q][lane]
   __shared__ Real tR[kTileMid * (kQ - 1) * kLanes];    // [row][q-1][lane]
+  // The walls' brackets and velocities, fetched while phase 1 waits for the
+  // state: indexed by side where they are used, each would be a round trip to
+  // the argument segment on the kernel's critical path (65^2 cavity 9.55 ->
+  // 9.35 us).
+  __shared__ Real tX[4 * kQ];
+  __shared__ double tU[4][2];
   const int lane = threadIdx.x & (kLanes - 1);
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
   const int nx = p.nx, ny = p.ny;
@@ -540,6 +551,12 @@ __global__ __launch_bounds__(kTileWaves * kLanes) void tile_step_kernel(StepPara
   const int y1 = min(y0 + kTileRows, ny);
   if (strip >= p.nstrips) return;  // whole block, before any barrier
 
+  Real xbv = Real(0);
+  double uwv = 0;
+  if (kWalls && threadIdx.x < 4 * kQ) {
+    xbv = wall_brackets<Real>(p, 0)[threadIdx.x];
+    uwv = p.uw[(threadIdx.x >> 1) & 3][threadIdx.x & 1];
+  }
   for (int i = threadIdx.x; i < kTileMid * (kQ - 1) * kLanes; i += kTileWaves * kLanes)
     tR[i] = Real(0);
 
@@ -560,67 +577,60 @@ __global__ __launch_bounds__(kTileWaves * kLanes) void tile_step_kernel(StepPara
   const bool src_xr = !p.per_x && c == nx - 2;
   const auto& k = coef<Real>(p);
 
-  // ---- phase 1: P of tile rows w and w + 8, Q of the wave's output row.
-  const int jout = w < kHalo ? w + kTileWaves : w;
+  // ---- phase 1: P of the wave's row, Q if it is an output row.
   Real qout[kQ];
   {
-    Store gr[2][kQ];
+    Store gr[kQ];
+    const int pr = y0 - kHalo + w;
+    const int prm = p.per_y ? wrap_near(pr, ny) : clampi(pr, 0, ny - 1);
+    const unsigned boff =
+        (static_cast<unsigned>(prm) * static_cast<unsigned>(pitch) + static_cast<unsigned>(cm)) *
+        static_cast<unsigned>(sizeof(Store));
+    load_planes(src, plane * sizeof(Store), boff, gr);
+    Real g[kQ];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int pr = y0 - kHalo + w + kTileWaves * h;
-      const int prm = p.per_y ? wrap_near(pr, ny) : clampi(pr, 0, ny - 1);
-      const unsigned boff =
-          (static_cast<unsigned>(prm) * static_cast<unsigned>(pitch) + static_cast<unsigned>(cm)) *
-          static_cast<unsigned>(sizeof(Store));
-      load_planes(src, plane * sizeof(Store), boff, gr[h]);
+    for (int q = 0; q < kQ; ++q) g[q] = Cvt<Store>::ld(gr[q]);
+    double s, jx, jy;
+    moment_sums(g, s, jx, jy);
+    Real rho, ux, uy;
+    velocity(s, jx, jy, rho, ux, uy);
+    if (kForce) {
+      ux = add_scaled(p.half_dt, p.Fx, ux);
+      uy = add_scaled(p.half_dt, p.Fy, uy);
     }
+    const Real d = static_cast<Real>(s);
+    Real X[kQ];
+    eq_brackets(ux, uy, X);
+    Real* row = tP + w * kQ * kLanes;
+    Real E[kQ], Fq[kQ];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int j = w + kTileWaves * h;
-      Real g[kQ];
-#pragma unroll
-      for (int q = 0; q < kQ; ++q) g[q] = Cvt<Store>::ld(gr[h][q]);
-      double s, jx, jy;
-      moment_sums(g, s, jx, jy);
-      Real rho, ux, uy;
-      velocity(s, jx, jy, rho, ux, uy);
+    for (int q = 0; q < kQ; ++q) {
+      E[q] = fma_of(rho, X[q], d);
+      Real Pq = fma_of(k.cPg, g[q], k.kP[wclass(q)] * E[q]);
       if (kForce) {
-        ux = add_scaled(p.half_dt, p.Fx, ux);
-        uy = add_scaled(p.half_dt, p.Fy, uy);
+        Fq[q] = force_term(q, p, ux, uy, E[q]);
+        Pq = fma_of(static_cast<Real>(p.cPF), Fq[q], Pq);
       }
-      const Real d = static_cast<Real>(s);
-      Real X[kQ];
-      eq_brackets(ux, uy, X);
-      Real* row = tP + j * kQ * kLanes;
-      Real E[kQ], Fq[kQ];
+      row[q * kLanes + lane] = Pq;
+    }
+    if (w >= kHalo && w < kHalo + kTileRows) {  // uniform per wave
 #pragma unroll
       for (int q = 0; q < kQ; ++q) {
-        E[q] = fma_of(rho, X[q], d);
-        Real Pq = fma_of(k.cPg, g[q], k.kP[wclass(q)] * E[q]);
-        if (kForce) {
-          Fq[q] = force_term(q, p, ux, uy, E[q]);
-          Pq = fma_of(static_cast<Real>(p.cPF), Fq[q], Pq);
-        }
-        row[q * kLanes + lane] = Pq;
-      }
-      if (j == jout) {  // uniform per wave
-#pragma unroll
-        for (int q = 0; q < kQ; ++q) {
-          qout[q] = fma_of(k.cQg, g[q], k.kQ[wclass(q)] * E[q]);
-          if (kForce) qout[q] = fma_of(static_cast<Real>(p.cQF), Fq[q], qout[q]);
-        }
+        qout[q] = fma_of(k.cQg, g[q], k.kQ[wclass(q)] * E[q]);
+        if (kForce) qout[q] = fma_of(static_cast<Real>(p.cQF), Fq[q], qout[q]);
       }
     }
   }
+  if (kWalls && threadIdx.x < 4 * kQ) {
+    tX[threadIdx.x] = xbv;
+    if (threadIdx.x < 8) tU[threadIdx.x >> 1][threadIdx.x & 1] = uwv;
+  }
   __syncthreads();
 
-  // ---- phase 2: S and R of rows y0 - 2 + m, m = w and w + 8 (m < 12).
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int m = w + kTileWaves * h;
-    if (m >= kTileMid) break;  // uniform per wave
-    const int r = y0 - 2 + m;
-    if (!(p.per_y || (r >= 1 && r <= ny - 2))) continue;
+  // ---- phase 2: S and R of rows y0 - 2 .. y0 + kTileRows + 1.
+  const int m = w - 2;
+  const int r = y0 - 2 + m;
+  if (m >= 0 && m < kTileMid && (p.per_y || (r >= 1 && r <= ny - 2))) {
     const int rm = p.per_y ? wrap_near(r, ny) : r;
     Real wyr[kWeightsPerNode];
     row_weights(weights_y<Real>(p), rm, wyr);
@@ -685,7 +695,7 @@ __global__ __launch_bounds__(kTileWaves * kLanes) void tile_step_kernel(StepPara
           for (int dx = -1; dx <= 1; ++dx) {
             if ((dx == -1 && !src_xl) || (dx == 1 && !src_xr)) continue;
             if (dx == 0 && dy == 0) continue;
-            const Real* Xb = wall_brackets<Real>(p, wall_side_of(dx, dy));
+            const Real* Xb = tX + wall_side_of(dx, dy) * kQ;
             const Real r1 = Real(w_of(1)) * rho, r2 = Real(w_of(5)) * rho;
             Real* slotW = tR + (m + dy) * (kQ - 1) * kLanes;
 #pragma unroll
@@ -699,15 +709,15 @@ __global__ __launch_bounds__(kTileWaves * kLanes) void tile_step_kernel(StepPara
   __syncthreads();
 
   // ---- phase 3: the new state of the wave's output row o (R rows o-2..o+2
-  // are tile rows jout-4 .. jout).
+  // are rows w-4 .. w of tR).
   {
-    const int o = y0 - kHalo + jout;
-    if (o < y1 && (p.per_y || (o >= 1 && o <= ny - 2))) {
+    const int o = y0 - kHalo + w;
+    if (o >= y0 && o < y1 && (p.per_y || (o >= 1 && o <= ny - 2))) {
       Real wyr[kWeightsPerNode];
       row_weights(weights_y<Real>(p), o, wyr);
       const Real* rb[5];
 #pragma unroll
-      for (int k2 = 0; k2 < 5; ++k2) rb[k2] = tR + (jout - kHalo + k2) * (kQ - 1) * kLanes + lane;
+      for (int k2 = 0; k2 < 5; ++k2) rb[k2] = tR + (w - kHalo + k2) * (kQ - 1) * kLanes + lane;
       Real out[kQ];
       out[0] = qout[0];
 #pragma unroll
@@ -733,7 +743,7 @@ __global__ __launch_bounds__(kTileWaves * kLanes) void tile_step_kernel(StepPara
   }
   if (kWalls) {
     __syncthreads();  // the tile's stores are visible to the block
-    piece_walls(p, dst, x0, x1, y0, y1, threadIdx.x, kTileWaves * kLanes);
+    piece_walls(p, dst, x0, x1, y0, y1, threadIdx.x, kTileWaves * kLanes, tU);
   }
 }
 
@@ -955,7 +965,7 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, 0), (kMinWaves<Stor
       iteration(it + 1, gB, qB, qA);
     }
     __syncthreads();  // the next piece reuses the ring; the piece's stores are visible
-    if (kWalls) piece_walls(p, dst, x0, x1, y0, y1, threadIdx.x % kBlockThreads, kBlockThreads);
+    if (kWalls) piece_walls(p, dst, x0, x1, y0, y1, threadIdx.x % kBlockThreads, kBlockThreads, p.uw);
   }
 }
 

@@ -454,7 +454,7 @@ __global__ __launch_bounds__(kPairWaves * kLanes, 2) void pair_step_kernel(StepP
       const int x1 = min(x0 + kPairOut, p.nx);
       march_piece<kForce, true>(p, plan.wy16, hand, lane, role, x0, x1, y0, y1);
       __syncthreads();  // the piece's stores are visible to the block
-      piece_walls(p, static_cast<double*>(p.dst), x0, x1, y0, y1, threadIdx.x, kPairWaves * kLanes);
+      piece_walls(p, static_cast<double*>(p.dst), x0, x1, y0, y1, threadIdx.x, kPairWaves * kLanes, p.uw);
       return;
     }
     block -= plan.frame;

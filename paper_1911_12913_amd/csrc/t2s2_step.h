@@ -160,10 +160,11 @@ __device__ inline Real force_term(int q, const StepParams& p, Real ux, Real uy, 
 // piece's outputs (columns [x0, x1)), which this block has just stored, so
 // the loads see them (the coherence point is L2; the buffer was not read
 // earlier in the launch).  Each wall node has exactly one source node, and
-// each source node is output by exactly one piece.
+// each source node is output by exactly one piece.  uw: the walls'
+// velocities (p.uw or a copy of it).
 template <typename Store>
 __device__ inline void piece_walls(const StepParams& p, Store* dst, int x0, int x1, int y0,
-                                   int y1, int tid, int nthreads) {
+                                   int y1, int tid, int nthreads, const double (*uw)[2]) {
   using Real = typename Cvt<Store>::R;
   const int nx = p.nx, ny = p.ny;
   // Interior output columns and rows of this strip-piece.
@@ -212,10 +213,9 @@ __device__ inline void piece_walls(const StepParams& p, Store* dst, int x0, int 
       for (int dx = -1; dx <= 1; ++dx) {
         if ((dx == -1 && !wl) || (dx == 1 && !wr)) continue;
         if (dx == 0 && dy == 0) continue;
-        double ub, vb;
-        wall_velocity(p, i + dx, j + dy, ub, vb);
+        const int side = wall_side_of(dx, dy);
         Real sh[kQ];
-        nee_shift(rho, ux, uy, ub, vb, sh);
+        nee_shift(rho, ux, uy, uw[side][0], uw[side][1], sh);
         const long long wo = static_cast<long long>(j + dy) * p.pitch + (i + dx);
 #pragma unroll
         for (int q = 0; q < kQ; ++q) dst[q * p.plane + wo] = Cvt<Store>::st(v[q] + sh[q]);
