@@ -273,8 +273,10 @@ size_t t2s2_adjoint_scratch_bytes(const t2s2_ctx* ctx);
  * adjoint's buffers (ny * pitch elements of its arithmetic type) is not
  * under 4 GiB (16-bit storage above about 1.07 G nodes).  Plans the
  * reverse march from the device's compute units and the kernels' occupancy
- * (blocks of four waves, or eight on small meshes; the environment variable
- * T2S2_ADJ_ROWS=4 or 8, read here, forces the shape); launches nothing. */
+ * (blocks of four waves, or eight; on small meshes tiles of one or two rows
+ * per wave; the environment variable T2S2_ADJ_ROWS=4 or 8, read here, forces
+ * the march with that block shape, 16 or 17 the tiles while there are at most
+ * 1024 of them); launches nothing. */
 int t2s2_bind_adjoint(t2s2_ctx* ctx, void* scratch);
 
 /* lambda = d(<gu, u> + <gv, v>)/dg of the velocity of eq 3.3 at every node,

@@ -18,7 +18,8 @@
 // nodes and their interior neighbours, where alone it differs from
 // lam_{n+1}; [5'] .. [1'] then run in one kernel that marches down strips of
 // the mesh like the forward step, holding lamS in an LDS ring, so neither
-// lamR nor lamS goes to memory.  The wall-to-fluid scatter of [4] and [6] is
+// lamR nor lamS goes to memory.  On small meshes one kernel takes [6'] ..
+// [1'] tile by tile.  The wall-to-fluid scatter of [4] and [6] is
 // gathered at the fluid node, so no atomics are needed and the result is
 // deterministic.  d/d omega of the step (omega = dt / tau) enters only
 // through the pointwise coefficients; its inner products with the adjoints
@@ -29,6 +30,7 @@
 
 #include "t2s2_device.h"
 #include "t2s2_internal.h"
+#include "t2s2_step.h"
 
 namespace t2s2 {
 namespace {
@@ -215,7 +217,7 @@ __device__ inline void load9(const T* base, long long plane, long long off, T v[
 // differs from lam: the wall nodes and the interior nodes next to a wall
 // (the two outermost rows and columns of each walled axis).  This kernel
 // writes mu there; the reverse march reads mu on the frame and lam
-// everywhere else.
+// everywhere else.  (Tiles form mu themselves.)
 template <typename Store>
 __global__ __launch_bounds__(256) void adj_out_walls(AdjParams a, const Store* next,
                                                       const typename Cvt<Store>::R* lam) {
@@ -699,6 +701,381 @@ __global__ __launch_bounds__(kLanes * kRows, (adj_waves_per_simd<Store, kRows, k
   if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
 }
 
+// ---- [6'] .. [1'] of small meshes, one tile per block: 56 output columns and
+// the output rows of kWaves * kH rows less the halo of four on each side;
+// wave w holds rows w and (kH = 2) w + kWaves of the tile in every phase.  Two
+// barriers:
+//   1. mu of the rows from lam (zero off the interior; at the nodes next to a
+//      wall with the extrapolation of the wall nodes transposed, as in
+//      adj_out_walls), its y-moving populations to LDS;
+//   2. lamR = L^T mu and lamS of all but the outer two rows, lamS's y-moving
+//      populations to LDS;
+//   3. lamP and lam_n of the output rows.
+// The x taps and the other populations stay in the wave's registers.  The
+// stages are adj_strip's.
+//
+// On small meshes the march is a chain of phases, each with its loads and
+// barriers (20 rows per block at 513^2, so four turns of two phases and a
+// launch for the frame before it); the tile takes each phase once.  What
+// bounds it is that chain's latency, and from 500^2 up the arithmetic (FP32:
+// about 290 and 400 vector instructions per row in phases 2 and 3).  Two rows
+// per wave make the halo a smaller share and keep 513^2 to one round of
+// blocks in FP32.  The reverse stages of a step, us, march -> tile, cavity
+// 129^2 / 257^2 / 385^2 / 513^2 / 769^2: FP32 23.9 -> 13.4, 27.9 -> 13.9,
+// 34.1 -> 21.0, 39.5 -> 24.6, 55.9 -> 44.1; FP64 28.9 -> 20.4, 34.3 -> 23.4,
+// 42.0 -> 25.1, 50.1 -> 40.2, 74.4 -> 61.2.
+constexpr int kYMoving = 6;  // populations with xi_y != 0
+
+__device__ constexpr int y_slot(int q) {
+  int n = 0;
+  for (int k = 0; k < q; ++k) n += ey_of(k) != 0 ? 1 : 0;
+  return n;
+}
+
+template <typename Store, bool kWalls, int kWaves, int kH>
+__global__ __launch_bounds__(kWaves* kLanes) void adj_tile(
+    AdjParams a, const Store* g, const Store* next, const typename Cvt<Store>::R* lam,
+    typename Cvt<Store>::R* lam_out, double* partial) {
+  using Real = typename Cvt<Store>::R;
+  constexpr int kIn = kWaves * kH;          // rows of mu
+  constexpr int kMid = kIn - 4;             // rows of lamS
+  constexpr int kOut = kIn - 2 * kHalo;     // rows of lam_n
+  // The FP32 forms have the registers to issue loads long before their use.
+  constexpr bool kEarly = sizeof(Real) == 4;
+  __shared__ Real tM[kIn * kYMoving * kLanes];   // mu: [row][slot][lane]
+  __shared__ Real tS[kMid * kYMoving * kLanes];  // lamS: [row][slot][lane]
+  __shared__ double red[kWaves];
+  const int lane = threadIdx.x & (kLanes - 1);
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
+  const int nx = a.nx, ny = a.ny;
+  const bool per_x = !kWalls || a.per_x, per_y = !kWalls || a.per_y;
+  const unsigned long long pbr = static_cast<unsigned long long>(a.plane) * sizeof(Real);
+  const unsigned long long pbs = static_cast<unsigned long long>(a.plane) * sizeof(Store);
+  const Real* WX = wtab_x<Real>(a);
+  const Real* WY = wtab_y<Real>(a);
+  const int ntiles = (ny + kOut - 1) / kOut;
+  const int strip = blockIdx.x / ntiles;
+  const int y0 = (blockIdx.x % ntiles) * kOut;
+  const int y1 = min(y0 + kOut, ny);
+  const int x1 = min(strip * kStripOut + kStripOut, nx);
+  const int c0 = strip * kStripOut - kHalo + lane;  // this lane's column, unwrapped
+  const bool in_x = per_x || (c0 >= 0 && c0 < nx);
+  const int c = per_x ? wrap(c0, nx) : clampi(c0, 0, nx - 1);
+  const bool col_int = in_x && (per_x || (c0 >= 1 && c0 <= nx - 2));
+  const bool lane_o = lane >= kHalo && lane < kLanes - kHalo && c0 < x1;
+  const bool xl = !per_x && c0 == 1, xr = !per_x && c0 == nx - 2;
+  double dw = 0.0;
+
+  // The wave's row h: y unwrapped, r the grid row it loads (off the grid of a
+  // walled y axis the nearest one; its values are zero there).
+  auto y_of = [&](int h) { return y0 - kHalo + w + kWaves * h; };
+  auto r_of = [&](int h) {
+    return per_y ? wrap_near(y_of(h), ny) : clampi(y_of(h), 0, ny - 1);
+  };
+  auto off_of = [&](int h) {
+    return static_cast<unsigned>(static_cast<long long>(r_of(h)) * a.pitch + c);
+  };
+  auto interior_row = [&](int h) { return per_y || (y_of(h) >= 1 && y_of(h) <= ny - 2); };
+  auto mid_row = [&](int h) {
+    const int m = w + kWaves * h;
+    return m >= 2 && m < kIn - 2;
+  };
+  auto out_row = [&](int h) {
+    const int m = w + kWaves * h;
+    return m >= kHalo && m < kIn - kHalo && y_of(h) < y1;
+  };
+  // Beside, above or below: the row has a wall row next to it (uniform per
+  // wave); which one, and the walls' velocities.
+  auto edge_row = [&](int h) { return kWalls && !per_y && (y_of(h) == 1 || y_of(h) == ny - 2); };
+  const bool side = xl || xr;
+  const int bc = xl ? 0 : nx - 1;
+  // Velocity of wall row or column k (sides 0 left, 1 right, 2 bottom, 3 top).
+  auto wall_u = [&](int k, Real& u, Real& v) {
+    u = static_cast<Real>(a.uw[k][0]);
+    v = static_cast<Real>(a.uw[k][1]);
+  };
+  const int ks = xl ? 0 : 1;
+
+  // y weight of tap k, sign class sc, at source row yi (wave-uniform; rows off
+  // the interior carry zeros, so the nearest row's weight will do there).
+  using CReal = const __attribute__((address_space(4))) Real*;
+  auto ywt = [&](int yi, int sc, int k) {
+    const int ym = per_y ? wrap_near(yi, ny) : clampi(yi, 0, ny - 1);
+    const int idx = __builtin_amdgcn_readfirstlane(ym * kWeightsPerNode + sc * kTaps + k);
+    return ((CReal)(WY))[idx];
+  };
+
+  // ---- phase 1: mu.
+  Real mu[kH][kQ], sv[kH][kQ];
+#pragma unroll
+  for (int h = 0; h < kH; ++h)
+    load_planes(lam, pbr, off_of(h) * static_cast<unsigned>(sizeof(Real)), mu[h]);
+  auto load_s = [&](int h) {
+    load_planes(static_cast<const Real*>(a.S), pbr, off_of(h) * static_cast<unsigned>(sizeof(Real)),
+                sv[h]);
+  };
+  if (kEarly) {
+#pragma unroll
+    for (int h = 0; h < kH; ++h)
+      if (mid_row(h)) load_s(h);
+  }
+  Real wx[kWeightsPerNode];
+#pragma unroll
+  for (int k = 0; k < kWeightsPerNode; ++k) wx[k] = in_x ? WX[c * kWeightsPerNode + k] : Real(0);
+#pragma unroll
+  for (int h = 0; h < kH; ++h) {
+    const bool nin = col_int && interior_row(h), edge = edge_row(h);
+    if (kWalls && nin && (side || edge)) {
+      // The wall nodes extrapolated from this node: beside it, above or below
+      // it, and at the corners both and the diagonal one.
+      const int r = r_of(h), br = y_of(h) == 1 ? 0 : ny - 1;
+      const int ke = br == 0 ? 2 : 3;
+      Store ns[kQ];
+      Real l1[kQ], l2[kQ], l3[kQ];
+      auto load_lam = [&](int col, int row, Real (&out)[kQ]) {
+        load_planes(lam, pbr, static_cast<unsigned>(static_cast<long long>(row) * a.pitch + col) *
+                                  static_cast<unsigned>(sizeof(Real)), out);
+      };
+      load_planes(next, pbs, off_of(h) * static_cast<unsigned>(sizeof(Store)), ns);
+      // A node without one of the three loads its own lam there, unused.
+      if (kEarly) {
+        load_lam(side ? bc : c, r, l1);
+        if (edge) {
+          load_lam(c, br, l2);
+          load_lam(side ? bc : c, br, l3);
+        }
+      }
+      Real o[kQ];
+#pragma unroll
+      for (int q = 0; q < kQ; ++q) o[q] = Cvt<Store>::ld(ns[q]);
+      Real d, rho, ux, uy;
+      node_rho_u(o, d, rho, ux, uy);
+      auto add = [&](const Real (&lb)[kQ], int k) {
+        Real ub, vb, sa, sbx, sby;
+        wall_u(k, ub, vb);
+        shift_ab(rho, ux, uy, ub, vb, lb, sa, sbx, sby);
+#pragma unroll
+        for (int q = 0; q < kQ; ++q) mu[h][q] += lb[q];
+        through_moments(rho, ux, uy, sa, sbx, sby, mu[h], true);
+      };
+      if (kEarly) {
+        if (side) add(l1, ks);
+        if (edge) {
+          add(l2, ke);
+          if (side) add(l3, ks);
+        }
+      } else {
+#pragma unroll 1
+        for (int k = 0; k < 3; ++k) {
+          const bool dx = k != 1, dy = k != 0;
+          if ((dx && !side) || (dy && !edge)) continue;
+          load_lam(dx ? bc : c, dy ? br : r, l1);
+          add(l1, dx ? ks : ke);
+        }
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) {
+      if (kWalls) mu[h][q] = nin ? mu[h][q] : Real(0);
+      if (ey_of(q) != 0)
+        tM[((w + kWaves * h) * kYMoving + y_slot(q)) * kLanes + lane] = mu[h][q];
+    }
+  }
+  __syncthreads();
+
+  // The y taps of population q of L^T at row j of buf, with the weights wy
+  // of the source rows; the x taps of the wave's own row.
+  auto y_taps = [&](const Real* buf, int j, int q, const Real (&wy)[2][kTaps]) {
+    const int s = ey_of(q) > 0 ? 0 : 1;
+    Real acc = Real(0);
+#pragma unroll
+    for (int k = 0; k < kTaps; ++k)
+      acc += wy[s][k] * buf[((j - tap_offset(s, k)) * kYMoving + y_slot(q)) * kLanes + lane];
+    return acc;
+  };
+  auto x_part = [&](int q, Real m) {
+    if (ex_of(q) > 0)  // offsets -2, -1, 0, +1
+      return from_above(from_above(wx[0] * m)) + from_above(wx[1] * m) + wx[2] * m +
+             from_below(wx[3] * m);
+    if (ex_of(q) < 0)  // offsets -1, 0, +1, +2
+      return from_above(wx[4] * m) + wx[5] * m + from_below(wx[6] * m) +
+             from_below(from_below(wx[7] * m));
+    return Real(0);
+  };
+  auto row_wy = [&](int h, Real (&wy)[2][kTaps]) {
+#pragma unroll
+    for (int sc = 0; sc < 2; ++sc) {
+#pragma unroll
+      for (int k = 0; k < kTaps; ++k) wy[sc][k] = ywt(y_of(h) - tap_offset(sc, k), sc, k);
+    }
+  };
+
+  // ---- phase 2: lamS.
+  Real ls[kH][kQ];
+  Store gs[kH][kQ];
+  auto load_g = [&](int h) {
+    load_planes(g, pbs, off_of(h) * static_cast<unsigned>(sizeof(Store)), gs[h]);
+  };
+#pragma unroll
+  for (int h = 0; h < kH; ++h) {
+    if (!mid_row(h)) continue;
+    if (!kEarly) load_s(h);
+    if (kEarly && out_row(h)) load_g(h);
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) ls[h][q] = Real(0);
+    if (interior_row(h)) {  // uniform per wave
+      const int j = w + kWaves * h;
+      const bool nin = col_int;
+      Real wy[2][kTaps];
+      row_wy(h, wy);
+      Real lr[kQ];
+      lr[0] = Real(0);
+#pragma unroll
+      for (int q = 1; q < kQ; ++q) {
+        if (ey_of(q) != 0) mu[h][q] = tM[(j * kYMoving + y_slot(q)) * kLanes + lane];
+        lr[q] = x_part(q, mu[h][q]);
+        if (ey_of(q) != 0) {
+          const Real ly = y_taps(tM, j, q, wy);
+          lr[q] += kWalls ? (col_int ? ly : Real(0)) : ly;
+        }
+      }
+      // lamR of the x-wall neighbour
+      Real lw[kQ];
+      lw[0] = Real(0);
+      if (kWalls && !per_x) {
+#pragma unroll
+        for (int q = 1; q < kQ; ++q) {
+          const Real lo = from_below(lr[q]), hi = from_above(lr[q]);
+          lw[q] = xl ? lo : hi;
+        }
+      }
+      if (nin) {
+        Real d, rho, ux, uy;
+        node_rho_u(sv[h], d, rho, ux, uy);
+        if (kWalls) {
+          auto add_wall = [&](const Real (&lb)[kQ], int k) {
+            Real ub, vb, sa, sbx, sby;
+            wall_u(k, ub, vb);
+            shift_ab(rho, ux, uy, ub, vb, lb, sa, sbx, sby);
+#pragma unroll
+            for (int q = 0; q < kQ; ++q) lr[q] += lb[q];
+            through_moments(rho, ux, uy, sa, sbx, sby, ls[h], true);
+          };
+          if (side) add_wall(lw, ks);
+          if (edge_row(h)) {
+            // lamR of the wall row: its y taps from this row and the next
+            // one inwards (the other sources are off the interior).
+            const int r = r_of(h);
+            const bool bottom = r == 1;
+            const int in = bottom ? 1 : -1;  // inwards
+            const Real w1[2] = {ywt(r, 0, bottom ? 1 : 3), ywt(r, 1, bottom ? 0 : 2)};
+            const Real w2 = ywt(r + in, bottom ? 0 : 1, bottom ? 0 : 3);
+            Real lb[kQ];
+#pragma unroll
+            for (int q = 0; q < kQ; ++q) {
+              lb[q] = Real(0);
+              if (ey_of(q) == 0) continue;
+              const bool two = (ey_of(q) > 0) == bottom;  // uniform per wave
+              lb[q] = (two ? w2 : Real(0)) * tM[((j + in) * kYMoving + y_slot(q)) * kLanes + lane] +
+                      w1[ey_of(q) > 0 ? 0 : 1] * mu[h][q];
+            }
+            add_wall(lb, bottom ? 2 : 3);
+          }
+        }
+        Real feq[kQ];
+        feq_of(d, rho, ux, uy, feq);
+        Real fa, fbx, fby;
+        feq_ab(rho, ux, uy, lr, fa, fbx, fby);
+        Real jt[kQ];
+        const Real cRe = static_cast<Real>(a.cRe);
+        through_moments(rho, ux, uy, cRe * fa, cRe * fbx, cRe * fby, jt, false);
+        Real dn = Real(0);  // this node's <lamR, d R / d cRs>
+#pragma unroll
+        for (int q = 0; q < kQ; ++q) {
+          ls[h][q] += static_cast<Real>(a.cRs) * lr[q] + jt[q];
+          dn += lr[q] * (sv[h][q] - feq[q]);
+        }
+        if (lane_o && out_row(h)) dw += a.dcRs * static_cast<double>(dn);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kQ; ++q)
+      if (ey_of(q) != 0)
+        tS[((w + kWaves * h - 2) * kYMoving + y_slot(q)) * kLanes + lane] = ls[h][q];
+  }
+  __syncthreads();
+
+  // ---- phase 3: lam_n.
+#pragma unroll
+  for (int h = 0; h < kH; ++h) {
+    if (!out_row(h)) continue;  // uniform per wave
+    const int j = w + kWaves * h;
+    const Real A = static_cast<Real>(a.A);
+    if (!kEarly) load_g(h);
+    Real wy[2][kTaps];
+    row_wy(h, wy);
+    // The y-moving populations of mu and lamS come back from LDS, which frees
+    // their registers across the barrier.
+    Real v[kQ], lp[kQ];
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) {
+      if (ey_of(q) == 0) continue;
+      mu[h][q] = tM[(j * kYMoving + y_slot(q)) * kLanes + lane];
+      ls[h][q] = tS[((j - 2) * kYMoving + y_slot(q)) * kLanes + lane];
+    }
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) v[q] = Cvt<Store>::ld(gs[h][q]);
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) {
+      Real acc = x_part(q, ls[h][q]);
+      if (ey_of(q) != 0) acc += y_taps(tS, j - 2, q, wy);
+      lp[q] = ls[h][q] + (q == 0 ? Real(0) : A * acc);
+    }
+    Real d, rho, ux, uy;
+    node_rho_u(v, d, rho, ux, uy);
+    Real feq[kQ], mix[kQ];
+    feq_of(d, rho, ux, uy, feq);
+#pragma unroll
+    for (int q = 0; q < kQ; ++q)
+      mix[q] = static_cast<Real>(a.cPe) * lp[q] + static_cast<Real>(a.cQe) * mu[h][q];
+    Real fa, fbx, fby;
+    feq_ab(rho, ux, uy, mix, fa, fbx, fby);
+    Real out[kQ];
+    through_moments(rho, ux, uy, fa, fbx, fby, out, false);
+    Real dp = Real(0), dq = Real(0);  // this node's <lamP, g - feq>, <lamQ, g - feq>
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) {
+      out[q] += static_cast<Real>(a.cPg) * lp[q] + static_cast<Real>(a.cQg) * mu[h][q];
+      const Real neq = v[q] - feq[q];
+      dp += lp[q] * neq;
+      dq += mu[h][q] * neq;
+    }
+    if (lane_o) {
+      store_planes<false>(lam_out, pbr, off_of(h) * static_cast<unsigned>(sizeof(Real)), out);
+      dw += a.dcPg * static_cast<double>(dp) + a.dcQg * static_cast<double>(dq);
+    }
+  }
+  dw = wave_sum(dw);
+  if (lane == 0) red[w] = dw;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double s = 0.0;
+    for (int k = 0; k < kWaves; ++k) s += red[k];
+    partial[blockIdx.x] = s;
+  }
+}
+
+// Tile shapes: one row per wave, and two (FP64 with fewer waves: its LDS and
+// registers hold 24 rows).
+template <typename Store, bool kTall>
+constexpr int tile_waves() {
+  return kTall && sizeof(typename Cvt<Store>::R) == 8 ? 12 : 16;
+}
+template <typename Store, bool kTall>
+constexpr int tile_out_rows() {
+  return tile_waves<Store, kTall>() * (kTall ? 2 : 1) - 2 * kHalo;
+}
+
 // accum += scale * (the sum of the n block partials of d/d omega), by one
 // wave: lane l adds partials l, l + 64, ... in that order, then the lanes
 // are summed by the butterfly; the same order on every run.  scale is
@@ -783,6 +1160,24 @@ hipError_t adjoint_reverse_t(const AdjParams& a, const void* state_n, const void
   const bool walls = !a.per_x || !a.per_y;
   const Real* mu = static_cast<const Real*>(lam_np1);
   const Store* g = static_cast<const Store*>(state_n);
+  Real* lo = static_cast<Real*>(lam_n);
+  int blocks = a.march_grid;
+  const int nstrips = (a.nx + kStripOut - 1) / kStripOut;
+  if (a.march_rows >= kAdjTiles) {
+    const Store* nx = static_cast<const Store*>(a.next);
+    auto go = [&](auto kernel, int waves) {
+      hipLaunchKernelGGL(kernel, dim3(blocks), dim3(waves * kLanes), 0, s, a, g, nx, mu, lo, partial);
+    };
+    constexpr int kW1 = tile_waves<Store, false>(), kW2 = tile_waves<Store, true>();
+    if (a.march_rows == kAdjTiles)
+      walls ? go(adj_tile<Store, true, kW1, 1>, kW1) : go(adj_tile<Store, false, kW1, 1>, kW1);
+    else
+      walls ? go(adj_tile<Store, true, kW2, 2>, kW2) : go(adj_tile<Store, false, kW2, 2>, kW2);
+    if (accum)
+      hipLaunchKernelGGL(adj_accumulate, dim3(1), dim3(64), 0, s, partial, blocks,
+                         a.dnu_per_domega, accum);
+    return hipGetLastError();
+  }
   // mu on the frame of a walled domain; without walls mu is lam_np1 itself.
   const Real* muf = mu;
   if (walls) {
@@ -792,10 +1187,8 @@ hipError_t adjoint_reverse_t(const AdjParams& a, const void* state_n, const void
                        static_cast<const Store*>(a.next), mu);
     muf = static_cast<const Real*>(a.mu);
   }
-  const int nstrips = (a.nx + kStripOut - 1) / kStripOut;
-  const bool rows8 = a.march_rows8 != 0;
-  const int Gs = a.march_grid;
-  Real* lo = static_cast<Real*>(lam_n);
+  const bool rows8 = a.march_rows == 8;
+  const int Gs = blocks;
   if (rows8 && walls)
     hipLaunchKernelGGL((adj_strip<Store, 8, true>), dim3(Gs), dim3(kLanes * 8), 0, s, a, g, mu,
                        muf, lo, partial, nstrips);
@@ -840,8 +1233,13 @@ hipError_t march_blocks_per_cu(int& n) {
 // see adj_waves_per_simd).  Small meshes, where a four-wave block would
 // march fewer than kAdjRows8Below strip-rows, take eight-wave blocks: a
 // block then marches twice the rows and fewer of its rows are the two-row
-// halos above and below its range.  The plan is fixed per context, so the
-// order of the d/d omega reduction is too.
+// halos above and below its range.  Still smaller ones take tiles: those of
+// one row per wave while each CU gets at most one (FP32 340^2, past that:
+// 24.2 us against 21.7 with two rows per wave; 300^2, before it: 14.8 against
+// 20.9), else those of two rows per wave up to three blocks per CU in FP32
+// and four in FP64 (cavity: FP64 945^2 87 us against the march's 101; FP32
+// 769^2 44 against 56, but 1100^2, at 3.6 blocks per CU, 80 against 77).  The
+// plan is fixed per context, so the order of the d/d omega reduction is too.
 template <typename Store>
 hipError_t plan_march_t(AdjParams& a, int cus) {
   const bool walls = !a.per_x || !a.per_y;
@@ -857,13 +1255,25 @@ hipError_t plan_march_t(AdjParams& a, int cus) {
   };
   const int g4 = grid(n4);
   const long long nstrips = (a.nx + kStripOut - 1) / kStripOut;
-  a.march_rows8 = nstrips * a.ny < kAdjRows8Below * g4 ? 1 : 0;
-  // T2S2_ADJ_ROWS=4 or 8 forces the block shape (tests compare the two).
+  auto tiles = [&](int rows) { return nstrips * ((a.ny + rows - 1) / rows); };
+  const long long t1 = tiles(tile_out_rows<Store, false>()), t2 = tiles(tile_out_rows<Store, true>());
+  a.march_rows = nstrips * a.ny < kAdjRows8Below * g4 ? 8 : 4;
+  const int rounds = sizeof(typename Cvt<Store>::R) == 8 ? 4 : 3;
+  if (t2 <= static_cast<long long>(rounds) * cus && t2 <= kAdjMaxBlocks)
+    a.march_rows = kAdjTiles + 1;
+  if (t1 <= cus) a.march_rows = kAdjTiles;
+  // T2S2_ADJ_ROWS=4 or 8 forces the march and its block shape, 16 or 17 the
+  // tiles where each has a partial (tests compare them).
   if (const char* env = std::getenv("T2S2_ADJ_ROWS")) {
-    if (env[0] == '4' && env[1] == 0) a.march_rows8 = 0;
-    if (env[0] == '8' && env[1] == 0) a.march_rows8 = 1;
+    const int rows = std::atoi(env);
+    if (rows == 4 || rows == 8 || (rows == kAdjTiles && t1 <= kAdjMaxBlocks) ||
+        (rows == kAdjTiles + 1 && t2 <= kAdjMaxBlocks))
+      a.march_rows = rows;
   }
-  a.march_grid = a.march_rows8 ? grid(n8) : g4;
+  a.march_grid = a.march_rows == kAdjTiles       ? static_cast<int>(t1)
+                 : a.march_rows == kAdjTiles + 1 ? static_cast<int>(t2)
+                 : a.march_rows == 8             ? grid(n8)
+                                                 : g4;
   return hipSuccess;
 }
 

@@ -185,9 +185,10 @@ struct AdjParams {
   void* S;     // S, from the recompute of the step
   void* mu;    // adjoint of the interior output (= adjoint of Q); walled domains
   void* next;  // f~^{n+1} recomputed (storage type)
-  // Plan of the reverse march (plan_adjoint_march): eight-wave blocks or
-  // four, and the block count (at most kAdjMaxBlocks).
-  int march_rows8;
+  // Plan of the reverse stages (plan_adjoint_march): the march with blocks of
+  // four or eight waves, or tiles (kAdjTiles with one row per wave,
+  // kAdjTiles + 1 with two); and the block count (at most kAdjMaxBlocks).
+  int march_rows;
   int march_grid;
 };
 
@@ -195,6 +196,7 @@ constexpr int kDiagBlocks = 512;
 constexpr int kDiagSlots = 8;
 // Blocks of the reverse march of the adjoint (one d/d omega partial each).
 constexpr int kAdjMaxBlocks = 1024;
+constexpr int kAdjTiles = 16;
 
 // Launchers (t2s2_kernels.hip).  Return hipError_t of the launch.
 hipError_t launch_step(int storage, const StepParams& p, int grid, hipStream_t s);

@@ -252,6 +252,45 @@ def test_adjoint_march_block_shapes_agree(storage, monkeypatch):
         assert abs(outs[0][1] - outs[1][1]) <= 1e-12 * abs(outs[1][1])
 
 
+@pytest.mark.parametrize("storage", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("rows", ["16", "17"])
+def test_adjoint_tiles_are_the_march(rows, storage, monkeypatch):
+    """The reverse stages by tiles of one row per wave and of two (forced with
+    T2S2_ADJ_ROWS) give the march's lambda_n and dL/dnu.  Both sum each
+    value's terms (about 100, of one size) in their own order: eps times 100
+    of the largest value bounds the difference, for lambda_n and, with the
+    products' sums over the nodes in FP64, for dL/dnu relative to the sum of
+    its terms' magnitudes, which the random lambda keeps within 1e3 of the
+    result.  Sizes: the smallest meshes, a tile's last and first row and
+    column at either wall (8, 16 and 24 output rows, 56 columns), wall columns
+    in a neighbour strip's halo, one walled axis."""
+    eps = 2.2e-16 if storage == "f64" else 1.2e-7
+    cases = [W.cavity_case(n, lid=0.1, re=400.0, cfl=0.9, eta=0.1, noise=1e-3, seed=n)
+             for n in (5, 9, 24, 48, 58, 60, 114)]
+    cases += [W.tgv_case(nx, ny, u0=0.05, nu=0.01, cfl=0.6, eta=0.05)
+              for nx, ny in ((5, 6), (56, 24), (57, 25), (113, 41))]
+    cases += [_one_walled_axis(False), _one_walled_axis(True)]
+    for case in cases:
+        print(f"[gpu] adjoint tiles {case.name} {case.nx}x{case.ny} {storage} {rows}", flush=True)
+        w = W.random_state((9, case.ny, case.nx), 1.0, 23)
+        outs = []
+        for force in ("4", rows):
+            monkeypatch.setenv("T2S2_ADJ_ROWS", force)
+            ctx = t2s2.context_for_case(case, storage=storage)
+            ctx.enable_adjoint()
+            ctx.init_macro(case.rho0, case.ux0, case.uy0)
+            ctx.step(3)
+            state = ctx.save_state()
+            lam_w = ctx.adjoint_load(w)
+            lam_out = ctx.adjoint_buffer()
+            acc = torch.zeros(1, dtype=torch.float64, device="cuda:0")
+            ctx.adjoint_step(state, lam_w, lam_out, acc)
+            outs.append((ctx.adjoint_read(lam_out).cpu().numpy(), float(acc.item())))
+            ctx.close()
+        assert np.abs(outs[0][0] - outs[1][0]).max() <= 100 * eps * np.abs(outs[0][0]).max()
+        assert abs(outs[0][1] - outs[1][1]) <= 1e5 * eps * abs(outs[0][1])
+
+
 @pytest.mark.parametrize("storage", ["f64", "f32"])
 @pytest.mark.parametrize("kind", ["cavity", "tgv", "cavity_t1s2"])
 def test_stored_adjoint_step_is_the_recomputing_one(kind, storage):
