@@ -724,14 +724,6 @@ __global__ __launch_bounds__(kLanes * kRows, (adj_waves_per_simd<Store, kRows, k
 // 129^2 / 257^2 / 385^2 / 513^2 / 769^2: FP32 23.9 -> 13.4, 27.9 -> 13.9,
 // 34.1 -> 21.0, 39.5 -> 24.6, 55.9 -> 44.1; FP64 28.9 -> 20.4, 34.3 -> 23.4,
 // 42.0 -> 25.1, 50.1 -> 40.2, 74.4 -> 61.2.
-constexpr int kYMoving = 6;  // populations with xi_y != 0
-
-__device__ constexpr int y_slot(int q) {
-  int n = 0;
-  for (int k = 0; k < q; ++k) n += ey_of(k) != 0 ? 1 : 0;
-  return n;
-}
-
 template <typename Store, bool kWalls, int kWaves, int kH>
 __global__ __launch_bounds__(kWaves* kLanes) void adj_tile(
     AdjParams a, const Store* g, const Store* next, const typename Cvt<Store>::R* lam,

@@ -255,6 +255,37 @@ constexpr long long kPairPieceWork = 25;
 // (Cavity 2049^2: 115.9 us per step at 1.5 / 1.5, 116.2 at 2 / 2, 118.4 at
 // 3 / 2.5; 4097^2: 375.8 at 2 / 1.5, 381.7 at 3 / 2.)
 constexpr double kPairEdgeCost = 2.0, kPairTopCost = 1.5;
+// Which kernel takes single steps of scheme 1 with A > 0: the march (0) or
+// tiles of one row per wave (1) or two (2), by the rounds of tiles the CUs
+// take.  A CU holds one tile of either shape in FP64, two one-row tiles or one
+// two-row tile in the narrower forms; the two-row tiles spend less on halo
+// rows, but fewer of them may leave CUs idle.  Measured, us per step (march /
+// one row / two rows):
+//   FP64 one-row tiles while each CU gets at most one: cavity 321^2
+//     - / 10.6 / 12.4, 385^2 - / 16.1 / 12.9; then two-row tiles up to four per
+//     CU with walls (897^2 45.1 / 54.9 / 42.1), two per CU on periodic grids
+//     (640^2 21.1 / 25.5 / 19.5, 768^2 28.2 / 37.3 / 28.8);
+//   narrower forms: one-row tiles up to twelve per CU (bf16 with stochastic
+//     rounding, cavity 1153^2 39.0 / 32.3 / 33.7, 1300^2 42.1 / 41.3 / 42.8),
+//     six in FP32 on periodic grids (768^2 18.5 / 18.1 / 16.8, 896^2
+//     21.0 / 22.0 / 26.5); two-row tiles where they alone take one round
+//     (FP32 cavity 513^2 21.6 / 13.4 / 12.5), but not the 16-bit forms on
+//     periodic grids (512^2 19.3 / 10.8 / 11.7).
+int plan_tile(const StepParams& sp, int storage, int cus) {
+  const bool walls = !sp.per_x || !sp.per_y;
+  auto tiles = [&](int kind) {
+    const int rows = step_tile_rows(storage, kind);
+    return static_cast<long long>(sp.nstrips) * ((sp.ny + rows - 1) / rows);
+  };
+  const long long t1 = tiles(1), t2 = tiles(2);
+  if (storage == kF64) {
+    if (t1 <= cus) return 1;
+    return t2 <= (walls ? 4LL : 2LL) * cus ? 2 : 0;
+  }
+  if (t1 > 2LL * cus && t2 <= cus && (walls || storage == kF32)) return 2;
+  return t1 <= (walls || storage != kF32 ? 12LL : 6LL) * cus ? 1 : 0;
+}
+
 // The two-step kernel takes meshes whose busiest block marches at least this
 // many rows (piece work included); on smaller ones the rows read again cost
 // more than the saved pass.  FP64, us per step, single steps / two-step:
@@ -721,13 +752,15 @@ int t2s2_bind(t2s2_ctx* c, void* state_a, void* state_b, void* workspace, void* 
   }
   c->grid = plan_blocks(c->sp, c->cfg.storage, cus);
   c->grid_gen = c->sp.single ? plan_blocks(c->sp_gen, c->cfg.storage, cus) : c->grid;
-  // Small meshes take the tile kernel (scheme 1, A > 0), when a march would
-  // leave each block fewer than kTileMaxMarchRows unit-rows; not when the
-  // block count is forced (T2S2_BLOCKS), which selects the march.
+  // Small meshes take the tile kernel (scheme 1, A > 0); not when the block
+  // count is forced (T2S2_BLOCKS), which selects the march.  T2S2_TILE=0, 1 or
+  // 2 forces the march or a tile shape.
   c->sp.tile = 0;
-  if (c->sp.scheme == 1 && !c->sp.single && !std::getenv("T2S2_BLOCKS") &&
-      static_cast<long long>(c->sp.nunits) * c->ny < static_cast<long long>(kTileMaxMarchRows) * c->grid)
-    c->sp.tile = 1;
+  if (c->sp.scheme == 1 && !c->sp.single && !std::getenv("T2S2_BLOCKS")) {
+    c->sp.tile = plan_tile(c->sp, c->cfg.storage, cus);
+    if (const char* t = std::getenv("T2S2_TILE"))
+      if (t[0] >= '0' && t[0] <= '2') c->sp.tile = t[0] - '0';
+  }
   if (!c->sp.single) c->sp_gen = c->sp;
   // Meshes that fit one block take all steps of a call in it (us per step,
   // FP64: forced channel 10 x 21 8.6 -> 2.6, Taylor-Green 32^2 6.3 -> 3.9;

@@ -506,32 +506,73 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, kScheme), (kMinWave
 
 // ---------------------------------------------------------------------------
 // Tile step for small meshes (T2S2-FDLBM1 family).  A block takes one strip
-// (56 output columns) and kTileRows output rows as a whole tile instead of
-// marching down a range of rows: it loads the tile's rows y0-4 ..
-// y0+kTileRows+3 at once, forms P of all of them (LDS) and Q of its output
-// rows (registers), then S and R of rows y0-2 .. y0+kTileRows+1 (LDS), then
-// the new state: three phases and two barriers, where a march over a few rows
-// runs four pipelined iterations of three phases each.  Each node takes the
-// expressions of step_kernel.  Wave w holds row y0 - 4 + w in every phase.
-// kSaveS also stores S at the interior nodes, as in step_kernel.
+// (56 output columns) and a whole tile of rows instead of marching down a
+// range of rows: it loads the tile's rows with their halo of four at once,
+// forms P of all of them and Q of its output rows, then S and R of all but the
+// outer two rows, then the new state: three phases and two barriers, where a
+// march over a few rows runs pipelined iterations of three phases each.  Each
+// node takes the expressions of step_kernel.  Wave w holds rows w and (kH =
+// 2) w + kWaves of the tile in every phase, so the x taps and the populations
+// that do not move in y stay in its registers; the y-moving ones of P and R go
+// through LDS.  kSaveS also stores S at the interior nodes, as in step_kernel.
 //
-// A chain of latencies bounds it: of the 9.7 us of a 257^2 FP64 cavity step
-// an empty launch is 3.5, P 0.5, S and R 1.8, the new state and its way to
-// memory 2.7, the wall nodes 1.2.  Sixteen waves, one per row, cover each
-// other's latencies better than eight that take two rows of P and of S in
-// turn: 257^2 cavity FP64 9.86 -> 9.70 us, FP32 8.65 -> 7.70, bf16 with
-// stochastic rounding 8.26 -> 7.20; 64^2 periodic FP64 6.83 -> 6.63.
+// A chain of latencies bounds it on the smallest meshes: of the 9.7 us of a
+// 257^2 FP64 cavity step an empty launch is 3.5, P 0.5, S and R 1.8, the new
+// state and its way to memory 2.7, the wall nodes 1.2.  Sixteen waves, one per
+// row, cover each other's latencies better than eight that take two rows of P
+// and of S in turn (257^2 cavity FP64 9.86 -> 9.70 us, FP32 8.65 -> 7.70).  On
+// larger ones the halo rows of the eight output rows count (16 of P and 12 of
+// S for 8): two rows per wave give 16 output rows in FP64 and 24 in the
+// narrower forms.  FP64 cavity, one row -> two rows per wave: 385^2
+// 16.1 -> 12.9 us, 641^2 29.7 -> 25.7, 769^2 41.4 -> 33.0; see plan_tile.
 // ---------------------------------------------------------------------------
-constexpr int kTileRows = 8;
-constexpr int kTileIn = kTileRows + 2 * kHalo;   // rows of P
-constexpr int kTileWaves = kTileIn;               // one wave per row of P
-constexpr int kTileMid = kTileRows + kHalo;      // rows of R
+// Tile shapes: kH rows per wave; FP64 with two has fewer waves (its LDS and
+// registers hold 24 rows).
+template <typename Store, int kH>
+constexpr int tile_waves() {
+  return kH == 2 && sizeof(typename Cvt<Store>::R) == 8 ? 12 : 16;
+}
+template <typename Store, int kH>
+constexpr int tile_rows() {
+  return kH * tile_waves<Store, kH>() - 2 * kHalo;
+}
 
-template <typename Store, bool kForce, bool kWalls, bool kSaveS = false>
-__global__ __launch_bounds__(kTileWaves * kLanes) void tile_step_kernel(StepParams p) {
+// Moments and brackets of a node, unforced FP32: velocity and eq_brackets
+// with their products fused as the compiler fuses them in step_kernel, where
+// the sums ux + uy and uy - ux take one of the two velocities as a product
+// (uy's where kFuseY, else ux's).  Left to the compiler here, another choice
+// would differ in the last bit, which stochastic rounding turns into whole
+// units of the 16-bit forms.
+template <bool kFuseY>
+__device__ inline void moments_f32(double s, double jx, double jy, float& r, float X[kQ]) {
+#pragma clang fp contract(off)
+  r = 1.0f + static_cast<float>(s);
+  const float r0 = __builtin_amdgcn_rcpf(r);
+  const float ir = __builtin_fmaf(__builtin_fmaf(-r, r0, 1.0f), r0, r0);
+  const float fx = static_cast<float>(jx), fy = static_cast<float>(jy);
+  const float x = fx * ir, y = fy * ir;
+  const float uu = 1.5f * __builtin_fmaf(x, x, y * y);
+  X[0] = -uu;
+  auto pair = [&](float e, int qp, int qm) {
+    const float T = __builtin_fmaf(e, 4.5f * e, -uu);
+    X[qp] = __builtin_fmaf(3.0f, e, T);
+    X[qm] = __builtin_fmaf(-3.0f, e, T);
+  };
+  pair(x, 1, 3);
+  pair(y, 2, 4);
+  pair(kFuseY ? __builtin_fmaf(ir, fy, x) : __builtin_fmaf(ir, fx, y), 5, 7);
+  pair(kFuseY ? __builtin_fmaf(ir, fy, -x) : __builtin_fmaf(-ir, fx, y), 6, 8);
+}
+
+template <typename Store, bool kForce, bool kWalls, bool kSaveS, int kH>
+__global__ __launch_bounds__((tile_waves<Store, kH>() * kLanes)) void tile_step_kernel(StepParams p) {
   using Real = typename Cvt<Store>::R;
-  __shared__ Real tP[kTileIn * kQ * kLanes];           // [row][q][lane]
-  __shared__ Real tR[kTileMid * (kQ - 1) * kLanes];    // [row][q-1][lane]
+  constexpr int kWaves = tile_waves<Store, kH>();
+  constexpr int kIn = kWaves * kH;   // rows of P
+  constexpr int kMid = kIn - 4;      // rows of R
+  constexpr int kOut = tile_rows<Store, kH>();
+  __shared__ Real tP[kIn * kYMoving * kLanes];   // [row][slot][lane]
+  __shared__ Real tR[kMid * kYMoving * kLanes];  // [row][slot][lane]
   // The walls' brackets and velocities, fetched while phase 1 waits for the
   // state: indexed by side where they are used, each would be a round trip to
   // the argument segment on the kernel's critical path (65^2 cavity 9.55 ->
@@ -545,10 +586,10 @@ __global__ __launch_bounds__(kTileWaves * kLanes) void tile_step_kernel(StepPara
   Store* __restrict__ dst = static_cast<Store*>(p.dst);
   const long long plane = p.plane;
   const int pitch = static_cast<int>(p.pitch);
-  const int ntiles = (ny + kTileRows - 1) / kTileRows;
+  const int ntiles = (ny + kOut - 1) / kOut;
   const int strip = blockIdx.x / ntiles;
-  const int y0 = (blockIdx.x % ntiles) * kTileRows;
-  const int y1 = min(y0 + kTileRows, ny);
+  const int y0 = (blockIdx.x % ntiles) * kOut;
+  const int y1 = min(y0 + kOut, ny);
   if (strip >= p.nstrips) return;  // whole block, before any barrier
 
   Real xbv = Real(0);
@@ -557,8 +598,6 @@ __global__ __launch_bounds__(kTileWaves * kLanes) void tile_step_kernel(StepPara
     xbv = wall_brackets<Real>(p, 0)[threadIdx.x];
     uwv = p.uw[(threadIdx.x >> 1) & 3][threadIdx.x & 1];
   }
-  for (int i = threadIdx.x; i < kTileMid * (kQ - 1) * kLanes; i += kTileWaves * kLanes)
-    tR[i] = Real(0);
 
   const int x0 = strip * kStripOut;
   const int x1 = min(x0 + kStripOut, nx);
@@ -571,53 +610,72 @@ __global__ __launch_bounds__(kTileWaves * kLanes) void tile_step_kernel(StepPara
     for (int k = 0; k < kWeightsPerNode; ++k) wxr[k] = wx[cm * kWeightsPerNode + k];
   }
   const bool col_interior = p.per_x || (c >= 1 && c <= nx - 2);
-  const bool lane_r = lane >= 2 && lane < kLanes - 2;
   const bool lane_o = lane >= kHalo && lane < kLanes - kHalo && c < x1;
-  const bool src_xl = !p.per_x && c == 1;
-  const bool src_xr = !p.per_x && c == nx - 2;
+  // Strips with a wall column or columns past it (uniform per block).
+  const bool side = kWalls && !p.per_x && (strip == 0 || x0 + kLanes - kHalo >= nx);
   const auto& k = coef<Real>(p);
 
-  // ---- phase 1: P of the wave's row, Q if it is an output row.
-  Real qout[kQ];
+  auto y_of = [&](int h) { return y0 - kHalo + w + kWaves * h; };
+  auto interior_row = [&](int h) { return p.per_y || (y_of(h) >= 1 && y_of(h) <= ny - 2); };
+  auto out_row = [&](int h) {  // uniform per wave, as all row tests
+    const int j = w + kWaves * h;
+    return j >= kHalo && j < kIn - kHalo && y_of(h) < y1;
+  };
+
+  // ---- phase 1: P of the wave's rows, Q of those that are output rows.
+  Real pr[kH][kQ], qout[kH][kQ];
   {
-    Store gr[kQ];
-    const int pr = y0 - kHalo + w;
-    const int prm = p.per_y ? wrap_near(pr, ny) : clampi(pr, 0, ny - 1);
-    const unsigned boff =
-        (static_cast<unsigned>(prm) * static_cast<unsigned>(pitch) + static_cast<unsigned>(cm)) *
-        static_cast<unsigned>(sizeof(Store));
-    load_planes(src, plane * sizeof(Store), boff, gr);
-    Real g[kQ];
+    Store gr[kH][kQ];
 #pragma unroll
-    for (int q = 0; q < kQ; ++q) g[q] = Cvt<Store>::ld(gr[q]);
-    double s, jx, jy;
-    moment_sums(g, s, jx, jy);
-    Real rho, ux, uy;
-    velocity(s, jx, jy, rho, ux, uy);
-    if (kForce) {
-      ux = add_scaled(p.half_dt, p.Fx, ux);
-      uy = add_scaled(p.half_dt, p.Fy, uy);
+    for (int h = 0; h < kH; ++h) {
+      const int prm = p.per_y ? wrap_near(y_of(h), ny) : clampi(y_of(h), 0, ny - 1);
+      const unsigned boff =
+          (static_cast<unsigned>(prm) * static_cast<unsigned>(pitch) + static_cast<unsigned>(cm)) *
+          static_cast<unsigned>(sizeof(Store));
+      load_planes(src, plane * sizeof(Store), boff, gr[h]);
     }
-    const Real d = static_cast<Real>(s);
-    Real X[kQ];
-    eq_brackets(ux, uy, X);
-    Real* row = tP + w * kQ * kLanes;
-    Real E[kQ], Fq[kQ];
 #pragma unroll
-    for (int q = 0; q < kQ; ++q) {
-      E[q] = fma_of(rho, X[q], d);
-      Real Pq = fma_of(k.cPg, g[q], k.kP[wclass(q)] * E[q]);
-      if (kForce) {
-        Fq[q] = force_term(q, p, ux, uy, E[q]);
-        Pq = fma_of(static_cast<Real>(p.cPF), Fq[q], Pq);
+    for (int h = 0; h < kH; ++h) {
+      const int j = w + kWaves * h;
+      Real g[kQ];
+#pragma unroll
+      for (int q = 0; q < kQ; ++q) g[q] = Cvt<Store>::ld(gr[h][q]);
+      double s, jx, jy;
+      moment_sums(g, s, jx, jy);
+      Real rho, ux = Real(0), uy = Real(0), X[kQ];
+      if constexpr (sizeof(Real) == 4 && !kForce) {
+        moments_f32<true>(s, jx, jy, rho, X);
+      } else {
+        velocity(s, jx, jy, rho, ux, uy);
+        if (kForce) {
+          ux = add_scaled(p.half_dt, p.Fx, ux);
+          uy = add_scaled(p.half_dt, p.Fy, uy);
+        }
+        eq_brackets(ux, uy, X);
       }
-      row[q * kLanes + lane] = Pq;
-    }
-    if (w >= kHalo && w < kHalo + kTileRows) {  // uniform per wave
+      const Real d = static_cast<Real>(s);
+      Real E[kQ], Fq[kQ];
 #pragma unroll
       for (int q = 0; q < kQ; ++q) {
-        qout[q] = fma_of(k.cQg, g[q], k.kQ[wclass(q)] * E[q]);
-        if (kForce) qout[q] = fma_of(static_cast<Real>(p.cQF), Fq[q], qout[q]);
+        E[q] = fma_of(rho, X[q], d);
+        Real Pq = fma_of(k.cPg, g[q], k.kP[wclass(q)] * E[q]);
+        if (kForce) {
+          Fq[q] = force_term(q, p, ux, uy, E[q]);
+          Pq = fma_of(static_cast<Real>(p.cPF), Fq[q], Pq);
+        }
+        // Formed here: moved to the later phases, the FP32 products would be
+        // fused another way than in step_kernel.
+        if constexpr (sizeof(Real) == 4) asm volatile("" : "+v"(Pq));
+        pr[h][q] = Pq;
+        if (ey_of(q) != 0) tP[(j * kYMoving + y_slot(q)) * kLanes + lane] = Pq;
+      }
+      if (j >= kHalo && j < kIn - kHalo) {
+#pragma unroll
+        for (int q = 0; q < kQ; ++q) {
+          qout[h][q] = fma_of(k.cQg, g[q], k.kQ[wclass(q)] * E[q]);
+          if (kForce) qout[h][q] = fma_of(static_cast<Real>(p.cQF), Fq[q], qout[h][q]);
+          if constexpr (sizeof(Real) == 4) asm volatile("" : "+v"(qout[h][q]));
+        }
       }
     }
   }
@@ -627,21 +685,34 @@ __global__ __launch_bounds__(kTileWaves * kLanes) void tile_step_kernel(StepPara
   }
   __syncthreads();
 
-  // ---- phase 2: S and R of rows y0 - 2 .. y0 + kTileRows + 1.
-  const int m = w - 2;
-  const int r = y0 - 2 + m;
-  if (m >= 0 && m < kTileMid && (p.per_y || (r >= 1 && r <= ny - 2))) {
+  // ---- phase 2: S and R of all but the outer two rows.
+  Real R[kH][kQ];
+#pragma unroll
+  for (int h = 0; h < kH; ++h) {
+    const int j = w + kWaves * h;
+    if (j < 2 || j >= kIn - 2) continue;
+    Real* slot = tR + (j - 2) * kYMoving * kLanes + lane;
+    const int r = y_of(h);
+    if (!interior_row(h)) {
+      // Wall rows are written from the interior rows next to them; rows past
+      // them are zero.
+      if (r < 0 || r >= ny) {
+#pragma unroll
+        for (int q = 0; q < kYMoving; ++q) slot[q * kLanes] = Real(0);
+      }
+      continue;
+    }
     const int rm = p.per_y ? wrap_near(r, ny) : r;
     Real wyr[kWeightsPerNode];
     row_weights(weights_y<Real>(p), rm, wyr);
     const Real* rb[5];
 #pragma unroll
-    for (int o = 0; o < 5; ++o) rb[o] = tP + (m + o) * kQ * kLanes + lane;
-    Real S[kQ], R[kQ];
+    for (int o = 0; o < 5; ++o) rb[o] = tP + (j - 2 + o) * kYMoving * kLanes + lane;
+    Real S[kQ];
 #pragma unroll
     for (int q = 0; q < kQ; ++q) {
-      const int pq = q * kLanes;
-      const Real centre = rb[2][pq];
+      const int pq = y_slot(q) * kLanes;
+      const Real centre = ey_of(q) != 0 ? rb[2][pq] : pr[h][q];
       Real acc = Real(0);
       if (ex_of(q) > 0) acc = x_taps<0>(wxr, centre, acc);
       if (ex_of(q) < 0) acc = x_taps<1>(wxr, centre, acc);
@@ -652,7 +723,7 @@ __global__ __launch_bounds__(kTileWaves * kLanes) void tile_step_kernel(StepPara
       }
       S[q] = q == 0 ? centre : fma_of(k.A, acc, centre);
     }
-    if (kSaveS && lane_o && col_interior && r >= y0 && r < y1) {
+    if (kSaveS && lane_o && col_interior && out_row(h)) {
       Real* sv = static_cast<Real*>(p.save_s);
       const unsigned boff =
           (static_cast<unsigned>(r) * static_cast<unsigned>(pitch) + static_cast<unsigned>(c)) *
@@ -662,88 +733,93 @@ __global__ __launch_bounds__(kTileWaves * kLanes) void tile_step_kernel(StepPara
     }
     double s, jx, jy;
     moment_sums(S, s, jx, jy);
-    Real rho, ux, uy;
-    velocity(s, jx, jy, rho, ux, uy);
-    if (kForce) {
-      ux = add_scaled(p.half_h, p.Fx, ux);
-      uy = add_scaled(p.half_h, p.Fy, uy);
+    Real rho, ux = Real(0), uy = Real(0), X[kQ];
+    if constexpr (sizeof(Real) == 4 && !kForce) {
+      moments_f32<kWalls>(s, jx, jy, rho, X);
+    } else {
+      velocity(s, jx, jy, rho, ux, uy);
+      if (kForce) {
+        ux = add_scaled(p.half_h, p.Fx, ux);
+        uy = add_scaled(p.half_h, p.Fy, uy);
+      }
+      eq_brackets(ux, uy, X);
     }
     const Real d = static_cast<Real>(s);
-    Real X[kQ];
-    eq_brackets(ux, uy, X);
-    R[0] = Real(0);
 #pragma unroll
     for (int q = 1; q < kQ; ++q) {
       const Real E = fma_of(rho, X[q], d);
       Real Rq = fma_of(k.cRs, S[q], k.kR[wclass(q)] * E);
       if (kForce) Rq = fma_of(static_cast<Real>(p.cRF), force_term(q, p, ux, uy, E), Rq);
-      R[q] = Rq;
+      R[h][q] = Rq;
     }
-    if (lane_r && col_interior) {
-      Real* slot = tR + m * (kQ - 1) * kLanes;
-#pragma unroll
-      for (int q = 1; q < kQ; ++q) slot[(q - 1) * kLanes + lane] = R[q];
+    if (kWalls) {
       // Wall nodes whose nearest interior node is this one (eq 3.10 on
-      // f(t*); corners take the diagonal neighbour); a wall row past the
-      // tile's last R row is read by none of its outputs.
-      const bool src_yb = !p.per_y && r == 1;
-      const bool src_yt = !p.per_y && r == ny - 2;
-      if (kWalls && (src_xl || src_xr || src_yb || src_yt)) {
-        for (int dy = -1; dy <= 1; ++dy) {
-          if ((dy == -1 && !src_yb) || (dy == 1 && !src_yt)) continue;
-          if (m + dy < 0 || m + dy >= kTileMid) continue;
-          for (int dx = -1; dx <= 1; ++dx) {
-            if ((dx == -1 && !src_xl) || (dx == 1 && !src_xr)) continue;
-            if (dx == 0 && dy == 0) continue;
-            const Real* Xb = tX + wall_side_of(dx, dy) * kQ;
-            const Real r1 = Real(w_of(1)) * rho, r2 = Real(w_of(5)) * rho;
-            Real* slotW = tR + (m + dy) * (kQ - 1) * kLanes;
+      // f(t*)).  A wall row's y-moving populations go to its row of tR (no
+      // output reads the others, nor the corners); a wall column's values
+      // are taken over by its own lane, and lanes past a wall column hold
+      // zero.
+      const Real r1 = Real(w_of(1)) * rho, r2 = Real(w_of(5)) * rho;
+      const bool bottom = !p.per_y && r == 1, top = !p.per_y && r == ny - 2;
+      const int jw = bottom ? j - 3 : j - 1;  // the wall row's row of tR
+      if ((bottom || top) && jw >= 0 && jw < kMid) {
+        const Real* Xb = tX + (bottom ? 2 : 3) * kQ;
+        Real* wall = tR + jw * kYMoving * kLanes + lane;
 #pragma unroll
-            for (int q = 1; q < kQ; ++q)
-              slotW[(q - 1) * kLanes + lane + dx] = nee_r(wclass(q) == 1 ? r1 : r2, X[q], Xb[q], R[q]);
-          }
+        for (int q = 1; q < kQ; ++q)
+          if (ey_of(q) != 0)
+            wall[y_slot(q) * kLanes] = nee_r(wclass(q) == 1 ? r1 : r2, X[q], Xb[q], R[h][q]);
+      }
+      if (side) {
+#pragma unroll
+        for (int q = 1; q < kQ; ++q) {
+          const Real wr = wclass(q) == 1 ? r1 : r2;
+          const Real lo = from_above(nee_r(wr, X[q], tX[q], R[h][q]));
+          const Real hi = from_below(nee_r(wr, X[q], tX[kQ + q], R[h][q]));
+          R[h][q] = col_interior ? R[h][q] : (c == 0 ? lo : (c == nx - 1 ? hi : Real(0)));
         }
       }
     }
+#pragma unroll
+    for (int q = 1; q < kQ; ++q)
+      if (ey_of(q) != 0) slot[y_slot(q) * kLanes] = R[h][q];
   }
   __syncthreads();
 
-  // ---- phase 3: the new state of the wave's output row o (R rows o-2..o+2
-  // are rows w-4 .. w of tR).
-  {
-    const int o = y0 - kHalo + w;
-    if (o >= y0 && o < y1 && (p.per_y || (o >= 1 && o <= ny - 2))) {
-      Real wyr[kWeightsPerNode];
-      row_weights(weights_y<Real>(p), o, wyr);
-      const Real* rb[5];
+  // ---- phase 3: the new state of the output rows.
 #pragma unroll
-      for (int k2 = 0; k2 < 5; ++k2) rb[k2] = tR + (w - kHalo + k2) * (kQ - 1) * kLanes + lane;
-      Real out[kQ];
-      out[0] = qout[0];
+  for (int h = 0; h < kH; ++h) {
+    if (!out_row(h) || !interior_row(h)) continue;
+    const int j = w + kWaves * h, o = y_of(h);
+    Real wyr[kWeightsPerNode];
+    row_weights(weights_y<Real>(p), o, wyr);
+    const Real* rb[5];
 #pragma unroll
-      for (int q = 1; q < kQ; ++q) {
-        const int pq = (q - 1) * kLanes;
-        const Real centre = rb[2][pq];
-        Real acc = qout[q];
-        const int sy = ey_of(q) > 0 ? 0 : 1;
-        Real rows[kTaps] = {};
-        if (ey_of(q) != 0) {
+    for (int k2 = 0; k2 < 5; ++k2) rb[k2] = tR + (j - kHalo + k2) * kYMoving * kLanes + lane;
+    Real out[kQ];
+    out[0] = qout[h][0];
 #pragma unroll
-          for (int k2 = 0; k2 < kTaps; ++k2) rows[k2] = rb[k2 + sy][pq];
-        }
-        out[q] = full_taps(q, wxr, wyr, centre, acc, rows);
+    for (int q = 1; q < kQ; ++q) {
+      const int pq = y_slot(q) * kLanes;
+      const Real centre = ey_of(q) != 0 ? rb[2][pq] : R[h][q];
+      Real acc = qout[h][q];
+      const int sy = ey_of(q) > 0 ? 0 : 1;
+      Real rows[kTaps] = {};
+      if (ey_of(q) != 0) {
+#pragma unroll
+        for (int k2 = 0; k2 < kTaps; ++k2) rows[k2] = rb[k2 + sy][pq];
       }
-      if (lane_o && col_interior) {
-        const unsigned boff =
-            (static_cast<unsigned>(o) * static_cast<unsigned>(pitch) + static_cast<unsigned>(c)) *
-            static_cast<unsigned>(sizeof(Store));
-        store_node(dst, plane, boff, out);
-      }
+      out[q] = full_taps(q, wxr, wyr, centre, acc, rows);
+    }
+    if (lane_o && col_interior) {
+      const unsigned boff =
+          (static_cast<unsigned>(o) * static_cast<unsigned>(pitch) + static_cast<unsigned>(c)) *
+          static_cast<unsigned>(sizeof(Store));
+      store_node(dst, plane, boff, out);
     }
   }
   if (kWalls) {
     __syncthreads();  // the tile's stores are visible to the block
-    piece_walls(p, dst, x0, x1, y0, y1, threadIdx.x, kTileWaves * kLanes, tU);
+    piece_walls(p, dst, x0, x1, y0, y1, threadIdx.x, kWaves * kLanes, tU);
   }
 }
 
@@ -1193,20 +1269,32 @@ void launch_single(const StepParams& p, dim3 g, dim3 b, hipStream_t s, bool wall
   }
 }
 
-template <typename Store>
-void launch_tile(const StepParams& p, hipStream_t s, bool walls) {
-  const dim3 g(p.nstrips * ((p.ny + kTileRows - 1) / kTileRows)), b(kTileWaves * kLanes);
-  if (p.has_force) {
-    if (walls)
-      hipLaunchKernelGGL((tile_step_kernel<Store, true, true>), g, b, 0, s, p);
-    else
-      hipLaunchKernelGGL((tile_step_kernel<Store, true, false>), g, b, 0, s, p);
-  } else {
-    if (walls)
-      hipLaunchKernelGGL((tile_step_kernel<Store, false, true>), g, b, 0, s, p);
-    else
-      hipLaunchKernelGGL((tile_step_kernel<Store, false, false>), g, b, 0, s, p);
+template <typename Store, bool kSaveS, int kH>
+void launch_tile_h(const StepParams& p, hipStream_t s) {
+  constexpr int kRows = tile_rows<Store, kH>();
+  const dim3 g(p.nstrips * ((p.ny + kRows - 1) / kRows)), b(tile_waves<Store, kH>() * kLanes);
+  const bool walls = !p.per_x || !p.per_y;
+  if constexpr (!kSaveS) {
+    if (p.has_force) {
+      if (walls)
+        hipLaunchKernelGGL((tile_step_kernel<Store, true, true, false, kH>), g, b, 0, s, p);
+      else
+        hipLaunchKernelGGL((tile_step_kernel<Store, true, false, false, kH>), g, b, 0, s, p);
+      return;
+    }
   }
+  if (walls)
+    hipLaunchKernelGGL((tile_step_kernel<Store, false, true, kSaveS, kH>), g, b, 0, s, p);
+  else
+    hipLaunchKernelGGL((tile_step_kernel<Store, false, false, kSaveS, kH>), g, b, 0, s, p);
+}
+
+template <typename Store, bool kSaveS>
+void launch_tile(const StepParams& p, hipStream_t s) {
+  if (p.tile == 2)
+    launch_tile_h<Store, kSaveS, 2>(p, s);
+  else
+    launch_tile_h<Store, kSaveS, 1>(p, s);
 }
 
 template <typename Store>
@@ -1214,7 +1302,7 @@ hipError_t launch_step_t(const StepParams& p, int grid, hipStream_t s) {
   const dim3 g(grid), b(step_threads(kStorageOf<Store>, p.single ? 0 : p.scheme));
   const bool walls = !p.per_x || !p.per_y;
   if (p.tile)
-    launch_tile<Store>(p, s, walls);
+    launch_tile<Store, false>(p, s);
   else if (p.single)
     launch_single<Store>(p, g, b, s, walls);
   else if (p.scheme == 1)
@@ -1318,6 +1406,11 @@ int step_blocks_per_cu(int storage, bool force, bool walls, int scheme) {
   }
 }
 
+int step_tile_rows(int storage, int tile) {
+  if (tile == 1) return tile_rows<float, 1>();
+  return storage == kF64 ? tile_rows<double, 2>() : tile_rows<float, 2>();
+}
+
 hipError_t launch_step(int storage, const StepParams& p, int grid, hipStream_t s) {
   T2S2_DISPATCH(storage, return launch_step_t<Store>(p, grid, s));
   return hipSuccess;
@@ -1330,11 +1423,7 @@ template <typename Store>
 hipError_t launch_step_save_s_t(const StepParams& p, int grid, hipStream_t s) {
   const dim3 g(grid), b(step_threads(kStorageOf<Store>, 1));
   if (p.tile) {
-    const dim3 gt(p.nstrips * ((p.ny + kTileRows - 1) / kTileRows)), bt(kTileWaves * kLanes);
-    if (!p.per_x || !p.per_y)
-      hipLaunchKernelGGL((tile_step_kernel<Store, false, true, true>), gt, bt, 0, s, p);
-    else
-      hipLaunchKernelGGL((tile_step_kernel<Store, false, false, true>), gt, bt, 0, s, p);
+    launch_tile<Store, true>(p, s);
     return hipGetLastError();
   }
   if (!p.per_x || !p.per_y)

@@ -61,6 +61,15 @@ __device__ inline void store_node(Store* dst, long long plane, unsigned boff,
   store_planes<kNt>(dst, plane * sizeof(Store), boff, r);
 }
 
+// LDS rows that serve y taps hold the populations with xi_y != 0 only:
+// population q is their slot y_slot(q).
+constexpr int kYMoving = 6;
+__device__ constexpr int y_slot(int q) {
+  int n = 0;
+  for (int k = 0; k < q; ++k) n += ey_of(k) != 0 ? 1 : 0;
+  return n;
+}
+
 // Row index brought into [0, n) by whole periods; the rows a piece touches
 // lie within a few rows of the grid, so this loops at most a few times.
 __device__ inline int wrap_near(int i, int n) {

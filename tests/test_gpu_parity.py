@@ -1022,3 +1022,46 @@ def test_one_block_steps_are_bitwise_the_tile_kernel(kind, storage, monkeypatch)
         ctx, g, d, u, v = _gpu_run(case, phi0, n, storage=storage)
         assert ctx.current == n % 2 and ctx.steps_taken == n
         assert np.array_equal(g, g_tile)
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "bf16", "f16", "bf16sr", "f16sr"])
+@pytest.mark.parametrize("kind", ["cavity59", "cavity114", "tgv56x33", "tgv_forced", "channel",
+                                  "walled_x"])
+def test_tile_shapes_are_bitwise_the_march(kind, storage, monkeypatch):
+    """Single steps by the march and by tiles of one row per wave and of two
+    (T2S2_TILE=0, 1, 2): bitwise the same state in every storage form, with
+    walls on both axes and on one, a force, the last strip one column wide,
+    the last tile one row high and a wall column in the neighbour strip's
+    halo.  (FP64 in calls of three steps, which the two-step kernel leaves
+    alone.  On a forced periodic grid in FP32 arithmetic the march fuses its
+    products otherwise, not even alike for the rows of one iteration, so there
+    the two tile shapes are compared with each other.)"""
+    if kind == "cavity59":
+        case = W.cavity_case(58, lid=0.1, re=100.0, cfl=0.9, eta=0.1, noise=1e-4, seed=5)
+    elif kind == "cavity114":
+        case = W.cavity_case(113, lid=0.1, re=100.0, cfl=0.9, eta=0.1, noise=1e-4, seed=6)
+    elif kind == "tgv56x33":
+        case = W.tgv_case(57, 33, u0=0.05, nu=0.01, cfl=0.6, eta=0.05)
+    elif kind == "walled_x":
+        case = W.couette_case(nx=70, ny_intervals=60, c=1.5, lid=0.05, nu=0.02, cfl=0.6, eta=0.1)
+        case.x, case.y = case.y.copy(), case.x.copy()
+        case.periodic_x, case.periodic_y = False, True
+        case.period_x, case.period_y = 0.0, 1.0
+        case.u_wall = np.zeros((4, 2))
+        case.u_wall[1, 1] = 0.05
+        case.rho0 = np.ones((case.ny, case.nx))
+        case.ux0 = case.uy0 = np.zeros((case.ny, case.nx))
+    else:
+        case = _mesh_case(kind)
+    phi0 = oracle.init(case) + W.random_state((9, case.ny, case.nx), 1e-5, 8)
+    monkeypatch.delenv("T2S2_BLOCKS", raising=False)
+    states = []
+    for tile in ("0", "1", "2"):
+        monkeypatch.setenv("T2S2_TILE", tile)
+        g = phi0
+        for _ in range(3):
+            _, g, *_ = _gpu_run(case, g, 3, storage=storage)
+        states.append(g)
+    assert np.array_equal(states[1], states[2])
+    if kind != "tgv_forced" or storage == "f64":
+        assert np.array_equal(states[0], states[1])
