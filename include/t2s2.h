@@ -276,8 +276,8 @@ size_t t2s2_adjoint_scratch_bytes(const t2s2_ctx* ctx);
  * reverse march from the device's compute units and the kernels' occupancy
  * (blocks of four waves, or eight; on small meshes tiles of one or two rows
  * per wave; the environment variable T2S2_ADJ_ROWS=4 or 8, read here, forces
- * the march with that block shape, 16 or 17 the tiles while there are at most
- * 1024 of them); launches nothing. */
+ * the march with that block shape, 16 the tiles and, with walls, 17 those of
+ * two rows while there are at most 1024 of them); launches nothing. */
 int t2s2_bind_adjoint(t2s2_ctx* ctx, void* scratch);
 
 /* lambda = d(<gu, u> + <gv, v>)/dg of the velocity of eq 3.3 at every node,

@@ -19,7 +19,8 @@
 // lam_{n+1}; [5'] .. [1'] then run in one kernel that marches down strips of
 // the mesh like the forward step, holding lamS in an LDS ring, so neither
 // lamR nor lamS goes to memory.  On small meshes one kernel takes [6'] ..
-// [1'] tile by tile.  The wall-to-fluid scatter of [4] and [6] is
+// [1'] tile by tile, and on periodic grids the march forms S from the state
+// as well.  The wall-to-fluid scatter of [4] and [6] is
 // gathered at the fluid node, so no atomics are needed and the result is
 // deterministic.  d/d omega of the step (omega = dt / tau) enters only
 // through the pointwise coefficients; its inner products with the adjoints
@@ -298,16 +299,27 @@ constexpr int adj_waves_per_simd() {
   return kWalls ? (f32 && kRows == 4 ? 3 : 2) : (f32 ? 4 : 2);
 }
 
-template <typename Store, int kRows, bool kWalls>
+//
+// kFormS (periodic grids): S is formed in the march from P = P(g), which a
+// second LDS ring holds for rows p0-2 .. p0+kRows+1 while phase A runs; phase B
+// forms the P of the next iteration's rows.  The step need not be run again
+// then, nor S written and read: 216 bytes per node in FP64 where the two
+// kernels move 504.  S is as step_kernel forms it. 
+// An adjoint step, us: periodic FP64 2048^2 550 -> 326, 4096^2 2264 -> 1256,
+// 800^2 103 -> 76; FP32 2048^2 359 -> 216.
+template <typename Store, int kRows, bool kWalls, bool kFormS>
 __global__ __launch_bounds__(kLanes * kRows, (adj_waves_per_simd<Store, kRows, kWalls>())) void adj_strip(AdjParams a, const Store* g,
                                                  const typename Cvt<Store>::R* lam,
                                                  const typename Cvt<Store>::R* muf,
                                                  typename Cvt<Store>::R* lam_out, double* partial,
-                                                 int nstrips) {
+                                                 int nstrips,
+                                                 StepParams::Coef<typename Cvt<Store>::R> ks) {
+  static_assert(!(kWalls && kFormS), "S is formed in the march on periodic grids only");
   using Real = typename Cvt<Store>::R;
   constexpr int kThreads = kLanes * kRows;
   constexpr int kSlots = 2 * kRows;  // rows p0-4 .. p0+kRows-1 in use, a power of two
   __shared__ Real ring[kSlots * kQ * kLanes];  // lamS: [slot][q][lane]
+  __shared__ Real ringP[kFormS ? kSlots * kQ * kLanes : 1];  // P: [slot][q][lane]
   __shared__ double red[kThreads];
   const int lane = threadIdx.x & (kLanes - 1);
   const int t = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
@@ -404,8 +416,9 @@ __global__ __launch_bounds__(kLanes * kRows, (adj_waves_per_simd<Store, kRows, k
     // of the y-moving ones too), their other three y taps, S at (c, r) and
     // the row's y weights.
     Real a_lc[kQ], a_yt[kQ][kTaps], a_sv[kQ], a_wy[2][kTaps];
-    // Phase B of row o: the state and lam at (c, o), the y weights at o.
-    Store b_gs[kQ];
+    // Phase B of row o: the state and lam at (c, o), the y weights at o; and
+    // the state at (c, o + kRows + 4), whose P it forms.
+    Store b_gs[kQ], p_gs[kQ];
     Real b_lq[kQ], b_wy[2][kTaps];
     auto issue_a = [&](int r0) {
       const int r = wrap(r0, ny);
@@ -434,7 +447,26 @@ __global__ __launch_bounds__(kLanes * kRows, (adj_waves_per_simd<Store, kRows, k
             if (tap_offset(sq, k) != 0) a_yt[q][k] = load_at<Real>(b, tb[sq][k]);
         }
       }
-      load_planes(S, pbr, rb, a_sv);
+      if constexpr (!kFormS) load_planes(S, pbr, rb, a_sv);
+    };
+    auto issue_p = [&](int row, Store (&gs)[kQ]) {
+      const unsigned off = static_cast<unsigned>(static_cast<long long>(wrap(row, ny)) * a.pitch + c);
+      load_planes(g, pbs, off * static_cast<unsigned>(sizeof(Store)), gs);
+    };
+    auto form_p = [&](int row, const Store (&gs)[kQ]) {
+      Real v[kQ], X[kQ];
+#pragma unroll
+      for (int q = 0; q < kQ; ++q) v[q] = Cvt<Store>::ld(gs[q]);
+      double s, jx, jy;
+      moment_sums(v, s, jx, jy);
+      Real rho, ux, uy;
+      velocity(s, jx, jy, rho, ux, uy);
+      const Real d = static_cast<Real>(s);
+      eq_brackets(ux, uy, X);
+      Real* slot = ringP + (row & (kSlots - 1)) * kQ * kLanes + lane;
+#pragma unroll
+      for (int q = 0; q < kQ; ++q)
+        slot[q * kLanes] = fma_of(ks.cPg, v[q], ks.kP[wclass(q)] * fma_of(rho, X[q], d));
     };
     auto issue_b = [&](int o0) {
       const int o = wrap(o0, ny);
@@ -448,10 +480,19 @@ __global__ __launch_bounds__(kLanes * kRows, (adj_waves_per_simd<Store, kRows, k
           b_wy[sc][k] = ywt(along(o, -tap_offset(sc, k), ny, true), sc, k);
       }
     };
+    if constexpr (kFormS) {
+      Store g0[kQ], g1[kQ];
+      issue_p(y0 - 4 + t, g0);
+      issue_p(y0 - 4 + kRows + t, g1);
+      form_p(y0 - 4 + t, g0);
+      form_p(y0 - 4 + kRows + t, g1);
+    }
     if constexpr (!kWalls) issue_a(y0 - 2 + t);
+    if constexpr (kFormS) __syncthreads();
     for (int it = 0; it < niter; ++it) {
       const int p0 = y0 - 2 + kRows * it;
       if constexpr (!kWalls) issue_b(p0 - 2 + t);
+      if constexpr (kFormS) issue_p(p0 + kRows + 2 + t, p_gs);
 
       // ---- phase A: lamS of row r
       {
@@ -489,8 +530,32 @@ __global__ __launch_bounds__(kLanes * kRows, (adj_waves_per_simd<Store, kRows, k
 #pragma unroll
               for (int k = 0; k < kTaps; ++k) wys[sc][k] = a_wy[sc][k];
             }
+            if constexpr (kFormS) {
+              Real wyr[kWeightsPerNode];
+              row_weights(WY, r, wyr);
+              const Real* rb[5];
 #pragma unroll
-            for (int q = 0; q < kQ; ++q) sv[q] = a_sv[q];
+              for (int k = 0; k < 5; ++k)
+                rb[k] = ringP + ((r0 - 2 + k) & (kSlots - 1)) * kQ * kLanes + lane;
+#pragma unroll
+              for (int q = 0; q < kQ; ++q) {
+                const int pq = q * kLanes;
+                const Real centre = rb[2][pq];
+                Real acc = Real(0);
+                if (ex_of(q) > 0) acc = x_taps<0>(wx, centre, acc);
+                if (ex_of(q) < 0) acc = x_taps<1>(wx, centre, acc);
+                if (ey_of(q) != 0) {
+                  const int sy = ey_of(q) > 0 ? 0 : 1;
+#pragma unroll
+                  for (int k = 0; k < kTaps; ++k)
+                    acc = fma_of(wyr[sy * kTaps + k], rb[k + sy][pq], acc);
+                }
+                sv[q] = q == 0 ? centre : fma_of(ks.A, acc, centre);
+              }
+            } else {
+#pragma unroll
+              for (int q = 0; q < kQ; ++q) sv[q] = a_sv[q];
+            }
           } else {
             int ysrc[2][kTaps];
 #pragma unroll
@@ -602,6 +667,7 @@ __global__ __launch_bounds__(kLanes * kRows, (adj_waves_per_simd<Store, kRows, k
       __syncthreads();
 
       // ---- phase B: lam_n of row o
+      if constexpr (kFormS) form_p(p0 + kRows + 2 + t, p_gs);
       {
         const int o = p0 - 2 + t;
         if (o >= y0 && o < y1) {  // uniform per wave
@@ -1137,6 +1203,14 @@ __global__ __launch_bounds__(256) void adj_convert(AdjParams a, const Real* lam,
   }
 }
 
+template <typename Real>
+const StepParams::Coef<Real>& coef_of(const StepParams& p) {
+  if constexpr (sizeof(Real) == 8)
+    return p.c64;
+  else
+    return p.c32;
+}
+
 int adj_grid(const AdjParams& a) {
   long long g = (static_cast<long long>(a.nx) * a.ny + 255) / 256;
   return static_cast<int>(g < 1 ? 1 : (g > kDiagBlocks ? kDiagBlocks : g));
@@ -1144,10 +1218,11 @@ int adj_grid(const AdjParams& a) {
 
 // The reverse stages of the step from state_n, given its S (a.S) and the
 // new state (a.next, whose moments the walls' adjoint needs at the fluid
-// nodes).
+// nodes); where form_s is given, the march forms S by the step's coefficients.
 template <typename Store>
 hipError_t adjoint_reverse_t(const AdjParams& a, const void* state_n, const void* lam_np1,
-                             void* lam_n, double* partial, double* accum, hipStream_t s) {
+                             void* lam_n, double* partial, double* accum, hipStream_t s,
+                             const StepParams* form_s = nullptr) {
   using Real = typename Cvt<Store>::R;
   const bool walls = !a.per_x || !a.per_y;
   const Real* mu = static_cast<const Real*>(lam_np1);
@@ -1164,7 +1239,7 @@ hipError_t adjoint_reverse_t(const AdjParams& a, const void* state_n, const void
     if (a.march_rows == kAdjTiles)
       walls ? go(adj_tile<Store, true, kW1, 1>, kW1) : go(adj_tile<Store, false, kW1, 1>, kW1);
     else
-      walls ? go(adj_tile<Store, true, kW2, 2>, kW2) : go(adj_tile<Store, false, kW2, 2>, kW2);
+      go(adj_tile<Store, true, kW2, 2>, kW2);
     if (accum)
       hipLaunchKernelGGL(adj_accumulate, dim3(1), dim3(64), 0, s, partial, blocks,
                          a.dnu_per_domega, accum);
@@ -1179,22 +1254,22 @@ hipError_t adjoint_reverse_t(const AdjParams& a, const void* state_n, const void
                        static_cast<const Store*>(a.next), mu);
     muf = static_cast<const Real*>(a.mu);
   }
+  StepParams::Coef<Real> ks = {};
+  auto go = [&](auto kernel, int waves) {
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(waves * kLanes), 0, s, a, g, mu, muf, lo, partial,
+                       nstrips, ks);
+  };
   const bool rows8 = a.march_rows == 8;
-  const int Gs = blocks;
-  if (rows8 && walls)
-    hipLaunchKernelGGL((adj_strip<Store, 8, true>), dim3(Gs), dim3(kLanes * 8), 0, s, a, g, mu,
-                       muf, lo, partial, nstrips);
-  else if (rows8)
-    hipLaunchKernelGGL((adj_strip<Store, 8, false>), dim3(Gs), dim3(kLanes * 8), 0, s, a, g, mu,
-                       muf, lo, partial, nstrips);
-  else if (walls)
-    hipLaunchKernelGGL((adj_strip<Store, 4, true>), dim3(Gs), dim3(kLanes * 4), 0, s, a, g, mu,
-                       muf, lo, partial, nstrips);
-  else
-    hipLaunchKernelGGL((adj_strip<Store, 4, false>), dim3(Gs), dim3(kLanes * 4), 0, s, a, g, mu,
-                       muf, lo, partial, nstrips);
+  if (form_s) {
+    ks = coef_of<Real>(*form_s);
+    rows8 ? go(adj_strip<Store, 8, false, true>, 8) : go(adj_strip<Store, 4, false, true>, 4);
+  } else if (rows8) {
+    walls ? go(adj_strip<Store, 8, true, false>, 8) : go(adj_strip<Store, 8, false, false>, 8);
+  } else {
+    walls ? go(adj_strip<Store, 4, true, false>, 4) : go(adj_strip<Store, 4, false, false>, 4);
+  }
   if (accum)
-    hipLaunchKernelGGL(adj_accumulate, dim3(1), dim3(64), 0, s, partial, Gs,
+    hipLaunchKernelGGL(adj_accumulate, dim3(1), dim3(64), 0, s, partial, blocks,
                        a.dnu_per_domega, accum);
   return hipGetLastError();
 }
@@ -1205,6 +1280,10 @@ template <typename Store>
 hipError_t adjoint_step_t(int storage, const AdjParams& a, const StepParams& sp, int step_grid,
                           const void* state_n, const void* lam_np1, void* lam_n,
                           double* partial, double* accum, hipStream_t s) {
+  // On a periodic grid that the march takes, it forms S itself and the new
+  // state is not needed.
+  if (a.march_rows < kAdjTiles && a.per_x && a.per_y)
+    return adjoint_reverse_t<Store>(a, state_n, lam_np1, lam_n, partial, accum, s, &sp);
   StepParams fwd = sp;
   fwd.src = state_n;
   fwd.dst = a.next;
@@ -1216,7 +1295,7 @@ hipError_t adjoint_step_t(int storage, const AdjParams& a, const StepParams& sp,
 
 template <typename Store, int kRows, bool kWalls>
 hipError_t march_blocks_per_cu(int& n) {
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, adj_strip<Store, kRows, kWalls>,
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, adj_strip<Store, kRows, kWalls, !kWalls>,
                                                       kLanes * kRows, 0);
 }
 
@@ -1228,10 +1307,14 @@ hipError_t march_blocks_per_cu(int& n) {
 // halos above and below its range.  Still smaller ones take tiles: those of
 // one row per wave while each CU gets at most one (FP32 340^2, past that:
 // 24.2 us against 21.7 with two rows per wave; 300^2, before it: 14.8 against
-// 20.9), else those of two rows per wave up to three blocks per CU in FP32
-// and four in FP64 (cavity: FP64 945^2 87 us against the march's 101; FP32
-// 769^2 44 against 56, but 1100^2, at 3.6 blocks per CU, 80 against 77).  The
-// plan is fixed per context, so the order of the d/d omega reduction is too.
+// 20.9); beyond, with walls, those of two rows per wave up to three blocks per
+// CU in FP32 and four in FP64 (cavity: FP64 945^2 87 us against the march's
+// 101; FP32 769^2 44 against 56, but 1100^2, at 3.6 blocks per CU, 80 against
+// 77), and on periodic grids the march, which forms S itself where the step is
+// not stored (an adjoint step at 600^2, FP64 54 us against 60 for the step
+// again and tiles, FP32 40 against 49; at 320^2 34 against 23).  The plan is
+// fixed per context, so the order of the d/d omega reduction is too, and a
+// stored step and one that is not give the same bits.
 template <typename Store>
 hipError_t plan_march_t(AdjParams& a, int cus) {
   const bool walls = !a.per_x || !a.per_y;
@@ -1251,7 +1334,7 @@ hipError_t plan_march_t(AdjParams& a, int cus) {
   const long long t1 = tiles(tile_out_rows<Store, false>()), t2 = tiles(tile_out_rows<Store, true>());
   a.march_rows = nstrips * a.ny < kAdjRows8Below * g4 ? 8 : 4;
   const int rounds = sizeof(typename Cvt<Store>::R) == 8 ? 4 : 3;
-  if (t2 <= static_cast<long long>(rounds) * cus && t2 <= kAdjMaxBlocks)
+  if (walls && t2 <= static_cast<long long>(rounds) * cus && t2 <= kAdjMaxBlocks)
     a.march_rows = kAdjTiles + 1;
   if (t1 <= cus) a.march_rows = kAdjTiles;
   // T2S2_ADJ_ROWS=4 or 8 forces the march and its block shape, 16 or 17 the
@@ -1259,7 +1342,7 @@ hipError_t plan_march_t(AdjParams& a, int cus) {
   if (const char* env = std::getenv("T2S2_ADJ_ROWS")) {
     const int rows = std::atoi(env);
     if (rows == 4 || rows == 8 || (rows == kAdjTiles && t1 <= kAdjMaxBlocks) ||
-        (rows == kAdjTiles + 1 && t2 <= kAdjMaxBlocks))
+        (rows == kAdjTiles + 1 && walls && t2 <= kAdjMaxBlocks))
       a.march_rows = rows;
   }
   a.march_grid = a.march_rows == kAdjTiles       ? static_cast<int>(t1)

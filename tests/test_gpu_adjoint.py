@@ -335,6 +335,42 @@ def test_stored_adjoint_step_is_the_recomputing_one(kind, storage):
     ctx.close()
 
 
+@pytest.mark.parametrize("storage", ["f64", "f32", "bf16", "f16"])
+@pytest.mark.parametrize("rows,nx,ny,A", [("4", 57, 30, 0.5), ("8", 57, 30, 0.5),
+                                          ("4", 5, 6, 0.5), ("8", 113, 9, 0.5),
+                                          ("4", 57, 30, 0.0), (None, 450, 300, 0.5)])
+def test_periodic_march_forms_the_stored_s(rows, nx, ny, A, storage, monkeypatch):
+    """On periodic grids beyond the tiles' range (forced with T2S2_ADJ_ROWS on
+    small ones) the march of a step that is not stored forms S itself:
+    bitwise the lambda_n and dL/dnu of the march that reads the S of
+    t2s2_step_save_s."""
+    case = W.tgv_case(nx, ny, u0=0.05, nu=0.01, cfl=0.6 if A else 0.25, eta=0.05)
+    case.A = A
+    if rows:
+        monkeypatch.setenv("T2S2_ADJ_ROWS", rows)
+    print(f"[gpu] march forms S {nx}x{ny} {storage} rows {rows} A {A}", flush=True)
+    ctx = t2s2.context_for_case(case, storage=storage)
+    ctx.enable_adjoint()
+    ctx.init_macro(case.rho0, case.ux0, case.uy0)
+    ctx.step(3)
+    state = ctx.save_state()
+    nxt, s_n = torch.empty_like(state), ctx.adjoint_buffer()
+    ctx.step_save_s(state, nxt, s_n)
+    lam = ctx.adjoint_load(W.random_state((9, ny, nx), 1.0, 23))
+    outs = []
+    for stored in (False, True):
+        out = ctx.adjoint_buffer()
+        acc = torch.zeros(1, dtype=torch.float64, device="cuda:0")
+        if stored:
+            ctx.adjoint_step_stored(state, nxt, s_n, lam, out, acc)
+        else:
+            ctx.adjoint_step(state, lam, out, acc)
+        outs.append((ctx.adjoint_read(out).cpu().numpy(), float(acc.item())))
+    ctx.close()
+    assert np.array_equal(outs[0][0], outs[1][0])
+    assert outs[0][1] == outs[1][1]
+
+
 @pytest.mark.parametrize("storage", ["f64", "f32"])
 def test_rollout_backward_with_stored_steps(storage):
     """The rollout's two backward passes (steps and S kept per segment, or
