@@ -819,7 +819,7 @@ __global__ __launch_bounds__((tile_waves<Store, kH>() * kLanes)) void tile_step_
   }
   if (kWalls) {
     __syncthreads();  // the tile's stores are visible to the block
-    piece_walls(p, dst, x0, x1, y0, y1, threadIdx.x, kWaves * kLanes, tU);
+    piece_walls<Store, false>(p, dst, x0, x1, y0, y1, threadIdx.x, kWaves * kLanes, tU);
   }
 }
 

@@ -170,8 +170,12 @@ __device__ inline Real force_term(int q, const StepParams& p, Real ux, Real uy, 
 // the loads see them (the coherence point is L2; the buffer was not read
 // earlier in the launch).  Each wall node has exactly one source node, and
 // each source node is output by exactly one piece.  uw: the walls'
-// velocities (p.uw or a copy of it).
-template <typename Store>
+// velocities (p.uw or a copy of it).  kLoadsFirst keeps the conversions of the
+// 16-bit forms behind all nine loads: taken one by one, each load waits out a
+// round trip (16-bit T2S2-FDLBM2 cavity 236 x 245, 18.7 us per step, 17.5 so;
+// the tile kernel's 16-bit forms are not scheduled that way and are 2% slower
+// with it).
+template <typename Store, bool kLoadsFirst = sizeof(Store) == 2>
 __device__ inline void piece_walls(const StepParams& p, Store* dst, int x0, int x1, int y0,
                                    int y1, int tid, int nthreads, const double (*uw)[2]) {
   using Real = typename Cvt<Store>::R;
@@ -204,9 +208,13 @@ __device__ inline void piece_walls(const StepParams& p, Store* dst, int x0, int 
       j = ry0 + (rb ? 1 : 0) + kb % nrows_b;
     }
     const long long fb = static_cast<long long>(j) * p.pitch + i;
+    Store raw[kQ];
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) raw[q] = dst[q * p.plane + fb];
+    if constexpr (kLoadsFirst) __builtin_amdgcn_sched_barrier(0);
     Real v[kQ];
 #pragma unroll
-    for (int q = 0; q < kQ; ++q) v[q] = Cvt<Store>::ld(dst[q * p.plane + fb]);
+    for (int q = 0; q < kQ; ++q) v[q] = Cvt<Store>::ld(raw[q]);
     double s, jx, jy;
     moment_sums(v, s, jx, jy);
     const double rho = 1.0 + s;
