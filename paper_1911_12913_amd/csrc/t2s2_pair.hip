@@ -256,10 +256,11 @@ __device__ __forceinline__ void stage_row(const StepParams& p0, const double* wy
 // row of the ring is complete 4 rows after its first population was written;
 // B reads it in the next iteration (walled: one later still, since a wall row
 // is formed from the row after it) and marches it in the one after.  One
-// barrier per iteration.  While A writes ring rows p - 4 .. p, B reads row
-// p - 5 (walled: p - 6, and when A is done the row below the top wall):
-// never one slot of the eight.  kWalls: the piece may reach wall nodes, or
-// nodes next to a wall.
+// barrier per iteration.  While A writes rows p (the rest population), p - 2,
+// p - 3 and p - 4, B reads row p - 5 (walled: p - 6, at the walls the interior
+// row beside them, past the top wall the slot of row p - 9, which is that of
+// p - 1): never a slot of the eight that A writes.  kWalls: the piece may
+// reach wall nodes, or nodes next to a wall.
 template <bool kForce, bool kWalls>
 __device__ __forceinline__ void march_piece(const StepParams& p, const double* wy16, double* hand, int lane, int role,
                                             int x0, int x1, int y0, int y1) {
@@ -350,7 +351,9 @@ __device__ __forceinline__ void march_piece(const StepParams& p, const double* w
     // A row of the ring is read in the iteration before its use.
     Real g[kQ];
     auto read_row = [&](int j) {
-      const int js = per_y ? j : clampi(j, 1, ny - 2);
+      // (Rows past the top wall enter with weight zero: any finite row that A
+      // does not write meanwhile will do, and it skips the slot of row j - 3.)
+      const int js = per_y ? j : (j < ny ? clampi(j, 1, ny - 2) : j - 3);
       const Real* slot = hand + (js & (kHandRows - 1)) * kQ * kLanes + src_lane;
 #pragma unroll
       for (int q = 0; q < kQ; ++q) g[q] = slot[q * kLanes];
