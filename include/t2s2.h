@@ -291,8 +291,9 @@ int t2s2_adjoint_seed_velocity(t2s2_ctx* ctx, const void* state, const double* g
  * non-NULL, adds <lam_np1, d f~^{n+1}/d nu> to it, the derivative at a fixed
  * dt through omega = dt / tau = dt c_s^2 / nu (d omega / d nu = -omega / nu;
  * zero without collision).  Summed over the steps of a rollout it is dL/dnu.
- * lam_np1 and lam_n must differ.  Asynchronous; deterministic (fixed
- * reduction order). */
+ * lam_np1 and lam_n must differ; lam_n may be the buffer of state_n (FP64 and
+ * FP32 storage, where both have one size), whose contents are then lost.
+ * Asynchronous; deterministic (fixed reduction order). */
 int t2s2_adjoint_step(t2s2_ctx* ctx, const void* state_n, const void* lam_np1, void* lam_n,
                       double* dnu_accum);
 

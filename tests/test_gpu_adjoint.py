@@ -372,6 +372,35 @@ def test_periodic_march_forms_the_stored_s(rows, nx, ny, A, storage, monkeypatch
 
 
 @pytest.mark.parametrize("storage", ["f64", "f32"])
+@pytest.mark.parametrize("kind", ["tgv_march", "tgv_tile", "cavity_march", "cavity_tile"])
+def test_adjoint_step_over_its_state(kind, storage, monkeypatch):
+    """lam_n may be the buffer of state_n: bitwise the lambda_n and dL/dnu of
+    an adjoint step into a buffer of its own, by the march and by tiles, on a
+    periodic grid of many blocks (whose march otherwise reads state_n around
+    each block's outputs) and with walls."""
+    if kind.startswith("tgv"):
+        case = W.tgv_case(313, 230, u0=0.05, nu=0.01, cfl=0.6, eta=0.05)
+    else:
+        case = W.cavity_case(230, lid=0.1, re=400.0, cfl=0.9, eta=0.1, noise=1e-3, seed=1)
+    monkeypatch.setenv("T2S2_ADJ_ROWS", "8" if kind.endswith("march") else "16")
+    print(f"[gpu] adjoint step over its state {kind} {storage}", flush=True)
+    ctx = t2s2.context_for_case(case, storage=storage)
+    ctx.enable_adjoint()
+    ctx.init_macro(case.rho0, case.ux0, case.uy0)
+    ctx.step(3)
+    state = ctx.save_state()
+    lam = ctx.adjoint_load(W.random_state((9, case.ny, case.nx), 1.0, 23))
+    outs = []
+    for out in (ctx.adjoint_buffer(), state):
+        acc = torch.zeros(1, dtype=torch.float64, device="cuda:0")
+        ctx.adjoint_step(state, lam, out, acc)
+        outs.append((ctx.adjoint_read(out).cpu().numpy(), float(acc.item())))
+    ctx.close()
+    assert np.array_equal(outs[0][0], outs[1][0])
+    assert outs[0][1] == outs[1][1]
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32"])
 def test_rollout_backward_with_stored_steps(storage):
     """The rollout's two backward passes (steps and S kept per segment, or
     the step recomputed inside each adjoint step) give the same gradients:
