@@ -22,16 +22,29 @@ __host__ __device__ constexpr double w_of(int q) {
   return q == 0 ? 4.0 / 9.0 : (q < 5 ? 1.0 / 9.0 : 1.0 / 36.0);
 }
 
-// a b + c.  FP64: in one rounding, so that every kernel rounds a node's
-// values the same way (of a sum of two products the compiler may fuse
-// either).  FP32: left to the compiler, whose choice is the same in every
-// kernel of the reduced forms.
-__device__ inline double fma_of(double a, double b, double c) { return __builtin_fma(a, b, c); }
-__device__ inline float fma_of(float a, float b, float c) { return a * b + c; }
+// a b + c.  FP64 with kExact: in one rounding, so that the kernels that take
+// the same step (T2S2-FDLBM1: march, tile, two steps per launch, one block)
+// round a node's values the same way (of a sum of two products the compiler may
+// fuse either).  Otherwise left to the compiler, which fuses FP32 products
+// alike in most kernels of the reduced forms but not in all: see moments_f32
+// and the exceptions that t2s2_bind makes.
+template <bool kExact = true>
+__device__ inline double fma_of(double a, double b, double c) {
+  if constexpr (kExact) return __builtin_fma(a, b, c);
+  return a * b + c;
+}
+template <bool kExact = true>
+__device__ inline float fma_of(float a, float b, float c) {
+  return a * b + c;
+}
 
-// a b + c with c in the arithmetic type and a, b FP64 parameters: FP64 in
-// one rounding, FP32 with the product rounded first.
-__device__ inline double add_scaled(double a, double b, double c) { return __builtin_fma(a, b, c); }
+// a b + c with c in the arithmetic type and a, b FP64 parameters: FP64 as
+// fma_of, FP32 with the product rounded first.
+template <bool kExact = true>
+__device__ inline double add_scaled(double a, double b, double c) {
+  return fma_of<kExact>(a, b, c);
+}
+template <bool kExact = true>
 __device__ inline float add_scaled(double a, double b, float c) {
   return c + static_cast<float>(a * b);
 }
@@ -330,16 +343,25 @@ __host__ __device__ constexpr int wclass(int q) { return q == 0 ? 0 : (q < 5 ? 1
 // moment sums.  FP64 arithmetic divides in FP64.  FP32 arithmetic rounds
 // the sums to FP32 and multiplies by the hardware reciprocal of rho refined
 // by one Newton step.
-// (FP64: no contraction here and in eq_brackets; x and y enter sums, and
-// whether the compiler fuses their products into those differs between
-// kernels.)
+// (FP64 with kExact: no contraction here and in eq_brackets; x and y enter
+// sums, and whether the compiler fuses their products into those differs
+// between kernels.)
+template <bool kExact = true>
 __device__ inline void velocity(double s, double jx, double jy, double& r, double& x, double& y) {
+  if constexpr (kExact) {
 #pragma clang fp contract(off)
-  r = 1.0 + s;
-  const double ir = recip(r);
-  x = jx * ir;
-  y = jy * ir;
+    r = 1.0 + s;
+    const double ir = recip(r);
+    x = jx * ir;
+    y = jy * ir;
+  } else {
+    r = 1.0 + s;
+    const double ir = recip(r);
+    x = jx * ir;
+    y = jy * ir;
+  }
 }
+template <bool kExact = true>
 __device__ inline void velocity(double s, double jx, double jy, float& r, float& x, float& y) {
   r = 1.0f + static_cast<float>(s);
   float ir = __builtin_amdgcn_rcpf(r);
@@ -351,52 +373,64 @@ __device__ inline void velocity(double s, double jx, double jy, float& r, float&
 // Brackets X_q of the equilibrium, f^eq_q - w_q = w_q (drho + rho X_q) with
 // X_q = 3 e_q + 9/2 e_q^2 - 3/2 |u|^2 and e_q = xi_q . u (eq 3.2, c_s^2 =
 // 1/3).  Opposite directions share 9/2 e^2 - 3/2 |u|^2.
-__device__ inline void eq_brackets(double x, double y, double X[kQ]) {
+template <bool kExact = true, typename Real>
+__device__ inline void eq_brackets(Real x, Real y, Real X[kQ]) {
+  if constexpr (kExact && sizeof(Real) == 8) {
 #pragma clang fp contract(off)
-  const double uu = 1.5 * fma_of(x, x, y * y);
-  X[0] = -uu;
-  auto pair = [&](double e, int qp, int qm) {
-    const double T = fma_of(4.5 * e, e, -uu);
-    X[qp] = fma_of(3.0, e, T);
-    X[qm] = fma_of(-3.0, e, T);
-  };
-  pair(x, 1, 3);
-  pair(y, 2, 4);
-  pair(x + y, 5, 7);
-  pair(y - x, 6, 8);
-}
-__device__ inline void eq_brackets(float x, float y, float X[kQ]) {
-  const float uu = float(1.5) * (x * x + y * y);
-  X[0] = -uu;
-  auto pair = [&](float e, int qp, int qm) {
-    const float T = (float(4.5) * e) * e - uu;
-    X[qp] = T + float(3) * e;
-    X[qm] = T - float(3) * e;
-  };
-  pair(x, 1, 3);
-  pair(y, 2, 4);
-  pair(x + y, 5, 7);
-  pair(y - x, 6, 8);
+    const double uu = 1.5 * fma_of(x, x, y * y);
+    X[0] = -uu;
+    auto pair = [&](double e, int qp, int qm) {
+      const double T = fma_of(4.5 * e, e, -uu);
+      X[qp] = fma_of(3.0, e, T);
+      X[qm] = fma_of(-3.0, e, T);
+    };
+    pair(x, 1, 3);
+    pair(y, 2, 4);
+    pair(x + y, 5, 7);
+    pair(y - x, 6, 8);
+  } else {
+    const Real uu = Real(1.5) * (x * x + y * y);
+    X[0] = -uu;
+    auto pair = [&](Real e, int qp, int qm) {
+      const Real T = (Real(4.5) * e) * e - uu;
+      X[qp] = T + Real(3) * e;
+      X[qm] = T - Real(3) * e;
+    };
+    pair(x, 1, 3);
+    pair(y, 2, 4);
+    pair(x + y, 5, 7);
+    pair(y - x, 6, 8);
+  }
 }
 
 // f^eq(rho, u_b) - f^eq(rho, u_f) (the non-equilibrium extrapolation shift
 // of eq 3.10, with rho taken at the fluid node).
-template <typename Real>
+template <bool kExact = true, typename Real>
 __device__ inline void nee_shift(double rho, double uxf, double uyf, double uxb, double uyb,
-                                 Real out[kQ]) {
+                                 Real (&out)[kQ]) {
   const Real r = static_cast<Real>(rho);
   const Real xf = static_cast<Real>(uxf), yf = static_cast<Real>(uyf);
   const Real xb = static_cast<Real>(uxb), yb = static_cast<Real>(uyb);
-  const Real uuf = Real(1.5) * fma_of(xf, xf, yf * yf);
-  const Real uub = Real(1.5) * fma_of(xb, xb, yb * yb);
+  const Real uuf = Real(1.5) * fma_of<kExact>(xf, xf, yf * yf);
+  const Real uub = Real(1.5) * fma_of<kExact>(xb, xb, yb * yb);
 #pragma unroll
   for (int q = 0; q < kQ; ++q) {
     const Real ef = Real(ex_of(q)) * xf + Real(ey_of(q)) * yf;
     const Real eb = Real(ex_of(q)) * xb + Real(ey_of(q)) * yb;
-    const Real Xf = fma_of(ef, Real(3) + Real(4.5) * ef, -uuf);
-    const Real Xb = fma_of(eb, Real(3) + Real(4.5) * eb, -uub);
+    const Real Xf = fma_of<kExact>(ef, Real(3) + Real(4.5) * ef, -uuf);
+    const Real Xb = fma_of<kExact>(eb, Real(3) + Real(4.5) * eb, -uub);
     out[q] = Real(w_of(q)) * r * (Xb - Xf);
   }
+}
+
+// f^eq(rho, u_b) - f^eq(rho, u_f) of eq 3.10 for q >= 1 from the brackets
+// Xf of the fluid node's velocity (eq_brackets) and Xb of the wall's
+// (StepParams::xb): w_q rho (Xb_q - Xf_q).  out[0] is not formed.
+template <typename Real>
+__device__ inline void nee_shift_x(Real rho, const Real (&Xf)[kQ], const Real* Xb, Real out[kQ]) {
+  const Real r1 = Real(w_of(1)) * rho, r2 = Real(w_of(5)) * rho;
+#pragma unroll
+  for (int q = 1; q < kQ; ++q) out[q] = (wclass(q) == 1 ? r1 : r2) * (Xb[q] - Xf[q]);
 }
 
 // The wall node's R_q of eq 3.10: R_q + f^eq_q(rho, u_b) - f^eq_q(rho, u_f)

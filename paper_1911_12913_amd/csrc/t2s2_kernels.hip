@@ -97,6 +97,14 @@ template <typename Store, bool kForce, bool kWalls, int kScheme, bool kSaveS = f
 __global__ __launch_bounds__(step_threads(kStorageOf<Store>, kScheme), (kMinWaves<Store, kForce, kWalls, kScheme>)) void step_kernel(
     StepParams p) {
   using Real = typename Cvt<Store>::R;
+  // FP64: scheme 1 is taken by other kernels too, which round alike (see
+  // fma_of), and the family with gradient weights (0, 1, 0) equals it.  What no
+  // other kernel takes leaves its sums to the compiler: in this form it runs 1 to
+  // 3% slower (walled family 16 x 10, BF16, 22.7 us per step, 23.1 so; T1S2 in
+  // FP16 with stochastic rounding 31 x 33, 16.3 and 16.6; channel 1500 x 1400
+  // FP32 61.6, 64.2).
+  constexpr bool kExact = sizeof(Real) == 8 && (kScheme == 1 || kScheme == 3);
+  using Row = std::conditional_t<kExact, LdsPtr<Real>, const Real*>;
   // T2S2-FDLBM2, FP64, periodic: f^n of the phase-2 row from a reload.
   constexpr bool kFnRegs = kFnRegsOf<Store, kWalls, kScheme>;
   constexpr int kNP = kPPlanes<kScheme, kFnRegs>;
@@ -235,28 +243,28 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, kScheme), (kMinWave
         double s, jx, jy;
         moment_sums(g, s, jx, jy);
         Real rho, ux, uy;
-        velocity(s, jx, jy, rho, ux, uy);
+        velocity<kExact>(s, jx, jy, rho, ux, uy);
         if (kForce) {
-          ux = add_scaled(p.half_dt, p.Fx, ux);
-          uy = add_scaled(p.half_dt, p.Fy, uy);
+          ux = add_scaled<kExact>(p.half_dt, p.Fx, ux);
+          uy = add_scaled<kExact>(p.half_dt, p.Fy, uy);
         }
         const Real d = static_cast<Real>(s);
         Real X[kQ];
-        eq_brackets(ux, uy, X);
+        eq_brackets<kExact>(ux, uy, X);
         const auto& k = coef<Real>(p);
         Real* slotP = ringP + (pr & (kRing - 1)) * kNP * kLanes;
 #pragma unroll
         for (int q = 0; q < kQ; ++q) {
           // E = (f^eq_q - w_q) / w_q; P and Q take their f^eq coefficient
           // times w_q per weight class.
-          const Real E = fma_of(rho, X[q], d);
-          Real Pq = fma_of(k.cPg, g[q], k.kP[wclass(q)] * E);
-          Real Qq = fma_of(k.cQg, g[q], k.kQ[wclass(q)] * E);
+          const Real E = fma_of<kExact>(rho, X[q], d);
+          Real Pq = fma_of<kExact>(k.cPg, g[q], k.kP[wclass(q)] * E);
+          Real Qq = fma_of<kExact>(k.cQg, g[q], k.kQ[wclass(q)] * E);
           Real Fq = Real(0);
           if (kForce) {
-            Fq = force_term(q, p, ux, uy, E);
-            Pq = fma_of(static_cast<Real>(p.cPF), Fq, Pq);
-            Qq = fma_of(static_cast<Real>(p.cQF), Fq, Qq);
+            Fq = force_term<kExact>(q, p, ux, uy, E);
+            Pq = fma_of<kExact>(static_cast<Real>(p.cPF), Fq, Pq);
+            Qq = fma_of<kExact>(static_cast<Real>(p.cQF), Fq, Qq);
           }
           slotP[q * kLanes + lane] = kScheme == 2 ? Qq : Pq;
           if (kScheme == 2 && !kFnRegs && q > 0) slotP[(kQ + q - 1) * kLanes + lane] = Pq;
@@ -264,15 +272,15 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, kScheme), (kMinWave
           if (kFamily) {
             slotP[(kQ + q) * kLanes + lane] = Qq;
             if (q > 0) {
-              Real Uq = fma_of(k.cU, g[q], k.kU[wclass(q)] * E);  // f^n
-              if (kForce) Uq = fma_of(static_cast<Real>(p.cUF), Fq, Uq);
+              Real Uq = fma_of<kExact>(k.cU, g[q], k.kU[wclass(q)] * E);  // f^n
+              if (kForce) Uq = fma_of<kExact>(static_cast<Real>(p.cUF), Fq, Uq);
               slotP[(2 * kQ + q - 1) * kLanes + lane] = Uq;
             }
           }
           qnew[q] = Qq;
           if constexpr (gen_bbar) {  // Q2 = f^n + B-0 dt Omega(f^n)
-            Real Q2 = fma_of(k.cQ2g, g[q], k.kQ2[wclass(q)] * E);
-            if (kForce) Q2 = fma_of(static_cast<Real>(p.cQ2F), Fq, Q2);
+            Real Q2 = fma_of<kExact>(k.cQ2g, g[q], k.kQ2[wclass(q)] * E);
+            if (kForce) Q2 = fma_of<kExact>(static_cast<Real>(p.cQ2F), Fq, Q2);
             qnew[q] = Q2;
           }
         }
@@ -292,10 +300,10 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, kScheme), (kMinWave
           Real wyr[kWeightsPerNode];
           row_weights(weights_y<Real>(p), rm, wyr);
           // One base pointer per ring row r-2 .. r+2 at this lane.
-          LdsPtr<Real> rb[5];
+          Row rb[5];
 #pragma unroll
           for (int o = 0; o < 5; ++o)
-            rb[o] = (LdsPtr<Real>)(ringP + ((r + o - 2) & (kRing - 1)) * kNP * kLanes + lane);
+            rb[o] = (Row)(ringP + ((r + o - 2) & (kRing - 1)) * kNP * kLanes + lane);
           const auto& k = coef<Real>(p);
           // A prediction along the characteristics from ring planes
           // [base, base + 9): S = centre + fac L(centre); then f at the
@@ -311,43 +319,43 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, kScheme), (kMinWave
               const int pq = (base + q) * kLanes;
               const Real centre = rb[2][pq];
               Real acc = Real(0);
-              if (ex_of(q) > 0) acc = x_taps<0>(wxr, centre, acc);
-              if (ex_of(q) < 0) acc = x_taps<1>(wxr, centre, acc);
+              if (ex_of(q) > 0) acc = x_taps<0, kExact>(wxr, centre, acc);
+              if (ex_of(q) < 0) acc = x_taps<1, kExact>(wxr, centre, acc);
               if (ey_of(q) != 0) {
                 const int sy = ey_of(q) > 0 ? 0 : 1;
 #pragma unroll
-                for (int k2 = 0; k2 < kTaps; ++k2) acc = fma_of(wyr[sy * kTaps + k2], rb[k2 + sy][pq], acc);
+                for (int k2 = 0; k2 < kTaps; ++k2) acc = fma_of<kExact>(wyr[sy * kTaps + k2], rb[k2 + sy][pq], acc);
               }
-              S[q] = q == 0 ? centre : fma_of(fac, acc, centre);
+              S[q] = q == 0 ? centre : fma_of<kExact>(fac, acc, centre);
             }
             double s, jx, jy;
             moment_sums(S, s, jx, jy);
-            velocity(s, jx, jy, rho, ux, uy);
+            velocity<kExact>(s, jx, jy, rho, ux, uy);
             if (kForce) {
-              ux = add_scaled(hf, p.Fx, ux);
-              uy = add_scaled(hf, p.Fy, uy);
+              ux = add_scaled<kExact>(hf, p.Fx, ux);
+              uy = add_scaled<kExact>(hf, p.Fy, uy);
             }
             const Real d = static_cast<Real>(s);
-            eq_brackets(ux, uy, X);
+            eq_brackets<kExact>(ux, uy, X);
             R[0] = Real(0);
 #pragma unroll
             for (int q = 1; q < kQ; ++q) {
-              const Real E = fma_of(rho, X[q], d);
-              Real Rq = fma_of(cs, S[q], ke[wclass(q)] * E);
-              if (kForce) Rq = fma_of(static_cast<Real>(cf), force_term(q, p, ux, uy, E), Rq);
+              const Real E = fma_of<kExact>(rho, X[q], d);
+              Real Rq = fma_of<kExact>(cs, S[q], ke[wclass(q)] * E);
+              if (kForce) Rq = fma_of<kExact>(static_cast<Real>(cf), force_term<kExact>(q, p, ux, uy, E), Rq);
               R[q] = Rq;
             }
             if (want_v) {
               // Omega(f*) dt = w (f^eq* - f*) + dt F*, in deviations from w.
 #pragma unroll
               for (int q = 0; q < kQ; ++q) {
-                const Real E = fma_of(rho, X[q], d);
+                const Real E = fma_of<kExact>(rho, X[q], d);
                 Real Fq = Real(0);
-                if (kForce) Fq = force_term(q, p, ux, uy, E);
-                Real Rq = fma_of(cs, S[q], ke[wclass(q)] * E);
-                if (kForce) Rq = fma_of(static_cast<Real>(cf), Fq, Rq);
+                if (kForce) Fq = force_term<kExact>(q, p, ux, uy, E);
+                Real Rq = fma_of<kExact>(cs, S[q], ke[wclass(q)] * E);
+                if (kForce) Rq = fma_of<kExact>(static_cast<Real>(cf), Fq, Rq);
                 Real Vq = k.kV[wclass(q)] * E - k.cV * Rq;
-                if (kForce) Vq = fma_of(static_cast<Real>(p.cVF), Fq, Vq);
+                if (kForce) Vq = fma_of<kExact>(static_cast<Real>(p.cVF), Fq, Vq);
                 V[q] = Vq;
               }
             }
@@ -410,14 +418,28 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, kScheme), (kMinWave
                   // The shift from the brackets of u_f, formed above, and
                   // of the wall's velocity.
                   const Real* Xb = wall_brackets<Real>(p, wall_side_of(dx, dy));
-                  const Real r1 = Real(w_of(1)) * rho, r2 = Real(w_of(5)) * rho;
-                  const Real r1b = Real(w_of(1)) * rho2, r2b = Real(w_of(5)) * rho2;
                   Real* slotW = dy == 1 ? topR : ringR + ((r + dy) & (kRing - 1)) * (kQ - 1) * kLanes;
+                  if constexpr (kExact) {
+                    const Real r1 = Real(w_of(1)) * rho, r2 = Real(w_of(5)) * rho;
+                    const Real r1b = Real(w_of(1)) * rho2, r2b = Real(w_of(5)) * rho2;
 #pragma unroll
-                  for (int q = 1; q < kQ; ++q)
-                    slotW[(q - 1) * kLanes + lane + dx] =
-                        t_of(q, r + dy, lane + dx, nee_r(wclass(q) == 1 ? r1 : r2, X[q], Xb[q], R[q]),
-                             kFamily ? nee_r(wclass(q) == 1 ? r1b : r2b, X2[q], Xb[q], R2[q]) : R2[q]);
+                    for (int q = 1; q < kQ; ++q) {
+                      const Real wall1 = nee_r(wclass(q) == 1 ? r1 : r2, X[q], Xb[q], R[q]);
+                      const Real wall2 =
+                          kFamily ? nee_r(wclass(q) == 1 ? r1b : r2b, X2[q], Xb[q], R2[q]) : R2[q];
+                      slotW[(q - 1) * kLanes + lane + dx] = t_of(q, r + dy, lane + dx, wall1, wall2);
+                    }
+                  } else {
+                    Real sh[kQ], sh2[kQ];
+                    nee_shift_x(rho, X, Xb, sh);
+#pragma unroll
+                    for (int q = 0; q < kQ; ++q) sh2[q] = Real(0);
+                    if constexpr (kFamily) nee_shift_x(rho2, X2, Xb, sh2);
+#pragma unroll
+                    for (int q = 1; q < kQ; ++q)
+                      slotW[(q - 1) * kLanes + lane + dx] =
+                          t_of(q, r + dy, lane + dx, R[q] + sh[q], R2[q] + sh2[q]);
+                  }
                 }
               }
             }
@@ -434,11 +456,11 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, kScheme), (kMinWave
         if (row_ok) {
           Real wyr[kWeightsPerNode];
           row_weights(weights_y<Real>(p), o, wyr);
-          LdsPtr<Real> rb[5];
+          Row rb[5];
 #pragma unroll
           for (int k = 0; k < 5; ++k) {
-            rb[k] = (LdsPtr<Real>)(ringR + ((o + k - 2) & (kRing - 1)) * (kQ - 1) * kLanes + lane);
-            if (kWalls && !p.per_y && o + k - 2 == ny - 1) rb[k] = (LdsPtr<Real>)(topR + lane);
+            rb[k] = (Row)(ringR + ((o + k - 2) & (kRing - 1)) * (kQ - 1) * kLanes + lane);
+            if (kWalls && !p.per_y && o + k - 2 == ny - 1) rb[k] = (Row)(topR + lane);
           }
           Real out[kQ];
           // V of this row: formed in this iteration's phase 2 by waves 2
@@ -453,12 +475,29 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, kScheme), (kMinWave
             Real acc = kScheme == 2 ? Real(0) : qold[q];
             if constexpr (gen_bbar) acc += v_now ? vnew[q] : vold[q];
             const int sy = ey_of(q) > 0 ? 0 : 1;
-            Real rows[kTaps] = {};
-            if (ey_of(q) != 0) {
+            if constexpr (kExact) {
+              // The rows ahead of the sum, or with a force each where it is
+              // added: 1.5 to 3% either way (family cavity 16 x 10 27.7 us per
+              // step, each where added 28.7; channel 1500 x 1400 88.0, ahead
+              // 89.6).
+              if constexpr (kForce) {
+                acc = full_taps(q, wxr, wyr, centre, acc, [&](int k) { return rb[k + sy][pq]; });
+              } else {
+                Real rows[kTaps] = {};
+                if (ey_of(q) != 0) {
 #pragma unroll
-              for (int k = 0; k < kTaps; ++k) rows[k] = rb[k + sy][pq];
+                  for (int k = 0; k < kTaps; ++k) rows[k] = rb[k + sy][pq];
+                }
+                acc = full_taps(q, wxr, wyr, centre, acc, [&](int k) { return rows[k]; });
+              }
+            } else {
+              if (ex_of(q) > 0) acc = x_taps<0, false>(wxr, centre, acc);
+              if (ex_of(q) < 0) acc = x_taps<1, false>(wxr, centre, acc);
+              if (ey_of(q) != 0) {
+#pragma unroll
+                for (int k = 0; k < kTaps; ++k) acc += wyr[sy * kTaps + k] * rb[k + sy][pq];
+              }
             }
-            acc = full_taps(q, wxr, wyr, centre, acc, rows);
             out[q] = kScheme == 2 ? qold[q] + Real(0.5) * acc : acc;
           }
           if constexpr (gen_bbar) {
@@ -469,19 +508,19 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, kScheme), (kMinWave
             double s, jx, jy;
             moment_sums(out, s, jx, jy);
             Real rho, ux, uy;
-            velocity(s, jx, jy, rho, ux, uy);
+            velocity<kExact>(s, jx, jy, rho, ux, uy);
             if (kForce) {
-              ux = add_scaled(p.b2dt, p.Fx, ux);
-              uy = add_scaled(p.b2dt, p.Fy, uy);
+              ux = add_scaled<kExact>(p.b2dt, p.Fx, ux);
+              uy = add_scaled<kExact>(p.b2dt, p.Fy, uy);
             }
             const Real d = static_cast<Real>(s);
             Real X[kQ];
-            eq_brackets(ux, uy, X);
+            eq_brackets<kExact>(ux, uy, X);
 #pragma unroll
             for (int q = 0; q < kQ; ++q) {
-              const Real E = fma_of(rho, X[q], d);
+              const Real E = fma_of<kExact>(rho, X[q], d);
               Real o = k.aY * out[q] + k.kA[wclass(q)] * E;
-              if (kForce) o = fma_of(static_cast<Real>(p.aF), force_term(q, p, ux, uy, E), o);
+              if (kForce) o = fma_of<kExact>(static_cast<Real>(p.aF), force_term<kExact>(q, p, ux, uy, E), o);
               out[q] = o;
             }
           }
@@ -500,7 +539,18 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, kScheme), (kMinWave
       iteration(it + 1, gB, qB, qA, vB, vA);
     }
     __syncthreads();  // the next piece reuses the rings; the piece's stores are visible
-    if (kWalls) piece_walls(p, dst, x0, x1, y0, y1, threadIdx.x % kBlockThreads, kBlockThreads, p.uw);
+    if (kWalls)
+      piece_walls<kExact, sizeof(Store) == 2>(
+          p, dst, x0, x1, y0, y1, threadIdx.x % kBlockThreads, kBlockThreads,
+          [&](int c2, int r2, int side, double& u, double& v) {
+            // (By address, the unforced FP64 forms are 2% faster, the others slower.)
+            if (kExact && !kForce) {
+              u = p.uw[side][0];
+              v = p.uw[side][1];
+            } else {
+              wall_velocity(p, c2, r2, u, v);
+            }
+          });
   }
 }
 
@@ -808,7 +858,7 @@ __global__ __launch_bounds__((tile_waves<Store, kH>() * kLanes)) void tile_step_
 #pragma unroll
         for (int k2 = 0; k2 < kTaps; ++k2) rows[k2] = rb[k2 + sy][pq];
       }
-      out[q] = full_taps(q, wxr, wyr, centre, acc, rows);
+      out[q] = full_taps(q, wxr, wyr, centre, acc, [&](int k) { return rows[k]; });
     }
     if (lane_o && col_interior) {
       const unsigned boff =
@@ -819,7 +869,11 @@ __global__ __launch_bounds__((tile_waves<Store, kH>() * kLanes)) void tile_step_
   }
   if (kWalls) {
     __syncthreads();  // the tile's stores are visible to the block
-    piece_walls<Store, false>(p, dst, x0, x1, y0, y1, threadIdx.x, kWaves * kLanes, tU);
+    piece_walls<true, false>(p, dst, x0, x1, y0, y1, threadIdx.x, kWaves * kLanes,
+                             [&](int, int, int side, double& u, double& v) {
+                               u = tU[side][0];
+                               v = tU[side][1];
+                             });
   }
 }
 
@@ -849,6 +903,7 @@ template <typename Store, bool kForce, bool kWalls>
 __global__ __launch_bounds__(step_threads(kStorageOf<Store>, 0), (kMinWaves<Store, kForce, kWalls, 1>)) void single_step_kernel(
     StepParams p) {
   using Real = typename Cvt<Store>::R;
+  constexpr bool kExact = false;  // no other kernel takes this step; see step_kernel
   constexpr int kSB = strips_per_block(kStorageOf<Store>, 0);
   constexpr int kThreads = step_threads(kStorageOf<Store>, 0);
   constexpr int kSizeR = kRing1 * (kQ - 1) * kLanes;
@@ -939,25 +994,25 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, 0), (kMinWaves<Stor
         double s, jx, jy;
         moment_sums(g, s, jx, jy);
         Real rho, ux, uy;
-        velocity(s, jx, jy, rho, ux, uy);
+        velocity<kExact>(s, jx, jy, rho, ux, uy);
         if (kForce) {
-          ux = add_scaled(p.half_dt, p.Fx, ux);
-          uy = add_scaled(p.half_dt, p.Fy, uy);
+          ux = add_scaled<kExact>(p.half_dt, p.Fx, ux);
+          uy = add_scaled<kExact>(p.half_dt, p.Fy, uy);
         }
         const Real d = static_cast<Real>(s);
         Real X[kQ];
-        eq_brackets(ux, uy, X);
+        eq_brackets<kExact>(ux, uy, X);
         const auto& k = coef<Real>(p);
         Real R[kQ];
 #pragma unroll
         for (int q = 0; q < kQ; ++q) {
-          const Real E = fma_of(rho, X[q], d);
-          Real Rq = fma_of(k.cPg, g[q], k.kP[wclass(q)] * E);
-          Real Qq = fma_of(k.cQg, g[q], k.kQ[wclass(q)] * E);
+          const Real E = fma_of<kExact>(rho, X[q], d);
+          Real Rq = fma_of<kExact>(k.cPg, g[q], k.kP[wclass(q)] * E);
+          Real Qq = fma_of<kExact>(k.cQg, g[q], k.kQ[wclass(q)] * E);
           if (kForce) {
-            const Real Fq = force_term(q, p, ux, uy, E);
-            Rq = fma_of(static_cast<Real>(p.cPF), Fq, Rq);
-            Qq = fma_of(static_cast<Real>(p.cQF), Fq, Qq);
+            const Real Fq = force_term<kExact>(q, p, ux, uy, E);
+            Rq = fma_of<kExact>(static_cast<Real>(p.cPF), Fq, Rq);
+            Qq = fma_of<kExact>(static_cast<Real>(p.cQF), Fq, Qq);
           }
           R[q] = Rq;
           qnew[q] = Qq;
@@ -975,9 +1030,9 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, 0), (kMinWaves<Stor
             double s2, jx2, jy2;
             moment_sums(R, s2, jx2, jy2);
             Real rho2, ux2, uy2;
-            velocity(s2, jx2, jy2, rho2, ux2, uy2);
+            velocity<kExact>(s2, jx2, jy2, rho2, ux2, uy2);
             Real X2[kQ];
-            eq_brackets(ux2, uy2, X2);
+            eq_brackets<kExact>(ux2, uy2, X2);
             for (int dy = -1; dy <= 1; ++dy) {
               if ((dy == -1 && !src_yb) || (dy == 1 && !src_yt)) continue;
               for (int dx = -1; dx <= 1; ++dx) {
@@ -986,12 +1041,11 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, 0), (kMinWaves<Stor
                 // A source in the strip's edge lane has its wall node outside
                 // the strip; no output of this strip reads it.
                 if (lane + dx < 0 || lane + dx >= kLanes) continue;
-                const Real* Xb = wall_brackets<Real>(p, wall_side_of(dx, dy));
-                const Real r1 = Real(w_of(1)) * rho2, r2 = Real(w_of(5)) * rho2;
+                Real sh[kQ];
+                nee_shift_x(rho2, X2, wall_brackets<Real>(p, wall_side_of(dx, dy)), sh);
                 Real* slotW = ringR + ((pr + dy) & (kRing1 - 1)) * (kQ - 1) * kLanes;
 #pragma unroll
-                for (int q = 1; q < kQ; ++q)
-                  slotW[(q - 1) * kLanes + lane + dx] = nee_r(wclass(q) == 1 ? r1 : r2, X2[q], Xb[q], R[q]);
+                for (int q = 1; q < kQ; ++q) slotW[(q - 1) * kLanes + lane + dx] = R[q] + sh[q];
               }
             }
           }
@@ -1018,13 +1072,14 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, 0), (kMinWaves<Stor
             const int pq = (q - 1) * kLanes;
             const Real centre = rb[2][pq];
             Real acc = qold[q];
-            const int sy = ey_of(q) > 0 ? 0 : 1;
-            Real rows[kTaps] = {};
+            if (ex_of(q) > 0) acc = x_taps<0, kExact>(wxr, centre, acc);
+            if (ex_of(q) < 0) acc = x_taps<1, kExact>(wxr, centre, acc);
             if (ey_of(q) != 0) {
+              const int sy = ey_of(q) > 0 ? 0 : 1;
 #pragma unroll
-              for (int k = 0; k < kTaps; ++k) rows[k] = rb[k + sy][pq];
+              for (int k = 0; k < kTaps; ++k) acc += wyr[sy * kTaps + k] * rb[k + sy][pq];
             }
-            out[q] = full_taps(q, wxr, wyr, centre, acc, rows);
+            out[q] = acc;
           }
           if (lane_o && col_interior) {
             const unsigned boff =
@@ -1041,7 +1096,10 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, 0), (kMinWaves<Stor
       iteration(it + 1, gB, qB, qA);
     }
     __syncthreads();  // the next piece reuses the ring; the piece's stores are visible
-    if (kWalls) piece_walls(p, dst, x0, x1, y0, y1, threadIdx.x % kBlockThreads, kBlockThreads, p.uw);
+    if (kWalls)
+      piece_walls<kExact, false>(
+          p, dst, x0, x1, y0, y1, threadIdx.x % kBlockThreads, kBlockThreads,
+          [&](int c2, int r2, int, double& u, double& v) { wall_velocity(p, c2, r2, u, v); });
   }
 }
 

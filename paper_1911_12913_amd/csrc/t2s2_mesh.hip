@@ -199,7 +199,7 @@ __global__ __launch_bounds__(kNodes) void mesh_steps_kernel(StepParams p, int ns
           for (int k2 = 0; k2 < kTaps; ++k2) rows[k2] = k2 + sy == 2 ? R[q] : t[iy[k2 + sy]];
         }
         out[q] = full_taps_of(
-            q, wy, Q[q], rows,
+            q, wy, Q[q], [&](int k2) { return rows[k2]; },
             [&](Real acc) { return x_taps_at(ex_of(q), wx, R[q], acc, [&](int o) { return x[o + 2]; }); });
       }
       if constexpr (kStochastic<Store>) {

@@ -457,7 +457,11 @@ __global__ __launch_bounds__(kPairWaves * kLanes, 2) void pair_step_kernel(StepP
       const int x1 = min(x0 + kPairOut, p.nx);
       march_piece<kForce, true>(p, plan.wy16, hand, lane, role, x0, x1, y0, y1);
       __syncthreads();  // the piece's stores are visible to the block
-      piece_walls(p, static_cast<double*>(p.dst), x0, x1, y0, y1, threadIdx.x, kPairWaves * kLanes, p.uw);
+      piece_walls<true, false>(p, static_cast<double*>(p.dst), x0, x1, y0, y1, threadIdx.x,
+                               kPairWaves * kLanes, [&](int, int, int side, double& u, double& v) {
+                                 u = p.uw[side][0];
+                                 v = p.uw[side][1];
+                               });
       return;
     }
     block -= plan.frame;

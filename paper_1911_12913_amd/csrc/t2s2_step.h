@@ -82,21 +82,21 @@ __device__ inline int wrap_near(int i, int n) {
 // along x: offsets (-2,-1,0,+1) for a positive velocity component (sx = 0),
 // (-1,0,+1,+2) for a negative one (sx = 1); the neighbours come from the
 // centre values of the other lanes.
-template <int sx, typename Real>
+template <int sx, bool kExact = true, typename Real>
 __device__ inline Real x_taps(const Real* w, Real centre, Real acc) {
   const Real m1 = from_below(centre), p1 = from_above(centre);
   if (sx == 0) {
     const Real m2 = from_below(m1);
-    acc = fma_of(w[0], m2, acc);
-    acc = fma_of(w[1], m1, acc);
-    acc = fma_of(w[2], centre, acc);
-    acc = fma_of(w[3], p1, acc);
+    acc = fma_of<kExact>(w[0], m2, acc);
+    acc = fma_of<kExact>(w[1], m1, acc);
+    acc = fma_of<kExact>(w[2], centre, acc);
+    acc = fma_of<kExact>(w[3], p1, acc);
   } else {
     const Real p2 = from_above(p1);
-    acc = fma_of(w[4], m1, acc);
-    acc = fma_of(w[5], centre, acc);
-    acc = fma_of(w[6], p1, acc);
-    acc = fma_of(w[7], p2, acc);
+    acc = fma_of<kExact>(w[4], m1, acc);
+    acc = fma_of<kExact>(w[5], centre, acc);
+    acc = fma_of<kExact>(w[6], p1, acc);
+    acc = fma_of<kExact>(w[7], p2, acc);
   }
   return acc;
 }
@@ -114,15 +114,15 @@ using LdsPtr = const __attribute__((address_space(3))) Real*;
 // terms: the rows above, the row itself (the x taps first), the rows below.
 // FP32 takes the x taps first.
 // x(acc): acc plus the x taps.
-template <typename Real, typename X>
+template <typename Real, typename Row, typename X>
 __device__ __forceinline__ Real full_taps_of(int q, const Real* wy, Real acc,
-                                             const Real (&row)[kTaps], X x) {
+                                             Row row, X x) {
   const int sy = ey_of(q) > 0 ? 0 : 1;
   if constexpr (sizeof(Real) == 4) {
     acc = x(acc);
     if (ey_of(q) != 0) {
 #pragma unroll
-      for (int k = 0; k < kTaps; ++k) acc += wy[sy * kTaps + k] * row[k];
+      for (int k = 0; k < kTaps; ++k) acc += wy[sy * kTaps + k] * row(k);
     }
     return acc;
   }
@@ -131,19 +131,19 @@ __device__ __forceinline__ Real full_taps_of(int q, const Real* wy, Real acc,
   if (ey_of(q) != 0) {
 #pragma unroll
     for (int k = 0; k < 2; ++k)
-      if (k < above) acc = fma_of(wy[sy * kTaps + k], row[k], acc);
+      if (k < above) acc = fma_of(wy[sy * kTaps + k], row(k), acc);
   }
   acc = x(acc);
   if (ey_of(q) != 0) {
 #pragma unroll
     for (int k = 1; k < kTaps; ++k)
-      if (k >= above) acc = fma_of(wy[sy * kTaps + k], row[k], acc);
+      if (k >= above) acc = fma_of(wy[sy * kTaps + k], row(k), acc);
   }
   return acc;
 }
-template <typename Real>
+template <typename Real, typename Row>
 __device__ __forceinline__ Real full_taps(int q, const Real* wx, const Real* wy, Real centre,
-                                          Real acc, const Real (&row)[kTaps]) {
+                                          Real acc, Row row) {
   return full_taps_of(q, wy, acc, row, [&](Real a) {
     if (ex_of(q) > 0) a = x_taps<0>(wx, centre, a);
     if (ex_of(q) < 0) a = x_taps<1>(wx, centre, a);
@@ -153,9 +153,9 @@ __device__ __forceinline__ Real full_taps(int q, const Real* wx, const Real* wy,
 
 // Guo force term (eq 3.12) of direction q from E = (f^eq_q - w_q) / w_q:
 // F_q = 3 (F . (xi_q - u)) f^eq_q with f^eq_q = w_q (1 + E).
-template <typename Real>
+template <bool kExact = true, typename Real>
 __device__ inline Real force_term(int q, const StepParams& p, Real ux, Real uy, Real E) {
-  const Real fu = fma_of(static_cast<Real>(p.Fx), Real(ex_of(q)) - ux,
+  const Real fu = fma_of<kExact>(static_cast<Real>(p.Fx), Real(ex_of(q)) - ux,
                          static_cast<Real>(p.Fy) * (Real(ey_of(q)) - uy));
   return Real(3.0 * w_of(q)) * fu * (Real(1) + E);
 }
@@ -169,15 +169,14 @@ __device__ inline Real force_term(int q, const StepParams& p, Real ux, Real uy, 
 // piece's outputs (columns [x0, x1)), which this block has just stored, so
 // the loads see them (the coherence point is L2; the buffer was not read
 // earlier in the launch).  Each wall node has exactly one source node, and
-// each source node is output by exactly one piece.  uw: the walls'
-// velocities (p.uw or a copy of it).  kLoadsFirst keeps the conversions of the
-// 16-bit forms behind all nine loads: taken one by one, each load waits out a
-// round trip (16-bit T2S2-FDLBM2 cavity 236 x 245, 18.7 us per step, 17.5 so;
-// the tile kernel's 16-bit forms are not scheduled that way and are 2% slower
-// with it).
-template <typename Store, bool kLoadsFirst = sizeof(Store) == 2>
+// each source node is output by exactly one piece.  wall_u(c, r, side, u, v):
+// the velocity of the wall's node (c, r).  kLoadsFirst keeps the conversions of
+// the 16-bit forms behind all nine loads, where step_kernel otherwise takes
+// them one by one and each load waits out a round trip (BF16 T2S2-FDLBM2 cavity
+// 23 x 215, 20.5 us per step, 19.1 so).
+template <bool kExact, bool kLoadsFirst, typename Store, typename WallU>
 __device__ inline void piece_walls(const StepParams& p, Store* dst, int x0, int x1, int y0,
-                                   int y1, int tid, int nthreads, const double (*uw)[2]) {
+                                   int y1, int tid, int nthreads, WallU wall_u) {
   using Real = typename Cvt<Store>::R;
   const int nx = p.nx, ny = p.ny;
   // Interior output columns and rows of this strip-piece.
@@ -208,19 +207,24 @@ __device__ inline void piece_walls(const StepParams& p, Store* dst, int x0, int 
       j = ry0 + (rb ? 1 : 0) + kb % nrows_b;
     }
     const long long fb = static_cast<long long>(j) * p.pitch + i;
-    Store raw[kQ];
-#pragma unroll
-    for (int q = 0; q < kQ; ++q) raw[q] = dst[q * p.plane + fb];
-    if constexpr (kLoadsFirst) __builtin_amdgcn_sched_barrier(0);
     Real v[kQ];
+    if constexpr (kLoadsFirst) {
+      Store raw[kQ];
 #pragma unroll
-    for (int q = 0; q < kQ; ++q) v[q] = Cvt<Store>::ld(raw[q]);
+      for (int q = 0; q < kQ; ++q) raw[q] = dst[q * p.plane + fb];
+      __builtin_amdgcn_sched_barrier(0x4);
+#pragma unroll
+      for (int q = 0; q < kQ; ++q) v[q] = Cvt<Store>::ld(raw[q]);
+    } else {
+#pragma unroll
+      for (int q = 0; q < kQ; ++q) v[q] = Cvt<Store>::ld(dst[q * p.plane + fb]);
+    }
     double s, jx, jy;
     moment_sums(v, s, jx, jy);
     const double rho = 1.0 + s;
     const double ir = recip(rho);
-    const double ux = fma_of(jx, ir, p.half_dt * p.Fx);
-    const double uy = fma_of(jy, ir, p.half_dt * p.Fy);
+    const double ux = fma_of<kExact>(jx, ir, p.half_dt * p.Fx);
+    const double uy = fma_of<kExact>(jy, ir, p.half_dt * p.Fy);
     const bool wl = !p.per_x && i == 1, wr = !p.per_x && i == nx - 2;
     const bool wb = !p.per_y && j == 1, wt = !p.per_y && j == ny - 2;
 #pragma unroll 1
@@ -230,9 +234,10 @@ __device__ inline void piece_walls(const StepParams& p, Store* dst, int x0, int 
       for (int dx = -1; dx <= 1; ++dx) {
         if ((dx == -1 && !wl) || (dx == 1 && !wr)) continue;
         if (dx == 0 && dy == 0) continue;
-        const int side = wall_side_of(dx, dy);
+        double ub, vb;
+        wall_u(i + dx, j + dy, wall_side_of(dx, dy), ub, vb);
         Real sh[kQ];
-        nee_shift(rho, ux, uy, uw[side][0], uw[side][1], sh);
+        nee_shift<kExact>(rho, ux, uy, ub, vb, sh);
         const long long wo = static_cast<long long>(j + dy) * p.pitch + (i + dx);
 #pragma unroll
         for (int q = 0; q < kQ; ++q) dst[q * p.plane + wo] = Cvt<Store>::st(v[q] + sh[q]);
