@@ -49,6 +49,7 @@ BYTES_PER_NODE = {"f64": 144, "f32": 72, "bf16": 36, "f16": 36, "bf16sr": 36, "f
 METRIC = "D2Q9 MLUPS & % HBM peak, FP64 vs FP32/BF16-store at stated L2 error"
 KERNEL_SOURCES = ["paper_1911_12913_amd/csrc/t2s2_kernels.hip",
                   "paper_1911_12913_amd/csrc/t2s2_pair.hip",
+                  "paper_1911_12913_amd/csrc/t2s2_mesh.hip",
                   "paper_1911_12913_amd/csrc/t2s2_step.h",
                   "paper_1911_12913_amd/csrc/t2s2_device.h",
                   "paper_1911_12913_amd/csrc/t2s2_internal.h",
@@ -157,7 +158,7 @@ def gpu_leg(case, storage, steps, warmup, warmup_s=1.0, windows=5, **overrides):
               "ms_per_step_median": ms / steps,
               "spread": (max(wins) - min(wins)) / ms,
               "warmup_steps": warmup, "warmup_s": warm_s, "warmup_time_steps": extra,
-              "steps_from_init": ctx.steps_taken}
+              "steps_from_init": ctx.steps_taken, "kernel": ctx.step_kernel(steps)}
     diag = ctx.diagnostics()
     _, ux, uy = ctx.moments()
     torch.cuda.synchronize()
@@ -346,7 +347,7 @@ def configs_leg(threads):
     out["tgv32x32"] = {"steps": 1000, "gpu_mlups": gm, "gpu_us_per_step": gms * 1e3,
                        "oracle_mlups": om, "oracle_threads": 1, "oracle_s": osec,
                        "rel_l2_gpu_vs_oracle": W.rel_l2(g, ref),
-                       "note": "launch-bound: one 1024-node launch per step"}
+                       "note": "one block takes 256 steps per launch"}
 
     # cavity 257^2: graph-launched GPU steps, oracle prefix
     c2 = W.cavity_case(256, lid=0.1, re=1000.0, cfl=0.9, eta=0.1, noise=1e-6, seed=0)
@@ -435,11 +436,10 @@ def main(argv=None):
         del a, b
     ms_step = ms / args.steps
     mlups = nodes * args.steps / (ms * 1e-3) / 1e6
-    # On large FP64 grids four steps at a time go as two launches of the
-    # kernel that takes two steps in one pass over the state; the rest are
-    # single steps.
-    pair = args.storage == "f64" and n >= 2048
-    passes = 2 * (args.steps // 4) + args.steps % 4 if pair else args.steps
+    # Passes over the state: the two-step kernel takes four steps of a window as
+    # two launches and the rest as single steps; one block takes up to 256.
+    passes = {"pair_step_kernel": 2 * (args.steps // 4) + args.steps % 4,
+              "mesh_steps_kernel": -(-args.steps // 256)}.get(timing["kernel"], args.steps)
     bytes_step = BYTES_PER_NODE[args.storage] * passes / args.steps
     achieved = bytes_step * nodes / (ms_step * 1e-3) / 1e9
     traffic = measured_traffic(args.storage)
@@ -480,7 +480,7 @@ def main(argv=None):
         exact0 = torch.stack([torch.from_numpy(ue0), torch.from_numpy(ve0)]).to("cuda:0")
         t1s2 = {"value": v_0, "unit": "MLUPS", "ms_per_step": ms_0 / t1s2_steps,
                 "steps": t1s2_steps, "scheme": "T1S2 (A = 0)", "storage": "f64", "cfl": 0.25,
-                "dt": dt_0, "kernel": "single_step_kernel",
+                "dt": dt_0, "kernel": tim_0["kernel"],
                 "hbm_frac": BYTES_PER_NODE["f64"] * nodes / (ms_0 / t1s2_steps * 1e-3) / 1e9
                 / HBM_PEAK_GBS,
                 "t2s2_fdlbm1_step_time_ratio": ms_step / (ms_0 / t1s2_steps),
@@ -566,7 +566,7 @@ def main(argv=None):
         "timing": timing,
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                     "kernel": "pair_step_kernel" if pair else "step_kernel",
+                     "kernel": timing["kernel"],
                      "bytes_per_node": bytes_step,
                      "frac_of_copy_ceiling": head["step_frac_of_ceiling"]},
         "copy_ceiling": ceiling,

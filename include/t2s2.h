@@ -152,6 +152,14 @@ size_t t2s2_workspace_bytes(const t2s2_ctx* ctx);
  * kind. */
 int t2s2_bind(t2s2_ctx* ctx, void* state_a, void* state_b, void* workspace, void* stream);
 
+/* Name of the kernel that takes the steps of a t2s2_step call of nsteps steps
+ * under the plan made by t2s2_bind (for reports and checks; a static string):
+ * "step_kernel", "single_step_kernel" (A = 0) and "tile_step_kernel" take one
+ * step per launch, "mesh_steps_kernel" up to 256, and "pair_step_kernel" two,
+ * four steps of the call at a time, the rest as for fewer steps.  "" for a
+ * NULL or unbound context. */
+const char* t2s2_step_kernel(const t2s2_ctx* ctx, int64_t nsteps);
+
 /* f~ = f^eq(rho, u) (Sec. 3), minus the non-equilibrium part of eq 3.5
  * when grad is non-NULL: rho0 w (2 tau + dt)/(2 c_s^2) xi xi : grad u with
  * rho0 = 1.  Device pointers: rho, ux, uy [ny][nx]; grad [4][ny][nx] =

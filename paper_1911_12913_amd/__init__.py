@@ -99,6 +99,7 @@ def load_library(path: str = LIB_PATH):
         "t2s2_state_bytes": (sz, [vp]),
         "t2s2_workspace_bytes": (sz, [vp]),
         "t2s2_bind": (i, [vp, vp, vp, vp, vp]),
+        "t2s2_step_kernel": (ctypes.c_char_p, [vp, i64]),
         "t2s2_init_macro": (i, [vp, vp, vp, vp, vp]),
         "t2s2_init_distributions": (i, [vp, vp]),
         "t2s2_step": (i, [vp, i64]),
@@ -139,7 +140,7 @@ def load_library(path: str = LIB_PATH):
 
 def exported_symbols() -> Sequence[str]:
     return ("t2s2_create", "t2s2_state_bytes", "t2s2_workspace_bytes", "t2s2_bind",
-            "t2s2_init_macro", "t2s2_init_distributions", "t2s2_step", "t2s2_graph_capture",
+            "t2s2_step_kernel", "t2s2_init_macro", "t2s2_init_distributions", "t2s2_step", "t2s2_graph_capture",
             "t2s2_graph_step", "t2s2_current",
             "t2s2_steps_taken", "t2s2_dt", "t2s2_moments", "t2s2_read_distributions",
             "t2s2_diagnostics", "t2s2_diagnostics_noalloc", "t2s2_velocity_error", "t2s2_stencil_weights", "t2s2_omega", "t2s2_adjoint_state_bytes",
@@ -310,6 +311,10 @@ class Context:
 
     def step(self, n: int = 1):
         self._call(_lib.t2s2_step, int(n))
+
+    def step_kernel(self, n: int) -> str:
+        """Name of the kernel that takes the steps of step(n) (t2s2_step_kernel)."""
+        return _lib.t2s2_step_kernel(self._h, int(n)).decode()
 
     def graph_capture(self, steps_per_graph: int):
         """Record steps_per_graph (even) steps into a HIP graph; needs the

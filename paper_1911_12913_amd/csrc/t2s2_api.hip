@@ -783,12 +783,15 @@ int t2s2_bind(t2s2_ctx* c, void* state_a, void* state_b, void* workspace, void* 
   return T2S2_OK;
 }
 
+// Whether one block takes all nsteps steps of a call.
+static bool takes_mesh(const t2s2_ctx* c, int64_t nsteps) { return c->mesh_steps && nsteps > 1; }
+
 // Launches nsteps steps from buffer cur, which ends as the buffer that holds
 // the result.  Where the two-step kernel applies, four steps at a time go as
 // two launches of it, which end in the buffer they began in, as four single
 // steps do.
 static hipError_t launch_steps(t2s2_ctx* c, int64_t nsteps, int& cur, int64_t* taken) {
-  if (c->mesh_steps && nsteps > 1) {
+  if (takes_mesh(c, nsteps)) {
     // All of them in one block, at most kMeshSteps to a launch, which ends in
     // the buffer that as many single steps end in.  (A step alone is faster
     // over many CUs: 16.5 against 18.8 us with its read-back, cavity 31^2.)
@@ -825,6 +828,14 @@ static hipError_t launch_steps(t2s2_ctx* c, int64_t nsteps, int& cur, int64_t* t
     if (taken) ++*taken;
   }
   return hipSuccess;
+}
+
+const char* t2s2_step_kernel(const t2s2_ctx* c, int64_t nsteps) {
+  if (!c || !c->bound) return "";
+  if (takes_mesh(c, nsteps)) return "mesh_steps_kernel";
+  if (c->grid_pair > 0 && nsteps >= 4) return "pair_step_kernel";
+  if (c->sp.tile) return "tile_step_kernel";
+  return c->sp.single ? "single_step_kernel" : "step_kernel";
 }
 
 int t2s2_init_macro(t2s2_ctx* c, const double* rho, const double* ux, const double* uy,

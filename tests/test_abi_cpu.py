@@ -37,6 +37,14 @@ def test_config_struct_layout():
     assert t2s2.Config.bbar.offset == 8 * 5 + 16 + 64 + 8 + 16 + 8 + 24
 
 
+def test_step_kernel_name_needs_a_bound_context():
+    lib = t2s2.load_library()
+    assert lib.t2s2_step_kernel(None, 4) == b""
+    rc, h = _create(_good_cfg(), _axis(20), _axis(20))
+    assert rc == t2s2.OK and lib.t2s2_step_kernel(h, 4) == b""
+    lib.t2s2_destroy(h)
+
+
 def test_scheme_validation():
     lib = t2s2.load_library()
     for scheme, ok in ((0, True), (1, True), (2, True), (3, True), (4, False), (-1, False)):

@@ -1065,3 +1065,17 @@ def test_tile_shapes_are_bitwise_the_march(kind, storage, monkeypatch):
     assert np.array_equal(states[1], states[2])
     if kind != "tgv_forced" or storage == "f64":
         assert np.array_equal(states[0], states[1])
+
+
+@pytest.mark.parametrize("n,storage,A,steps,kernel", [
+    (32, "f64", 0.5, 20, "mesh_steps_kernel"), (32, "f64", 0.5, 1, "tile_step_kernel"),
+    (200, "f64", 0.5, 20, "tile_step_kernel"), (1200, "f64", 0.5, 3, "step_kernel"),
+    (1400, "f64", 0.5, 4, "pair_step_kernel"), (1400, "f64", 0.5, 3, "step_kernel"),
+    (1400, "f32", 0.5, 20, "step_kernel"), (64, "f64", 0.0, 20, "single_step_kernel")])
+def test_step_kernel_names_the_plan(n, storage, A, steps, kernel):
+    """t2s2_step_kernel names the kernel of the bound plan: one block, tiles,
+    the march, two steps per launch (from four steps), the single stencil."""
+    x, p = W.uniform_periodic(n, 0.0, 1.0)
+    ctx = t2s2.Context(t2s2.make_config(nu=1e-3, cfl=0.5, A=A, storage=storage, period_x=p,
+                                        period_y=p), x, x)
+    assert ctx.step_kernel(steps) == kernel
