@@ -296,6 +296,31 @@ constexpr long long kPairMinWork = 52;
 // Steps of one launch of the one-block kernel: about a millisecond.
 constexpr int64_t kMeshSteps = 256;
 
+// Steps of a call from which one block takes them all, 0 if it never does.
+// Meshes that fit one block, where a launch per step is mostly the launch;
+// against the tile kernel, us per call (one block / tiles):
+//   up to 512 nodes from two steps (FP64 forced channel 10 x 21, 2 steps 7 / 15,
+//     20 steps 34 / 152; walled 16 x 32 14.7 / 18.2, 111 / 182);
+//   beyond, where a thread holds half the registers, FP64 on periodic grids so
+//     too (Taylor-Green 32^2, 2 steps 12.0 / 13.0, 20 steps 81 / 129); with walls
+//     it spills, so only from 8 steps and up to 800 nodes (784 nodes, 8 steps
+//     69.9 / 71.7, 20 steps 165 / 179; 900 nodes, 20 steps 183 / 178); with a
+//     force never (channel 31 x 33, 20 steps 288 / 157);
+//   the reduced forms with walls from three steps (1024 nodes, BF16, 2 steps 14.4
+//     / 14.7, 3 steps 19.9 / 22.1, 20 steps 113 / 147).  Not on periodic grids,
+//     where the compiler fuses the FP32 products in another way than in the tile
+//     kernel, and stochastic rounding would turn last-bit differences into whole
+//     units of the 16-bit forms.
+int plan_mesh(const StepParams& sp, int storage) {
+  const bool walls = !sp.per_x || !sp.per_y;
+  const long long nodes = static_cast<long long>(sp.nx) * sp.ny;
+  if (nodes > kMeshNodes || (storage != kF64 && !walls)) return 0;
+  if (nodes <= kMeshNodes / 2) return 2;
+  if (storage != kF64) return 3;
+  if (sp.has_force || (walls && nodes > 800)) return 0;
+  return walls ? 8 : 2;
+}
+
 // The two-step kernel's plan: the frame of a walled mesh and the main strips
 // and rows inside it, over one block per resident slot, so that a frame
 // piece and a main block's share take about the same time.  Returns the grid,
@@ -411,8 +436,8 @@ struct t2s2_ctx {
   // Plan of the two-step kernel; grid_pair 0: this context does not take it.
   PairPlan pair{};
   int grid_pair = 0;
-  // The mesh fits one block, which takes all steps of a call.
-  bool mesh_steps = false;
+  // One block takes all steps of a call of this many steps or more (0: never).
+  int mesh_from = 0;
   // adjoint
   AdjParams adj{};
   bool adj_bound = false;
@@ -762,15 +787,8 @@ int t2s2_bind(t2s2_ctx* c, void* state_a, void* state_b, void* workspace, void* 
       if (t[0] >= '0' && t[0] <= '2') c->sp.tile = t[0] - '0';
   }
   if (!c->sp.single) c->sp_gen = c->sp;
-  // Meshes that fit one block take all steps of a call in it (us per step,
-  // FP64: forced channel 10 x 21 8.6 -> 2.6, Taylor-Green 32^2 6.3 -> 3.9;
-  // T2S2_TILE keeps the tile kernel).  The reduced forms do so on walled
-  // meshes, where the compiler fuses the FP32 products as in the tile kernel;
-  // on periodic ones it does not, and stochastic rounding would turn last-bit
-  // differences into whole units of the 16-bit forms.
-  c->mesh_steps = c->sp.tile && static_cast<long long>(c->nx) * c->ny <= kMeshNodes &&
-                  (c->cfg.storage == T2S2_F64 || !c->sp.per_x || !c->sp.per_y) &&
-                  !std::getenv("T2S2_TILE");
+  // (T2S2_TILE selects single steps.)
+  c->mesh_from = c->sp.tile && !std::getenv("T2S2_TILE") ? plan_mesh(c->sp, c->cfg.storage) : 0;
   c->grid_pair = 0;
   if (c->cfg.storage == T2S2_F64 && c->sp.scheme == 1 && !c->sp.single &&
       !std::getenv("T2S2_BLOCKS")) {
@@ -784,7 +802,9 @@ int t2s2_bind(t2s2_ctx* c, void* state_a, void* state_b, void* workspace, void* 
 }
 
 // Whether one block takes all nsteps steps of a call.
-static bool takes_mesh(const t2s2_ctx* c, int64_t nsteps) { return c->mesh_steps && nsteps > 1; }
+static bool takes_mesh(const t2s2_ctx* c, int64_t nsteps) {
+  return c->mesh_from > 0 && nsteps >= c->mesh_from;
+}
 
 // Launches nsteps steps from buffer cur, which ends as the buffer that holds
 // the result.  Where the two-step kernel applies, four steps at a time go as
@@ -793,8 +813,7 @@ static bool takes_mesh(const t2s2_ctx* c, int64_t nsteps) { return c->mesh_steps
 static hipError_t launch_steps(t2s2_ctx* c, int64_t nsteps, int& cur, int64_t* taken) {
   if (takes_mesh(c, nsteps)) {
     // All of them in one block, at most kMeshSteps to a launch, which ends in
-    // the buffer that as many single steps end in.  (A step alone is faster
-    // over many CUs: 16.5 against 18.8 us with its read-back, cavity 31^2.)
+    // the buffer that as many single steps end in.
     for (int64_t left = nsteps; left > 0;) {
       const int n = static_cast<int>(std::min<int64_t>(left, kMeshSteps));
       c->sp.src = c->state[cur];

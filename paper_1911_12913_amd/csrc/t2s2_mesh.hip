@@ -246,13 +246,20 @@ template <typename Store, int kNodes>
 hipError_t launch_mesh_n(const StepParams& p, int nsteps, hipStream_t s) {
   const dim3 b((p.nx * p.ny + kLanes - 1) / kLanes * kLanes);
   auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(1), b, 0, s, p, nsteps); };
+  // The forms that a plan selects (plan_mesh): FP64 with a force on the smaller
+  // blocks only, the reduced forms with walls only.
+  constexpr bool kFp64 = std::is_same<Store, double>::value;
   const bool walls = !p.per_x || !p.per_y;
-  if (p.has_force)
-    walls ? go(mesh_steps_kernel<Store, true, true, kNodes>)
-          : go(mesh_steps_kernel<Store, true, false, kNodes>);
-  else
-    walls ? go(mesh_steps_kernel<Store, false, true, kNodes>)
-          : go(mesh_steps_kernel<Store, false, false, kNodes>);
+  if (p.has_force) {
+    if constexpr (kFp64 && kNodes > kMeshNodes / 2) return hipErrorInvalidValue;
+    else if (walls) go(mesh_steps_kernel<Store, true, true, kNodes>);
+    else if constexpr (kFp64) go(mesh_steps_kernel<Store, true, false, kNodes>);
+    else return hipErrorInvalidValue;
+  } else {
+    if (walls) go(mesh_steps_kernel<Store, false, true, kNodes>);
+    else if constexpr (kFp64) go(mesh_steps_kernel<Store, false, false, kNodes>);
+    else return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 template <typename Store>

@@ -1079,3 +1079,40 @@ def test_step_kernel_names_the_plan(n, storage, A, steps, kernel):
     ctx = t2s2.Context(t2s2.make_config(nu=1e-3, cfl=0.5, A=A, storage=storage, period_x=p,
                                         period_y=p), x, x)
     assert ctx.step_kernel(steps) == kernel
+
+
+@pytest.mark.parametrize("flow,nx,ny,storage,first", [
+    ("channel", 16, 32, "f64", 2), ("channel", 27, 19, "f64", None),
+    ("channel", 31, 33, "f64", None), ("channel", 31, 33, "bf16sr", 3),
+    ("channel", 16, 32, "f32", 2), ("cavity", 28, 28, "f64", 8), ("cavity", 29, 29, "f64", None),
+    ("cavity", 31, 33, "f16", 3), ("tgv_forced", 27, 19, "f64", None), ("tgv", 27, 19, "f64", 2),
+    ("tgv", 16, 32, "f32", None), ("tgv", 32, 33, "f64", None)])
+def test_one_block_is_taken_where_it_is_faster(flow, nx, ny, storage, first, monkeypatch):
+    """The steps of a call go to one block from `first` steps on (None: never:
+    FP64 beyond 512 nodes with a force or, beyond 800, with walls, where it took
+    up to twice the time of a launch per step; more than 1024 nodes; the reduced
+    forms on periodic grids), and on either side of the rule the state is bitwise
+    that of tiles."""
+    monkeypatch.delenv("T2S2_BLOCKS", raising=False)
+    if flow.startswith("tgv"):
+        case = W.tgv_case(nx, ny, u0=0.02, nu=0.05, cfl=0.7, eta=0.05)
+        case.force = (1e-3, -2e-3) if flow == "tgv_forced" else (0.0, 0.0)
+    else:
+        case = W.cavity_case(8, lid=0.1, re=100.0, cfl=0.8, eta=0.1, noise=0.0, seed=4)
+        case.y = W.tanh_walled(ny - 1, 1.5)
+        if flow == "cavity":
+            case.x = W.tanh_walled(nx - 1, 1.5)
+        else:
+            case.x, case.periodic_x, case.period_x = np.arange(nx) / nx, True, 1.0
+            case.force = (1e-3, 0.0)
+        case.rho0, case.ux0, case.uy0 = (np.full((ny, nx), v) for v in (1.0, 0.0, 0.0))
+    phi0 = W.random_state((9, ny, nx), 1e-3, 8)
+    for n in (1, 2, 3, 7, 8, 20):
+        ctx, g, *_ = _gpu_run(case, phi0, n, storage=storage)
+        one_block = first is not None and n >= first
+        assert (ctx.step_kernel(n) == "mesh_steps_kernel") == one_block, (n, ctx.step_kernel(n))
+        if n in (3, 8, 20):
+            monkeypatch.setenv("T2S2_TILE", "1")
+            _, g_tile, *_ = _gpu_run(case, phi0, n, storage=storage)
+            monkeypatch.delenv("T2S2_TILE")
+            assert np.array_equal(g, g_tile)
