@@ -787,13 +787,15 @@ int t2s2_bind(t2s2_ctx* c, void* state_a, void* state_b, void* workspace, void* 
       if (t[0] >= '0' && t[0] <= '2') c->sp.tile = t[0] - '0';
   }
   if (!c->sp.single) c->sp_gen = c->sp;
-  // (T2S2_TILE selects single steps.)
-  c->mesh_from = c->sp.tile && !std::getenv("T2S2_TILE") ? plan_mesh(c->sp, c->cfg.storage) : 0;
+  // T2S2_TILE selects single steps, T2S2_PAIR_BLOCKS the two-step kernel.
+  const bool single_steps = std::getenv("T2S2_TILE") != nullptr;
+  const bool two_steps = std::getenv("T2S2_PAIR_BLOCKS") != nullptr;
+  c->mesh_from =
+      c->sp.tile && !single_steps && !two_steps ? plan_mesh(c->sp, c->cfg.storage) : 0;
   c->grid_pair = 0;
   if (c->cfg.storage == T2S2_F64 && c->sp.scheme == 1 && !c->sp.single &&
-      !std::getenv("T2S2_BLOCKS")) {
+      !std::getenv("T2S2_BLOCKS"))
     c->grid_pair = plan_pair(c->sp, c->pair, cus);
-  }
   if (c->grid < 1 || c->grid_gen < 1) return fail(T2S2_ERR_HIP, "bind: step kernel cannot be resident");
   c->bound = true;
   c->cur = 0;

@@ -1116,3 +1116,61 @@ def test_one_block_is_taken_where_it_is_faster(flow, nx, ny, storage, first, mon
             _, g_tile, *_ = _gpu_run(case, phi0, n, storage=storage)
             monkeypatch.delenv("T2S2_TILE")
             assert np.array_equal(g, g_tile)
+
+
+def _forced_channel(nx, ny, walled_x=False):
+    """A channel (walls on y, on x too) with a force and main pieces, whose x and
+    y walls move."""
+    case = W.poiseuille_case(dt_over_y1=0.9, eta=0.1)
+    case.y = W.tanh_walled(ny - 1, 1.5)
+    case.x, case.period_x = np.arange(nx) / nx, 1.0
+    if walled_x:
+        case.x, case.periodic_x = W.tanh_walled(nx - 1, 1.5), False
+    case.force, case.nu, case.dt, case.cfl = (1e-3, -5e-4), 0.01, None, 0.7
+    case.u_wall = np.array([[0.002, 0.03], [-0.001, -0.02], [0.025, 0.0], [0.03, 0.0]])
+    case.rho0, case.ux0, case.uy0 = (np.full((ny, nx), v) for v in (1.0, 0.0, 0.0))
+    return case
+
+
+@pytest.mark.parametrize("kind", ["tgv5x7", "cavity5", "channel", "channel150x70",
+                                  "channel300x61", "cavity150x70_forced"])
+def test_two_step_kernel_runs_where_it_is_forced(kind, monkeypatch):
+    """T2S2_PAIR_BLOCKS selects the two-step kernel on the smallest meshes too
+    (which one block takes otherwise), and with a force and walls on one axis
+    and on both, in main pieces and frame: bitwise single steps of the march,
+    and the oracle."""
+    if kind.startswith("channel1") or kind.startswith("channel3"):
+        case = _forced_channel(*map(int, kind[len("channel"):].split("x")))
+    elif kind == "cavity150x70_forced":
+        case = _forced_channel(150, 70, walled_x=True)
+    else:
+        case = _pair_case(kind)
+    phi0 = W.random_state((9, case.ny, case.nx), 1e-4, 8)
+    monkeypatch.setenv("T2S2_BLOCKS", "8")
+    ctx, g_single, *_ = _gpu_run(case, phi0, 10)
+    assert ctx.step_kernel(10) == "step_kernel"
+    monkeypatch.delenv("T2S2_BLOCKS")
+    for blocks in ("8", "24", "64"):
+        monkeypatch.setenv("T2S2_PAIR_BLOCKS", blocks)
+        ctx, g, d, u, v = _gpu_run(case, phi0, 10)
+        assert ctx.step_kernel(10) == "pair_step_kernel"
+        assert np.array_equal(g, g_single)
+    _compare(case, g, d, u, v, oracle.run(case, phi0, 10))
+
+
+@pytest.mark.parametrize("kind", ["channel", "cavity5"])
+@pytest.mark.parametrize("storage", ["f64", "f32", "bf16sr"])
+def test_tiles_on_the_smallest_meshes_are_bitwise_the_march(kind, storage, monkeypatch):
+    """Both tile shapes (T2S2_TILE) on meshes that one block takes otherwise."""
+    case = _mesh_case(kind)
+    phi0 = oracle.init(case) + W.random_state((9, case.ny, case.nx), 1e-5, 8)
+    monkeypatch.setenv("T2S2_BLOCKS", "8")
+    _, g_march, *_ = _gpu_run(case, phi0, 60, storage=storage)
+    monkeypatch.delenv("T2S2_BLOCKS")
+    for tile in ("1", "2"):
+        monkeypatch.setenv("T2S2_TILE", tile)
+        ctx, g, d, u, v = _gpu_run(case, phi0, 60, storage=storage)
+        assert ctx.step_kernel(60) == "tile_step_kernel"
+        assert np.array_equal(g, g_march)
+    if storage == "f64":
+        _compare(case, g, d, u, v, oracle.run(case, phi0, 60))
