@@ -147,9 +147,8 @@ size_t t2s2_workspace_bytes(const t2s2_ctx* ctx);
  * hook for checking that results do not depend on the tiling, and selects
  * the single-step march.  T2S2_PAIR_BLOCKS (main blocks of the kernel that
  * takes two steps per launch, forced also on small meshes) and T2S2_TILE
- * (0: the march, 1 and 2: tiles of one and of two rows per wave; each with one
- * launch per step where one block would take them all) are hooks of the same
- * kind. */
+ * (0: the march, 1 and 2: tiles of one and of two rows per wave; one launch
+ * per step, unless T2S2_PAIR_BLOCKS is set too) are hooks of the same kind. */
 int t2s2_bind(t2s2_ctx* ctx, void* state_a, void* state_b, void* workspace, void* stream);
 
 /* Name of the kernel that takes the steps of a t2s2_step call of nsteps steps

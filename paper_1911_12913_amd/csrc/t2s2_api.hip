@@ -794,7 +794,7 @@ int t2s2_bind(t2s2_ctx* c, void* state_a, void* state_b, void* workspace, void* 
       c->sp.tile && !single_steps && !two_steps ? plan_mesh(c->sp, c->cfg.storage) : 0;
   c->grid_pair = 0;
   if (c->cfg.storage == T2S2_F64 && c->sp.scheme == 1 && !c->sp.single &&
-      !std::getenv("T2S2_BLOCKS"))
+      !std::getenv("T2S2_BLOCKS") && (!single_steps || two_steps))
     c->grid_pair = plan_pair(c->sp, c->pair, cus);
   if (c->grid < 1 || c->grid_gen < 1) return fail(T2S2_ERR_HIP, "bind: step kernel cannot be resident");
   c->bound = true;

@@ -1158,6 +1158,17 @@ def test_two_step_kernel_runs_where_it_is_forced(kind, monkeypatch):
     _compare(case, g, d, u, v, oracle.run(case, phi0, 10))
 
 
+def test_tile_hook_keeps_single_steps(monkeypatch):
+    """T2S2_TILE=0 selects the march also where calls of four steps and more go
+    to the two-step kernel, unless T2S2_PAIR_BLOCKS asks for that."""
+    x, p = W.uniform_periodic(1400, 0.0, 1.0)
+    cfg = t2s2.make_config(nu=1e-3, cfl=0.5, period_x=p, period_y=p)
+    monkeypatch.setenv("T2S2_TILE", "0")
+    assert t2s2.Context(cfg, x, x).step_kernel(20) == "step_kernel"
+    monkeypatch.setenv("T2S2_PAIR_BLOCKS", "64")
+    assert t2s2.Context(cfg, x, x).step_kernel(20) == "pair_step_kernel"
+
+
 @pytest.mark.parametrize("kind", ["channel", "cavity5"])
 @pytest.mark.parametrize("storage", ["f64", "f32", "bf16sr"])
 def test_tiles_on_the_smallest_meshes_are_bitwise_the_march(kind, storage, monkeypatch):
