@@ -1185,3 +1185,37 @@ def test_tiles_on_the_smallest_meshes_are_bitwise_the_march(kind, storage, monke
         assert np.array_equal(g, g_march)
     if storage == "f64":
         _compare(case, g, d, u, v, oracle.run(case, phi0, 60))
+
+
+@pytest.mark.parametrize("kind,per_graph,kernel", [("mesh", 2, "mesh_steps_kernel"),
+                                                   ("mesh", 300, "mesh_steps_kernel"),
+                                                   ("pair", 10, "pair_step_kernel"),
+                                                   ("pair", 2, "step_kernel")])
+def test_graphs_of_multi_step_launches_are_plain_steps(kind, per_graph, kernel, monkeypatch):
+    """Captured graphs of launches that take several steps (one block, more of
+    them than one launch takes; two steps per launch with two single ones left),
+    replayed several times with plain steps and reads in between, odd counts
+    among them: bitwise plain stepping, in the same buffer."""
+    if kind == "pair":
+        case = _forced_channel(150, 70)
+        monkeypatch.setenv("T2S2_PAIR_BLOCKS", "24")
+        monkeypatch.setenv("T2S2_TILE", "0")
+    else:
+        case = W.poiseuille_case(dt_over_y1=0.9, eta=0.1)
+    phi0 = W.random_state((9, case.ny, case.nx), 1e-4, 8)
+    outs = []
+    for graph in (True, False):
+        stream = torch.cuda.Stream()
+        ctx = t2s2.context_for_case(case, stream=stream)
+        assert ctx.step_kernel(per_graph) == kernel
+        ctx.init_distributions(torch.from_numpy(phi0))
+        states = []
+        if graph:
+            ctx.graph_capture(per_graph)
+        for n in (2 * per_graph, 3, per_graph + 1, per_graph):
+            (ctx.graph_step if graph else ctx.step)(n)
+            states.append((ctx.read_distributions().cpu().numpy(), ctx.current, ctx.steps_taken))
+            ctx.step(1)
+        outs.append(states)
+    for a, b in zip(*outs):
+        assert np.array_equal(a[0], b[0]) and a[1:] == b[1:]
