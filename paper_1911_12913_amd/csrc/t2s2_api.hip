@@ -288,10 +288,23 @@ int plan_tile(const StepParams& sp, int storage, int cus) {
 
 // The two-step kernel takes meshes whose busiest block marches at least this
 // many rows (piece work included); on smaller ones the rows read again cost
-// more than the saved pass.  FP64, us per step, single steps / two-step:
-// Taylor-Green 1101^2 (50 rows) 52.1 / 54.7, 1400^2 (66) 79 / 56; cavity
-// 1025^2 (53) 55.1 / 52.6, 2049^2 (125) 151 / 117.
+// more than the saved pass (Taylor-Green 1101^2, 50 rows, 52.1 us per step by
+// single steps, 54.7).
 constexpr long long kPairMinWork = 52;
+// Beyond that, meshes where two single steps march at least this many times the
+// rows of a two-step launch, each counted for the busiest block of its split,
+// pieces included: what a row of the two-step march takes over one of the
+// single step's, in blocks half as wide and twice as many per CU, by walls and
+// force (a force costs the two-step march more, whose vector units are the
+// busier).  Of 217 meshes from 800 x 1800 to 4096^2 and 60 x 20000 that its
+// first rule took, none is slower by more than 0.3% than by single steps under
+// this one, and it leaves gains of at most 6.7%; that rule, kPairMinWork alone,
+// lost up to 33%.  us per step, single steps / two-step (ratio): Taylor-Green
+// 1200^2 57 / 43 (2.33), 1300^2 62 / 64 (1.50), 4096^2 495 / 343 (2.88); with a
+// force 300 x 4000 53 / 70 (1.38), 2500^2 221 / 192 (2.3); cavity 1200^2 61 / 65
+// (1.24), 2049^2 151 / 114 (2.12); forced channel 1300^2 69 / 82 (1.52), 2500^2
+// 224 / 200 (2.8).
+constexpr double kPairRows[2][2] = {{1.52, 1.95}, {1.385, 1.82}};  // [walls][force]
 
 // Steps of one launch of the one-block kernel: about a millisecond.
 constexpr int64_t kMeshSteps = 256;
@@ -323,10 +336,10 @@ int plan_mesh(const StepParams& sp, int storage) {
 
 // The two-step kernel's plan: the frame of a walled mesh and the main strips
 // and rows inside it, over one block per resident slot, so that a frame
-// piece and a main block's share take about the same time.  Returns the grid,
-// 0 if the mesh does not take the kernel.  T2S2_PAIR_BLOCKS=n forces it with n
-// main blocks (a hook for checking small meshes and ragged splits against
-// single steps).
+// piece and a main block's share take about the same time.  p holds the single
+// step's plan.  Returns the grid, 0 if the mesh does not take the kernel.
+// T2S2_PAIR_BLOCKS=n forces it with n main blocks (a hook for checking small
+// meshes and ragged splits against single steps).
 int plan_pair(const StepParams& p, PairPlan& plan, int cus) {
   const bool walls = !p.per_x || !p.per_y;
   const int per_cu = pair_blocks_per_cu(p.has_force != 0, walls);
@@ -376,7 +389,13 @@ int plan_pair(const StepParams& p, PairPlan& plan, int cus) {
     plan.band = 1;
     return forced ? plan.frame : 0;
   }
-  return plan.frame + set_blocks(plan, plan.rows, nb, forced != nullptr, kPairPieceWork);
+  const int grid = plan.frame + set_blocks(plan, plan.rows, nb, forced != nullptr, kPairPieceWork);
+  if (forced) return grid;
+  const long long rows2 =
+      busiest_block_work(plan.nunits, plan.rows, plan.nblocks, kPairPieceWork, LLONG_MAX);
+  const long long rows1 = busiest_block_work(p.nunits, p.ny, p.nblocks, kPieceWork, LLONG_MAX);
+  const double least = kPairRows[walls ? 1 : 0][p.has_force ? 1 : 0];
+  return 2.0 * static_cast<double>(rows1) >= least * static_cast<double>(rows2) ? grid : 0;
 }
 
 }  // namespace

@@ -1069,7 +1069,7 @@ def test_tile_shapes_are_bitwise_the_march(kind, storage, monkeypatch):
 
 @pytest.mark.parametrize("n,storage,A,steps,kernel", [
     (32, "f64", 0.5, 20, "mesh_steps_kernel"), (32, "f64", 0.5, 1, "tile_step_kernel"),
-    (200, "f64", 0.5, 20, "tile_step_kernel"), (1200, "f64", 0.5, 3, "step_kernel"),
+    (200, "f64", 0.5, 20, "tile_step_kernel"), (1300, "f64", 0.5, 20, "step_kernel"),
     (1400, "f64", 0.5, 4, "pair_step_kernel"), (1400, "f64", 0.5, 3, "step_kernel"),
     (1400, "f32", 0.5, 20, "step_kernel"), (64, "f64", 0.0, 20, "single_step_kernel")])
 def test_step_kernel_names_the_plan(n, storage, A, steps, kernel):
@@ -1219,3 +1219,24 @@ def test_graphs_of_multi_step_launches_are_plain_steps(kind, per_graph, kernel, 
         outs.append(states)
     for a, b in zip(*outs):
         assert np.array_equal(a[0], b[0]) and a[1:] == b[1:]
+
+
+@pytest.mark.parametrize("force,walls,nx,ny,two", [
+    (False, False, 1200, 1200, True), (False, False, 1300, 1300, False),
+    (True, False, 300, 4000, False), (True, False, 1821, 853, False),
+    (True, False, 2500, 2500, True), (False, True, 1200, 1200, False),
+    (False, True, 2049, 2049, True), (True, True, 1400, 1400, False),
+    (True, True, 3000, 2900, True)])
+def test_two_steps_per_launch_where_they_are_faster(force, walls, nx, ny, two):
+    """Large FP64 meshes go two steps per launch only where the busiest block's
+    rows say that it is faster: on these sizes measured up to 25% slower (False)
+    or at least 12% faster (True) than single steps."""
+    x, px = W.uniform_periodic(nx, 0.0, 1.0)
+    y, py = W.uniform_periodic(ny, 0.0, 1.0)
+    kw = dict(period_x=px, period_y=py)
+    if walls:
+        x, y = W.tanh_walled(nx - 1, 1.5), W.tanh_walled(ny - 1, 1.5)
+        kw = dict(periodic_x=False, periodic_y=False)
+    cfg = t2s2.make_config(nu=1e-3, cfl=0.5, force=(1e-4 if force else 0.0, 0.0), **kw)
+    ctx = t2s2.Context(cfg, x, y)
+    assert ctx.step_kernel(8) == ("pair_step_kernel" if two else "step_kernel")
