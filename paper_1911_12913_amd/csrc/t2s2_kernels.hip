@@ -476,11 +476,11 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, kScheme), (kMinWave
             if constexpr (gen_bbar) acc += v_now ? vnew[q] : vold[q];
             const int sy = ey_of(q) > 0 ? 0 : 1;
             if constexpr (kExact) {
-              // The rows ahead of the sum, or with a force each where it is
-              // added: 1.5 to 3% either way (family cavity 16 x 10 27.7 us per
-              // step, each where added 28.7; channel 1500 x 1400 88.0, ahead
-              // 89.6).
-              if constexpr (kForce) {
+              // Each row where it is added, or ahead of the sum for the family
+              // without a force (cavity 16 x 10 27.7 us per step, each where it is
+              // added 28.7; scheme 1, channel 1100^2 without a force 54.9, ahead
+              // 55.8, channel 1500 x 1400 88.0, ahead 89.6).
+              if constexpr (kForce || kScheme == 1) {
                 acc = full_taps(q, wxr, wyr, centre, acc, [&](int k) { return rb[k + sy][pq]; });
               } else {
                 Real rows[kTaps] = {};
