@@ -268,8 +268,10 @@ __global__ __launch_bounds__(64) void stability_kernel(StabArgs a, const double*
   const int mine = chunk < nk ? (nk - 1 - chunk) / nchunks + 1 : 0;  // modes of this chunk
   const int stride = mine % 7919 == 0 ? 7907 : 7919;  // prime to mine (< 2^17.1)
   double best = 0.0;  // over this block's modes
-  for (int first = 0; first < mine + 1; first += kModes) {
-    const int item = first + grp;  // item 0: |k| = 0, then the chunk's modes
+  // Item 0 is |k| = 0, then come the chunk's modes; without item 0 where one
+  // batch holds them all and nothing is left to compare with it.
+  for (int first = mine < kModes ? 1 : 0; first <= mine; first += kModes) {
+    const int item = first + grp;
     const bool active = item <= mine;
     // The chunk's modes in a scattered order, so that the first of them
     // already sample the whole grid for a large radius to compare with.
@@ -285,9 +287,12 @@ __global__ __launch_bounds__(64) void stability_kernel(StabArgs a, const double*
 
     Rows X, Y;
     if constexpr (kPaper) {
-      // One mode after the other, each by the whole wave.
+      // One mode after the other, each by the whole wave (only the groups that
+      // have one: with six modes, one squaring and 4000 points, 312 us where a wave
+      // takes every mode in turn, 801 with all 21 groups, 260 so).
       cplx* const sym = solve + 2 * kN2;
-      for (int g = 0; g < kModes; ++g) {
+      const int ngroups = min(kModes, mine + 1 - first);  // those with a mode
+      for (int g = 0; g < ngroups; ++g) {
         __syncthreads();
         if (grp == g && lane < 63) {
 #pragma unroll
@@ -301,7 +306,8 @@ __global__ __launch_bounds__(64) void stability_kernel(StabArgs a, const double*
 #pragma unroll
       for (int i = 0; i < kRowsPerLane; ++i) {
 #pragma unroll
-        for (int j = 0; j < kN; ++j) X[i][j] = mat[(row0 + i) * kN + j];
+        for (int j = 0; j < kN; ++j)
+          X[i][j] = active ? mat[(row0 + i) * kN + j] : cplx{0.0, 0.0};
       }
     } else {
       // (I - c rS) J to LDS, then J_R times it: cRs T + cRe Gamma T.

@@ -143,3 +143,33 @@ def test_stability_map_is_the_largest_norm_root(squarings, npoints, nk):
     assert lib.t2s2_stability_map(prm, w.data_ptr(), r.data_ptr(), npoints, w.data_ptr(),
                                   torch.cuda.current_stream().cuda_stream) == t2s2.OK
     assert np.array_equal(w.cpu().numpy(), got)
+
+
+def _largest_norm_root(model, omega, r, nk, full, squarings, **kw):
+    """max over the modes of ||G^m||_max^(1/m), m = 2^squarings, and ||G||_max of
+    the modes."""
+    thx = np.linspace(-math.pi, math.pi, 2 * nk - 1) if full else np.linspace(0.0, math.pi, nk)
+    G = np.stack([S.growth(model, a, b, omega, r, **kw)
+                  for a in thx for b in np.linspace(0.0, math.pi, nk)])
+    first, ell = np.abs(G).max(axis=(1, 2)), np.zeros(len(G))
+    for s in range(squarings + 1):
+        if s:
+            G, ell = G @ G, 2 * ell
+        n = np.abs(G).max(axis=(1, 2))
+        G, ell = G / n[:, None, None], ell + np.log(n)
+    return np.exp(ell / 2.0 ** squarings).max(), first
+
+
+@pytest.mark.parametrize("squarings", [1, 7])
+@pytest.mark.parametrize("nk,full", [(2, False), (2, True), (3, True), (4, True), (5, False)])
+def test_eq47_with_few_modes(nk, full, squarings):
+    """Eq 4.7 on grids of 4 to 28 modes, fewer and more than a batch holds.
+    Tolerance: the elimination's error, 9 eps times the condition of its matrix,
+    which stays below 1e4 here."""
+    rng = np.random.Generator(np.random.PCG64(7))
+    omegas, rs = rng.uniform(0.05, 8.0, 40), rng.uniform(0.05, 1.5, 40)
+    ref = [_largest_norm_root("paper", w, r, nk, full, squarings, eta=0.1, u=(0.1, -0.05),
+                              B2bar=0.5, B2tilde=0.25)[0] for w, r in zip(omegas, rs)]
+    got = t2s2.stability_map("paper", omegas, rs, nk=nk, full_kx=full, squarings=squarings,
+                             eta=0.1, u=(0.1, -0.05), b2bar=0.5, b2tilde=0.25).cpu().numpy()
+    assert np.abs(got / ref - 1).max() <= 1e-10
