@@ -444,9 +444,11 @@ __global__ __launch_bounds__(64) void stability_kernel(StabArgs a, const double*
       e += x;
       biggest = sqrt(m2) * down;
       // ln rho <= ln ||G^(2^s)||_F / 2^s, f2 rounded up to a power of two
-      // (f2 is that of the matrix before the scaling by 2^x).
+      // (f2 is that of the matrix before the scaling by 2^x); no bound where
+      // the sum of squares is not finite.
+      if (!(known > 0.0) || !isfinite(f2)) return;
       const double bound = (e - x + 0.5 * (ilogb(f2) + 1)) * 0.6931471805599453;
-      if (known > 0.0 && bound < ldexp(log_known - 1e-11, s)) dead = true;
+      if (bound < ldexp(log_known - 1e-11, s)) dead = true;
     };
     scale(0);
     for (int s = 1; s <= a.squarings; ++s) {

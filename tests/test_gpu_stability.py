@@ -173,3 +173,19 @@ def test_eq47_with_few_modes(nk, full, squarings):
     got = t2s2.stability_map("paper", omegas, rs, nk=nk, full_kx=full, squarings=squarings,
                              eta=0.1, u=(0.1, -0.05), b2bar=0.5, b2tilde=0.25).cpu().numpy()
     assert np.abs(got / ref - 1).max() <= 1e-10
+
+
+def test_modes_whose_norm_overflows_are_not_dropped():
+    """Growth matrices whose elements are finite but whose sum of squares is not
+    (r about 1e77, elements about 1e154) have no norm bound; they stay in the
+    maximum (1e-12 as above)."""
+    kw = dict(eta=0.1, u=(0.1, -0.05), A=0.5)
+    rs, ref = [], []
+    for x in np.linspace(76.75, 77.1, 80):
+        radius, norms = _largest_norm_root("fdlbm1", 1.0, 10.0 ** x, 9, True, 7, **kw)
+        if 4e153 < norms.max() < 1.3e154:
+            rs.append(10.0 ** x)
+            ref.append(radius)
+    assert len(rs) >= 20
+    got = t2s2.stability_map("fdlbm1", np.ones(len(rs)), rs, nk=9, squarings=7, **kw)
+    assert np.abs(got.cpu().numpy() / ref - 1).max() <= 1e-12
