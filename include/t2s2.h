@@ -318,8 +318,11 @@ int t2s2_step_save_s(t2s2_ctx* ctx, const void* src, void* dst, void* s_out);
 
 /* t2s2_adjoint_step without its recompute of the step: state_np1 and s_n
  * are dst and s_out of t2s2_step_save_s(ctx, state_n, ...).  Same outputs
- * as t2s2_adjoint_step (lam_n bitwise equal).  For a backward pass that has
- * stored each step's S as it recomputed its segment.  Asynchronous. */
+ * as t2s2_adjoint_step (lam_n bitwise equal).  lam_n must differ from lam_np1
+ * and s_n; it may be the buffer of state_n (as there) or share memory with
+ * state_np1, whose contents are then lost (on small walled meshes lam_n then
+ * equals t2s2_adjoint_step's to rounding).  For a backward pass that has stored
+ * each step's S as it recomputed its segment.  Asynchronous. */
 int t2s2_adjoint_step_stored(t2s2_ctx* ctx, const void* state_n, const void* state_np1,
                              const void* s_n, const void* lam_np1, void* lam_n,
                              double* dnu_accum);

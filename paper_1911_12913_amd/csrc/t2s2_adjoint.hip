@@ -1237,20 +1237,23 @@ hipError_t adjoint_reverse_t(const AdjParams& a, const void* state_n, const void
   const Real* mu = static_cast<const Real*>(lam_np1);
   const Store* g = static_cast<const Store*>(state_n);
   Real* lo = static_cast<Real*>(lam_n);
-  int blocks = a.march_grid;
   const int nstrips = (a.nx + kStripOut - 1) / kStripOut;
-  if (a.march_rows >= kAdjTiles) {
+  // The tiles of a walled domain read the new state around their outputs, while
+  // other tiles are stored: not where lam_n overwrites it.  The march reads it
+  // before, in adj_out_walls.
+  if (a.tile_rows > 0 && !(walls && overlaps<Store>(a, lam_n, a.next))) {
     const Store* nx = static_cast<const Store*>(a.next);
     auto go = [&](auto kernel, int waves) {
-      hipLaunchKernelGGL(kernel, dim3(blocks), dim3(waves * kLanes), 0, s, a, g, nx, mu, lo, partial);
+      hipLaunchKernelGGL(kernel, dim3(a.tile_grid), dim3(waves * kLanes), 0, s, a, g, nx, mu, lo,
+                         partial);
     };
     constexpr int kW1 = tile_waves<Store, false>(), kW2 = tile_waves<Store, true>();
-    if (a.march_rows == kAdjTiles)
+    if (a.tile_rows == 1)
       walls ? go(adj_tile<Store, true, kW1, 1>, kW1) : go(adj_tile<Store, false, kW1, 1>, kW1);
     else
       go(adj_tile<Store, true, kW2, 2>, kW2);
     if (accum)
-      hipLaunchKernelGGL(adj_accumulate, dim3(1), dim3(64), 0, s, partial, blocks,
+      hipLaunchKernelGGL(adj_accumulate, dim3(1), dim3(64), 0, s, partial, a.tile_grid,
                          a.dnu_per_domega, accum);
     return hipGetLastError();
   }
@@ -1265,8 +1268,8 @@ hipError_t adjoint_reverse_t(const AdjParams& a, const void* state_n, const void
   }
   StepParams::Coef<Real> ks = {};
   auto go = [&](auto kernel, int waves) {
-    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(waves * kLanes), 0, s, a, g, mu, muf, lo, partial,
-                       nstrips, ks);
+    hipLaunchKernelGGL(kernel, dim3(a.march_grid), dim3(waves * kLanes), 0, s, a, g, mu, muf, lo,
+                       partial, nstrips, ks);
   };
   const bool rows8 = a.march_rows == 8;
   if (form_s) {
@@ -1278,7 +1281,7 @@ hipError_t adjoint_reverse_t(const AdjParams& a, const void* state_n, const void
     walls ? go(adj_strip<Store, 4, true, false>, 4) : go(adj_strip<Store, 4, false, false>, 4);
   }
   if (accum)
-    hipLaunchKernelGGL(adj_accumulate, dim3(1), dim3(64), 0, s, partial, blocks,
+    hipLaunchKernelGGL(adj_accumulate, dim3(1), dim3(64), 0, s, partial, a.march_grid,
                        a.dnu_per_domega, accum);
   return hipGetLastError();
 }
@@ -1294,7 +1297,7 @@ hipError_t adjoint_step_t(int storage, const AdjParams& a, const StepParams& sp,
   // while others are stored, so where lam_n overwrites state_n the step is run
   // again first, and the march reads each node of state_n once, before it
   // stores that node (2048^2 FP64 550 us against 326).
-  if (a.march_rows < kAdjTiles && a.per_x && a.per_y && !overlaps<Store>(a, lam_n, state_n))
+  if (a.tile_rows == 0 && a.per_x && a.per_y && !overlaps<Store>(a, lam_n, state_n))
     return adjoint_reverse_t<Store>(a, state_n, lam_np1, lam_n, partial, accum, s, &sp);
   StepParams fwd = sp;
   fwd.src = state_n;
@@ -1346,21 +1349,23 @@ hipError_t plan_march_t(AdjParams& a, int cus) {
   const long long t1 = tiles(tile_out_rows<Store, false>()), t2 = tiles(tile_out_rows<Store, true>());
   a.march_rows = nstrips * a.ny < kAdjRows8Below * g4 ? 8 : 4;
   const int rounds = sizeof(typename Cvt<Store>::R) == 8 ? 4 : 3;
-  if (walls && t2 <= static_cast<long long>(rounds) * cus && t2 <= kAdjMaxBlocks)
-    a.march_rows = kAdjTiles + 1;
-  if (t1 <= cus) a.march_rows = kAdjTiles;
+  int tile = 0;
+  if (walls && t2 <= static_cast<long long>(rounds) * cus && t2 <= kAdjMaxBlocks) tile = 2;
+  if (t1 <= cus) tile = 1;
   // T2S2_ADJ_ROWS=4 or 8 forces the march and its block shape, 16 or 17 the
   // tiles where each has a partial (tests compare them).
   if (const char* env = std::getenv("T2S2_ADJ_ROWS")) {
     const int rows = std::atoi(env);
-    if (rows == 4 || rows == 8 || (rows == kAdjTiles && t1 <= kAdjMaxBlocks) ||
-        (rows == kAdjTiles + 1 && walls && t2 <= kAdjMaxBlocks))
+    if (rows == 4 || rows == 8) {
       a.march_rows = rows;
+      tile = 0;
+    }
+    if (rows == 16 && t1 <= kAdjMaxBlocks) tile = 1;
+    if (rows == 17 && walls && t2 <= kAdjMaxBlocks) tile = 2;
   }
-  a.march_grid = a.march_rows == kAdjTiles       ? static_cast<int>(t1)
-                 : a.march_rows == kAdjTiles + 1 ? static_cast<int>(t2)
-                 : a.march_rows == 8             ? grid(n8)
-                                                 : g4;
+  a.march_grid = a.march_rows == 8 ? grid(n8) : g4;
+  a.tile_rows = tile;
+  a.tile_grid = static_cast<int>(tile == 0 ? 0 : (tile == 1 ? t1 : t2));
   return hipSuccess;
 }
 

@@ -182,18 +182,20 @@ struct AdjParams {
   void* S;     // S, from the recompute of the step
   void* mu;    // adjoint of the interior output (= adjoint of Q); walled domains
   void* next;  // f~^{n+1} recomputed (storage type)
-  // Plan of the reverse stages (plan_adjoint_march): the march with blocks of
-  // four or eight waves, or tiles (kAdjTiles with one row per wave,
-  // kAdjTiles + 1 with two); and the block count (at most kAdjMaxBlocks).
+  // Plan of the reverse stages (plan_adjoint_march): the march's rows per
+  // iteration (blocks of four or eight waves) and block count (at most
+  // kAdjMaxBlocks); where tiles take them, rows per wave (1 or 2, else 0) and
+  // tile count.
   int march_rows;
   int march_grid;
+  int tile_rows;
+  int tile_grid;
 };
 
 constexpr int kDiagBlocks = 512;
 constexpr int kDiagSlots = 8;
 // Blocks of the reverse march of the adjoint (one d/d omega partial each).
 constexpr int kAdjMaxBlocks = 1024;
-constexpr int kAdjTiles = 16;
 
 // Launchers (t2s2_kernels.hip).  Return hipError_t of the launch.
 hipError_t launch_step(int storage, const StepParams& p, int grid, hipStream_t s);
@@ -238,8 +240,9 @@ hipError_t launch_copy_probe(const void* src, void* dst, long long plane, int el
 
 // Adjoint launchers (t2s2_adjoint.hip).
 size_t adjoint_real_bytes(int storage);
-// Sets a.march_rows8 and a.march_grid for this mesh, storage and device
-// (cus compute units): as many blocks as fit on the device at once.
+// Sets the march's and the tiles' plan in a for this mesh, storage and device
+// (cus compute units); the march takes as many blocks as fit on the device at
+// once.
 hipError_t plan_adjoint_march(int storage, AdjParams& a, int cus);
 hipError_t launch_adjoint_step(int storage, const AdjParams& a, const StepParams& sp,
                                int step_grid, const void* state_n, const void* lam_np1,

@@ -400,6 +400,41 @@ def test_adjoint_step_over_its_state(kind, storage, monkeypatch):
     assert outs[0][1] == outs[1][1]
 
 
+@pytest.mark.parametrize("storage", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("rows", ["8", "16", "17", None])
+def test_stored_adjoint_step_over_the_new_state(rows, storage, monkeypatch):
+    """t2s2_adjoint_step_stored with lam_n in the memory of state_np1, on a
+    cavity of many blocks, planned as tiles (which read state_np1 around their
+    outputs) and as the march: the lambda_n and dL/dnu of the call into a buffer
+    of its own, bitwise where the march takes both, else within the tolerances
+    of test_adjoint_tiles_are_the_march, since the march then stands in for the
+    tiles."""
+    eps = 2.2e-16 if storage == "f64" else 1.2e-7
+    case = W.cavity_case(230, lid=0.1, re=400.0, cfl=0.9, eta=0.1, noise=1e-3, seed=1)
+    if rows:
+        monkeypatch.setenv("T2S2_ADJ_ROWS", rows)
+    print(f"[gpu] stored adjoint step over the new state {rows} {storage}", flush=True)
+    ctx = t2s2.context_for_case(case, storage=storage)
+    ctx.enable_adjoint()
+    ctx.init_macro(case.rho0, case.ux0, case.uy0)
+    ctx.step(3)
+    state = ctx.save_state()
+    shared, s_n = ctx.adjoint_buffer(), ctx.adjoint_buffer()
+    nxt = shared[: state.numel()]
+    lam = ctx.adjoint_load(W.random_state((9, case.ny, case.nx), 1.0, 23))
+    outs = []
+    for out in (ctx.adjoint_buffer(), shared):
+        ctx.step_save_s(state, nxt, s_n)
+        acc = torch.zeros(1, dtype=torch.float64, device="cuda:0")
+        ctx.adjoint_step_stored(state, nxt, s_n, lam, out, acc)
+        outs.append((ctx.adjoint_read(out).cpu().numpy(), float(acc.item())))
+    ctx.close()
+    if rows == "8":
+        assert np.array_equal(outs[0][0], outs[1][0]) and outs[0][1] == outs[1][1]
+    assert np.abs(outs[0][0] - outs[1][0]).max() <= 100 * eps * np.abs(outs[0][0]).max()
+    assert abs(outs[0][1] - outs[1][1]) <= 1e5 * eps * abs(outs[0][1])
+
+
 @pytest.mark.parametrize("storage", ["f64", "f32"])
 def test_rollout_backward_with_stored_steps(storage):
     """The rollout's two backward passes (steps and S kept per segment, or
