@@ -255,35 +255,70 @@ constexpr long long kPairPieceWork = 25;
 // (Cavity 2049^2: 115.9 us per step at 1.5 / 1.5, 116.2 at 2 / 2, 118.4 at
 // 3 / 2.5; 4097^2: 375.8 at 2 / 1.5, 381.7 at 3 / 2.)
 constexpr double kPairEdgeCost = 2.0, kPairTopCost = 1.5;
+// Estimated us of a step by the march, W unit-rows (pieces included) in the
+// busiest of nb blocks per CU, march[0] + W (march[1] + march[2] nb); by n
+// one-row tiles per CU (two at a time), one[0] + one[1] n + one[2] ceil(n / 2);
+// and by n two-row tiles per CU, two[0] + two[1] n + two[2] ceil(n).
+struct StepTimes {
+  double march[3], one[3], two[3];
+};
+// Fitted by walls and force to 900 measured cases of 2 to 12 one-row tiles per
+// CU, with sides up to 1 : 13 (residuals 3 to 6%, two-row tiles of the narrower
+// forms with walls 5 to 9%).
+constexpr StepTimes kTimes64[2][2] = {  // [walls][force]
+    {{{8.53, 0.39, 0.21}, {1.96, 5.36, 2.65}, {0.34, 3.10, 7.47}},
+     {{7.49, 0.86, 0.04}, {1.98, 5.79, 2.66}, {0.30, 3.05, 8.00}}},
+    {{{11.22, 0.37, 0.24}, {5.08, 5.53, 1.89}, {3.80, 3.95, 6.14}},
+     {{12.39, 0.56, 0.19}, {4.71, 5.59, 2.60}, {2.94, 3.67, 7.25}}}};
+constexpr StepTimes kTimes32[2][2] = {
+    {{{9.32, 0.13, 0.34}, {4.84, 2.19, 1.18}, {3.51, 4.95, 3.52}},
+     {{8.68, 0.40, 0.20}, {6.21, 2.51, 0.81}, {3.33, 5.49, 4.27}}},
+    {{{8.60, 0.33, 0.29}, {6.61, 2.02, 0.88}, {4.01, 4.16, 4.25}},
+     {{10.28, 0.45, 0.16}, {7.15, 2.64, 0.39}, {3.81, 4.71, 4.86}}}};
+constexpr StepTimes kTimes16[2][2] = {
+    {{{8.69, 0.23, 0.14}, {5.96, 1.51, 1.34}, {5.44, 2.47, 4.03}},
+     {{8.00, 0.27, 0.17}, {6.33, 1.32, 2.27}, {4.95, 1.03, 6.34}}},
+    {{{9.51, 0.32, 0.13}, {7.15, 1.35, 1.42}, {5.24, 2.37, 4.43}},
+     {{9.78, 0.37, 0.14}, {6.97, 1.63, 1.64}, {6.44, 2.05, 5.34}}}};
+
 // Which kernel takes single steps of scheme 1 with A > 0: the march (0) or
-// tiles of one row per wave (1) or two (2), by the rounds of tiles the CUs
-// take.  A CU holds one tile of either shape in FP64, two one-row tiles or one
-// two-row tile in the narrower forms; the two-row tiles spend less on halo
-// rows, but fewer of them may leave CUs idle.  Measured, us per step (march /
-// one row / two rows):
-//   FP64 one-row tiles while each CU gets at most one: cavity 321^2
-//     - / 10.6 / 12.4, 385^2 - / 16.1 / 12.9; then two-row tiles up to four per
-//     CU with walls (897^2 45.1 / 54.9 / 42.1), two per CU on periodic grids
-//     (640^2 21.1 / 25.5 / 19.5, 768^2 28.2 / 37.3 / 28.8);
-//   narrower forms: one-row tiles up to twelve per CU (bf16 with stochastic
-//     rounding, cavity 1153^2 39.0 / 32.3 / 33.7, 1300^2 42.1 / 41.3 / 42.8),
-//     six in FP32 on periodic grids (768^2 18.5 / 18.1 / 16.8, 896^2
-//     21.0 / 22.0 / 26.5); two-row tiles where they alone take one round
-//     (FP32 cavity 513^2 21.6 / 13.4 / 12.5), but not the 16-bit forms on
-//     periodic grids (512^2 19.3 / 10.8 / 11.7).
+// tiles of one row per wave (1) or two (2).  A CU holds one tile of either shape
+// in FP64, two one-row tiles or one two-row tile in the narrower forms; the
+// two-row tiles spend less on halo rows, but fewer of them may leave CUs idle.
+// One-row tiles while each CU gets at most one (FP64 cavity 321^2 10.6 / 12.4
+// us, one row / two), two in the narrower forms; FP64 then two-row tiles while
+// they take about one round (385^2 16.1 / 12.9), the narrower forms while they
+// take one (FP32 cavity 470^2 13.6 / 12.4); beyond, up to twelve one-row tiles
+// per CU, the least estimate, the march's counted 2 to 5% less: of those 900
+// cases 14 are then more than 1% slower than the march, and the choice is 0.9%
+// above the best on average.  By counts of tiles alone FP32 on periodic grids
+// took the march from six tiles per CU (879 x 883 27.0 us per step, 24.6 by
+// tiles), and FP64 with walls two-row tiles up to four (channel 848 x 840 42.8,
+// 36.1 by the march).  sp holds the march's plan.
 int plan_tile(const StepParams& sp, int storage, int cus) {
-  const bool walls = !sp.per_x || !sp.per_y;
-  auto tiles = [&](int kind) {
+  const int walls = !sp.per_x || !sp.per_y ? 1 : 0, force = sp.has_force ? 1 : 0;
+  auto per_cu = [&](int kind) {
     const int rows = step_tile_rows(storage, kind);
-    return static_cast<long long>(sp.nstrips) * ((sp.ny + rows - 1) / rows);
+    return static_cast<double>(sp.nstrips) * ((sp.ny + rows - 1) / rows) / cus;
   };
-  const long long t1 = tiles(1), t2 = tiles(2);
-  if (storage == kF64) {
-    if (t1 <= cus) return 1;
-    return t2 <= (walls ? 4LL : 2LL) * cus ? 2 : 0;
-  }
-  if (t1 > 2LL * cus && t2 <= cus && (walls || storage == kF32)) return 2;
-  return t1 <= (walls || storage != kF32 ? 12LL : 6LL) * cus ? 1 : 0;
+  const double n1 = per_cu(1), n2 = per_cu(2);
+  const bool fp64 = storage == kF64;
+  if (n1 <= 1.0) return 1;
+  if (!fp64 && n1 <= 2.01) return 1;
+  if (n2 <= (fp64 ? 1.1 : 1.0)) return 2;
+  if (n1 > 12.0) return 0;
+  const StepTimes& t = fp64              ? kTimes64[walls][force]
+                       : storage == kF32 ? kTimes32[walls][force]
+                                         : kTimes16[walls][force];
+  const double w = static_cast<double>(
+      busiest_block_work(sp.nunits, sp.ny, sp.nblocks, kPieceWork, LLONG_MAX));
+  const double less = fp64 ? 0.98 : (storage == kF32 ? 0.95 : 0.97);
+  const double march =
+      less * (t.march[0] + w * (t.march[1] + t.march[2] * static_cast<double>(sp.nblocks) / cus));
+  const double one = t.one[0] + t.one[1] * n1 + t.one[2] * std::ceil(n1 / 2);
+  const double two = t.two[0] + t.two[1] * n2 + t.two[2] * std::ceil(n2);
+  if (march <= std::min(one, two)) return 0;
+  return one <= two ? 1 : 2;
 }
 
 // The two-step kernel takes meshes whose busiest block marches at least this

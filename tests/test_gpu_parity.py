@@ -1240,3 +1240,20 @@ def test_two_steps_per_launch_where_they_are_faster(force, walls, nx, ny, two):
     cfg = t2s2.make_config(nu=1e-3, cfl=0.5, force=(1e-4 if force else 0.0, 0.0), **kw)
     ctx = t2s2.Context(cfg, x, y)
     assert ctx.step_kernel(8) == ("pair_step_kernel" if two else "step_kernel")
+
+
+@pytest.mark.parametrize("storage,channel,nx,ny,kernel", [
+    ("f32", False, 879, 883, "tile_step_kernel"), ("f32", False, 2317, 337, "tile_step_kernel"),
+    ("f64", True, 848, 840, "step_kernel"), ("f64", True, 641, 641, "tile_step_kernel"),
+    ("f64", False, 300, 300, "tile_step_kernel")])
+def test_single_steps_by_the_faster_kernel(storage, channel, nx, ny, kernel):
+    """Tiles or the march by their estimated time: sizes where a count of tiles
+    alone took the one that is 9 to 18% slower, and two where it did not."""
+    x, px = W.uniform_periodic(nx, 0.0, 1.0)
+    y, py = W.uniform_periodic(ny, 0.0, 1.0)
+    kw = dict(period_x=px, period_y=py)
+    if channel:
+        y = W.tanh_walled(ny - 1, 1.5)
+        kw = dict(period_x=px, periodic_y=False, force=(1e-4, 0.0))
+    ctx = t2s2.Context(t2s2.make_config(nu=1e-3, cfl=0.5, storage=storage, **kw), x, y)
+    assert ctx.step_kernel(1) == kernel
