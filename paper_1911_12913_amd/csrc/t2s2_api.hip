@@ -292,7 +292,7 @@ constexpr StepTimes kTimes16[2][2] = {
 // per CU, the least estimate, the march's counted 2 to 5% less: of those 900
 // cases 14 are then more than 1% slower than the march, and the choice is 0.9%
 // above the best on average.  By counts of tiles alone FP32 on periodic grids
-// took the march from six tiles per CU (879 x 883 27.0 us per step, 24.6 by
+// took the march from six tiles per CU (879 x 883 26.9 us per step, 22.8 by
 // tiles), and FP64 with walls two-row tiles up to four (channel 848 x 840 42.8,
 // 36.1 by the march).  sp holds the march's plan.
 int plan_tile(const StepParams& sp, int storage, int cus) {
@@ -316,7 +316,9 @@ int plan_tile(const StepParams& sp, int storage, int cus) {
   const double march =
       less * (t.march[0] + w * (t.march[1] + t.march[2] * static_cast<double>(sp.nblocks) / cus));
   const double one = t.one[0] + t.one[1] * n1 + t.one[2] * std::ceil(n1 / 2);
-  const double two = t.two[0] + t.two[1] * n2 + t.two[2] * std::ceil(n2);
+  // (Two-row tiles that also store S cost the narrower forms more.)
+  const double two =
+      (fp64 ? 1.0 : 1.03) * (t.two[0] + t.two[1] * n2 + t.two[2] * std::ceil(n2));
   if (march <= std::min(one, two)) return 0;
   return one <= two ? 1 : 2;
 }
