@@ -300,12 +300,11 @@ constexpr int adj_waves_per_simd() {
   return kWalls ? (f32 && kRows == 4 ? 3 : 2) : (f32 ? 4 : 2);
 }
 
-//
 // kFormS (periodic grids): S is formed in the march from P = P(g), which a
 // second LDS ring holds for rows p0-2 .. p0+kRows+1 while phase A runs; phase B
 // forms the P of the next iteration's rows.  The step need not be run again
 // then, nor S written and read: 216 bytes per node in FP64 where the two
-// kernels move 504.  S is as step_kernel forms it. 
+// kernels move 504.  S is as step_kernel forms it.
 // An adjoint step, us: periodic FP64 2048^2 550 -> 326, 4096^2 2264 -> 1256,
 // 800^2 103 -> 76; FP32 2048^2 359 -> 216.
 template <typename Store, int kRows, bool kWalls, bool kFormS>
@@ -451,7 +450,8 @@ __global__ __launch_bounds__(kLanes * kRows, (adj_waves_per_simd<Store, kRows, k
       if constexpr (!kFormS) load_planes(S, pbr, rb, a_sv);
     };
     auto issue_p = [&](int row, Store (&gs)[kQ]) {
-      const unsigned off = static_cast<unsigned>(static_cast<long long>(wrap(row, ny)) * a.pitch + c);
+      const unsigned off =
+          static_cast<unsigned>(static_cast<long long>(wrap(row, ny)) * a.pitch + c);
       load_planes(g, pbs, off * static_cast<unsigned>(sizeof(Store)), gs);
     };
     auto form_p = [&](int row, const Store (&gs)[kQ]) {
@@ -1346,7 +1346,8 @@ hipError_t plan_march_t(AdjParams& a, int cus) {
   const int g4 = grid(n4);
   const long long nstrips = (a.nx + kStripOut - 1) / kStripOut;
   auto tiles = [&](int rows) { return nstrips * ((a.ny + rows - 1) / rows); };
-  const long long t1 = tiles(tile_out_rows<Store, false>()), t2 = tiles(tile_out_rows<Store, true>());
+  const long long t1 = tiles(tile_out_rows<Store, false>());
+  const long long t2 = tiles(tile_out_rows<Store, true>());
   a.march_rows = nstrips * a.ny < kAdjRows8Below * g4 ? 8 : 4;
   const int rounds = sizeof(typename Cvt<Store>::R) == 8 ? 4 : 3;
   int tile = 0;

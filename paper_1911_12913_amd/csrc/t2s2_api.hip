@@ -58,7 +58,8 @@ std::vector<double> scatter_weights(const std::vector<double>& w, int n, bool pe
   std::vector<double> t(static_cast<size_t>(n) * 16, 0.0);
   for (int r = 0; r < n; ++r) {
     double* o = &t[static_cast<size_t>(r) * 16];
-    for (int k = 0; k < kWeightsPerNode; ++k) o[k] = w[static_cast<size_t>(r) * kWeightsPerNode + k];
+    for (int k = 0; k < kWeightsPerNode; ++k)
+      o[k] = w[static_cast<size_t>(r) * kWeightsPerNode + k];
     for (int s = 0; s < 2; ++s)
       for (int k = 0; k < kTaps; ++k) {
         int i = r - (s == 0 ? k - 2 : k - 1);  // the output whose tap k is row r
@@ -190,9 +191,9 @@ long long busiest_block_work(long long nunits, int ny, long long nb, long long p
   return worst;
 }
 
-// Sets p's split of nunits x ny unit-rows to about nb blocks (a multiple of 8; unless forced, fewer
-// where that makes the busiest block's work at least 3% less) and returns
-// the block count.
+// Sets p's split of nunits x ny unit-rows to about nb blocks (a multiple of 8;
+// unless forced, fewer where that makes the busiest block's work at least 3%
+// less) and returns the block count.
 template <typename Plan>  // StepParams or PairPlan
 int set_blocks(Plan& p, int ny, long long nb, bool forced, long long piece_work) {
   const long long rows = static_cast<long long>(p.nunits) * ny;

@@ -27,7 +27,7 @@ __host__ __device__ constexpr double w_of(int q) {
 // round a node's values the same way (of a sum of two products the compiler may
 // fuse either).  Otherwise left to the compiler, which fuses FP32 products
 // alike in most kernels of the reduced forms but not in all: see moments_f32
-// and the exceptions that t2s2_bind makes.
+// and plan_mesh.
 template <bool kExact = true>
 __device__ inline double fma_of(double a, double b, double c) {
   if constexpr (kExact) return __builtin_fma(a, b, c);
@@ -150,13 +150,14 @@ __device__ inline unsigned mix32(unsigned x) {
 // x_down), so the stored value is x on average and increments smaller than
 // half a unit in the last place are kept on average instead of lost, as
 // they are under rounding to nearest.  The random bits come from a counter
-// generator that needs no step counter: mix32 of the node's position (pos) and of the nine values'
-// FP32 bits, then a linear congruential sequence (multiplier 1664525,
-// increment 1013904223, on the low 24 bits of the state) whose upper 16
-// bits serve one value each.  They depend only on the node and the values,
-// so results do not depend on the launch's tiling, graph replays give the
-// values of plain launches, and a state that does not change rounds the
-// same way again.  BF16: add 16 random bits to the FP32 bits and cut them;
+// generator that needs no step counter: mix32 of the node's position (pos) and
+// of the nine values' FP32 bits, then a linear congruential sequence
+// (multiplier 1664525, increment 1013904223, on the low 24 bits of the state)
+// whose upper 16 bits serve one value each.  They depend only on the node and
+// the values: the same values round the same way under any tiling (on periodic
+// grids with a force the FP32 values themselves may differ in the last bit
+// between kernels), graph replays give the values of plain launches, and a state
+// that does not change rounds the same way again.  BF16: add 16 random bits to the FP32 bits and cut them;
 // FP16: the same with 13 bits on 2^14 x, then an exact conversion (in the
 // normal FP16 range; below it, 2^14 |x| < 6.1e-5, the conversion rounds to
 // nearest).  Non-finite values keep their class (canonical NaNs, Inf).

@@ -324,7 +324,8 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, kScheme), (kMinWave
               if (ey_of(q) != 0) {
                 const int sy = ey_of(q) > 0 ? 0 : 1;
 #pragma unroll
-                for (int k2 = 0; k2 < kTaps; ++k2) acc = fma_of<kExact>(wyr[sy * kTaps + k2], rb[k2 + sy][pq], acc);
+                for (int k2 = 0; k2 < kTaps; ++k2)
+                  acc = fma_of<kExact>(wyr[sy * kTaps + k2], rb[k2 + sy][pq], acc);
               }
               S[q] = q == 0 ? centre : fma_of<kExact>(fac, acc, centre);
             }
@@ -342,7 +343,8 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, kScheme), (kMinWave
             for (int q = 1; q < kQ; ++q) {
               const Real E = fma_of<kExact>(rho, X[q], d);
               Real Rq = fma_of<kExact>(cs, S[q], ke[wclass(q)] * E);
-              if (kForce) Rq = fma_of<kExact>(static_cast<Real>(cf), force_term<kExact>(q, p, ux, uy, E), Rq);
+              if (kForce)
+                Rq = fma_of<kExact>(static_cast<Real>(cf), force_term<kExact>(q, p, ux, uy, E), Rq);
               R[q] = Rq;
             }
             if (want_v) {
@@ -427,7 +429,8 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, kScheme), (kMinWave
                       const Real wall1 = nee_r(wclass(q) == 1 ? r1 : r2, X[q], Xb[q], R[q]);
                       const Real wall2 =
                           kFamily ? nee_r(wclass(q) == 1 ? r1b : r2b, X2[q], Xb[q], R2[q]) : R2[q];
-                      slotW[(q - 1) * kLanes + lane + dx] = t_of(q, r + dy, lane + dx, wall1, wall2);
+                      slotW[(q - 1) * kLanes + lane + dx] =
+                          t_of(q, r + dy, lane + dx, wall1, wall2);
                     }
                   } else {
                     Real sh[kQ], sh2[kQ];
@@ -520,7 +523,8 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, kScheme), (kMinWave
             for (int q = 0; q < kQ; ++q) {
               const Real E = fma_of<kExact>(rho, X[q], d);
               Real o = k.aY * out[q] + k.kA[wclass(q)] * E;
-              if (kForce) o = fma_of<kExact>(static_cast<Real>(p.aF), force_term<kExact>(q, p, ux, uy, E), o);
+              if (kForce)
+                o = fma_of<kExact>(static_cast<Real>(p.aF), force_term<kExact>(q, p, ux, uy, E), o);
               out[q] = o;
             }
           }
@@ -615,7 +619,8 @@ __device__ inline void moments_f32(double s, double jx, double jy, float& r, flo
 }
 
 template <typename Store, bool kForce, bool kWalls, bool kSaveS, int kH>
-__global__ __launch_bounds__((tile_waves<Store, kH>() * kLanes)) void tile_step_kernel(StepParams p) {
+__global__ __launch_bounds__((tile_waves<Store, kH>() * kLanes)) void tile_step_kernel(
+    StepParams p) {
   using Real = typename Cvt<Store>::R;
   constexpr int kWaves = tile_waves<Store, kH>();
   constexpr int kIn = kWaves * kH;   // rows of P

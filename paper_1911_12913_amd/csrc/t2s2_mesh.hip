@@ -200,7 +200,9 @@ __global__ __launch_bounds__(kNodes) void mesh_steps_kernel(StepParams p, int ns
         }
         out[q] = full_taps_of(
             q, wy, Q[q], [&](int k2) { return rows[k2]; },
-            [&](Real acc) { return x_taps_at(ex_of(q), wx, R[q], acc, [&](int o) { return x[o + 2]; }); });
+            [&](Real acc) {
+              return x_taps_at(ex_of(q), wx, R[q], acc, [&](int o) { return x[o + 2]; });
+            });
       }
       if constexpr (kStochastic<Store>) {
         round_node_sr(out, boff, gs);

@@ -39,11 +39,10 @@ constexpr int kPairHalo = 2 * kHalo;
 constexpr int kPairWaves = 2;
 constexpr int kHandRows = 8;  // rows of the ring between the two waves
 
-// What a wave carries from row to row: P of the rows p-1 .. p-4 and the
-// output rows p-1 .. p-4 under way, by row number modulo 4.
-using Real64 = double;
 typedef unsigned U32x2 __attribute__((ext_vector_type(2)));
 constexpr int kNonTemporal = 2;  // buffer instruction cache policy: nt
+// What a wave carries from row to row: P of the rows p-1 .. p-4 and the
+// output rows p-1 .. p-4 under way, by row number modulo 4.
 template <typename Real>
 struct Stage {
   Real P[kQ][4];
@@ -200,7 +199,8 @@ __device__ __forceinline__ void stage_row(const StepParams& p0, const double* wy
         R = wl.c == wl.last ? v : R;
       }
       if (wall_row && bottom) {
-        const Real Rw = (wl.c == 0 && wl.has_l) || (wl.c == wl.last && wl.has_r) ? R : nee_r(wr, X[q], xw[q], R);
+        const bool corner = (wl.c == 0 && wl.has_l) || (wl.c == wl.last && wl.has_r);
+        const Real Rw = corner ? R : nee_r(wr, X[q], xw[q], R);
         if (ey_of(q) > 0) {
           st.acc[q][i1] = fma_of(wb[8], Rw, st.acc[q][i1]);
           st.acc[q][i2] = fma_of(wb[9], Rw, st.acc[q][i2]);
@@ -224,7 +224,8 @@ __device__ __forceinline__ void stage_row(const StepParams& p0, const double* wy
       }
       st.acc[q][i2] = mid;
       if (wall_row && !bottom) {
-        const Real Rw = (wl.c == 0 && wl.has_l) || (wl.c == wl.last && wl.has_r) ? R : nee_r(wr, X[q], xw[q], R);
+        const bool corner = (wl.c == 0 && wl.has_l) || (wl.c == wl.last && wl.has_r);
+        const Real Rw = corner ? R : nee_r(wr, X[q], xw[q], R);
         if (ey_of(q) > 0) {
           st.acc[q][i2] = fma_of(wb[11], Rw, st.acc[q][i2]);
         } else if (ey_of(q) < 0) {
@@ -262,8 +263,8 @@ __device__ __forceinline__ void stage_row(const StepParams& p0, const double* wy
 // p - 1): never a slot of the eight that A writes.  kWalls: the piece may
 // reach wall nodes, or nodes next to a wall.
 template <bool kForce, bool kWalls>
-__device__ __forceinline__ void march_piece(const StepParams& p, const double* wy16, double* hand, int lane, int role,
-                                            int x0, int x1, int y0, int y1) {
+__device__ __forceinline__ void march_piece(const StepParams& p, const double* wy16, double* hand,
+                                            int lane, int role, int x0, int x1, int y0, int y1) {
   using Real = double;
   const int nx = p.nx, ny = p.ny;
   const bool per_x = !kWalls || p.per_x, per_y = !kWalls || p.per_y;
@@ -422,15 +423,15 @@ __device__ __forceinline__ void march_piece(const StepParams& p, const double* w
 }
 
 // Main pieces: work order and XCD-aware block map as in step_kernel, over
-// the strips of kPairOut columns from pair_x0 and the rows from pair_y0.
+// the strips of kPairOut columns from plan.x0 and the rows from plan.y0.
 // With walls (kFrame) these stay 8 nodes clear of them, and run the code
 // without wall paths; the frame around them (the strips along the x walls,
-// the rows along the y walls) goes to the grid's first pair_frame blocks, one
+// the rows along the y walls) goes to the grid's first plan.frame blocks, one
 // piece each, whose pieces are shorter because the wall paths are slower
 // (hundreds of scalar spills; in the main march they would slow every row).
 template <bool kForce, bool kFrame>
 __global__ __launch_bounds__(kPairWaves * kLanes, 2) void pair_step_kernel(StepParams p,
-                                                                               PairPlan plan) {
+                                                                           PairPlan plan) {
   __shared__ double hand[kHandRows * kQ * kLanes];  // [slot][q][lane]
   const int lane = threadIdx.x & (kLanes - 1);
   const int role = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
@@ -483,8 +484,8 @@ __global__ __launch_bounds__(kPairWaves * kLanes, 2) void pair_step_kernel(StepP
     const int y1 = static_cast<int>(min(static_cast<long long>(r0 + hb), y0 + (end - beg)));
     beg += y1 - y0;
     const int x0 = plan.x0 + strip * kPairOut;
-    march_piece<kForce, false>(p, plan.wy16, hand, lane, role, x0, min(x0 + kPairOut, p.nx), plan.y0 + y0,
-                               plan.y0 + y1);
+    march_piece<kForce, false>(p, plan.wy16, hand, lane, role, x0, min(x0 + kPairOut, p.nx),
+                               plan.y0 + y0, plan.y0 + y1);
   }
 }
 

@@ -300,7 +300,8 @@ __global__ __launch_bounds__(64) void stability_kernel(StabArgs a, const double*
         }
         __syncthreads();
         solve_paper(a, lane, gam, sym, w, r, solve, solve + kN2);
-        for_elems(lane, [&](int i, int j) { mats[g * kN2 + i * kN + j] = solve[kN2 + i * kN + j]; });
+        for_elems(lane,
+                  [&](int i, int j) { mats[g * kN2 + i * kN + j] = solve[kN2 + i * kN + j]; });
       }
       __syncthreads();
 #pragma unroll
