@@ -55,15 +55,11 @@ extern "C" {
  * step rounds the new interior values it stores stochastically (up in
  * magnitude with probability equal to the fraction of the unit in the last
  * place cut off; random bits from a hash of the node's position and new
- * values, so results do not depend on the launch tiling, as far as the FP32
- * arithmetic does not, and are reproducible): increments below half a unit in
- * the last place, lost
- * under rounding to nearest, are kept on average.  Initialisation and wall
- * nodes round to nearest.  (On periodic meshes with a force the kernels that a
- * mesh's size selects may fuse an FP32 product differently, a difference in the
- * last bit of the reduced forms' arithmetic; everywhere else they agree bit for
- * bit, and FP64 does on every mesh.)  The stochastic forms run T2S2_FDLBM1 (any A)
- * only, without the adjoint.  The calls that take or return FP64 fields and
+ * values, so results do not depend on the launch tiling and are reproducible):
+ * increments below half a unit in the last place, lost under rounding to
+ * nearest, are kept on average.  Initialisation and wall nodes round to
+ * nearest.  The stochastic forms run T2S2_FDLBM1 (any A) only, without the
+ * adjoint.  The calls that take or return FP64 fields and
  * distributions convert to and from g. */
 #define T2S2_F64 0
 #define T2S2_F32_DEV 1

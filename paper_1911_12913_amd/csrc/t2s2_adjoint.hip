@@ -101,7 +101,7 @@ template <typename V, typename T>
 __device__ inline void node_rho_u(const V v[kQ], T& d, T& rho, T& ux, T& uy) {
   double s, jx, jy;
   moment_sums(v, s, jx, jy);
-  velocity(s, jx, jy, rho, ux, uy);
+  velocity<kExactOf<T, false>>(s, jx, jy, rho, ux, uy);
   d = static_cast<T>(s);
 }
 
@@ -316,6 +316,7 @@ __global__ __launch_bounds__(kLanes * kRows, (adj_waves_per_simd<Store, kRows, k
                                                  StepParams::Coef<typename Cvt<Store>::R> ks) {
   static_assert(!(kWalls && kFormS), "S is formed in the march on periodic grids only");
   using Real = typename Cvt<Store>::R;
+  constexpr bool kExact = kExactOf<Real, false>;
   constexpr int kThreads = kLanes * kRows;
   constexpr int kSlots = 2 * kRows;  // rows p0-4 .. p0+kRows-1 in use, a power of two
   __shared__ Real ring[kSlots * kQ * kLanes];  // lamS: [slot][q][lane]
@@ -461,13 +462,14 @@ __global__ __launch_bounds__(kLanes * kRows, (adj_waves_per_simd<Store, kRows, k
       double s, jx, jy;
       moment_sums(v, s, jx, jy);
       Real rho, ux, uy;
-      velocity(s, jx, jy, rho, ux, uy);
+      velocity<kExact>(s, jx, jy, rho, ux, uy);
       const Real d = static_cast<Real>(s);
-      eq_brackets(ux, uy, X);
+      eq_brackets<kExact>(ux, uy, X);
       Real* slot = ringP + (row & (kSlots - 1)) * kQ * kLanes + lane;
 #pragma unroll
       for (int q = 0; q < kQ; ++q)
-        slot[q * kLanes] = fma_of(ks.cPg, v[q], ks.kP[wclass(q)] * fma_of(rho, X[q], d));
+        slot[q * kLanes] =
+            fma_of<kExact>(ks.cPg, v[q], ks.kP[wclass(q)] * fma_of<kExact>(rho, X[q], d));
     };
     auto issue_b = [&](int o0) {
       const int o = wrap(o0, ny);
@@ -543,15 +545,15 @@ __global__ __launch_bounds__(kLanes * kRows, (adj_waves_per_simd<Store, kRows, k
                 const int pq = q * kLanes;
                 const Real centre = rb[2][pq];
                 Real acc = Real(0);
-                if (ex_of(q) > 0) acc = x_taps<0>(wx, centre, acc);
-                if (ex_of(q) < 0) acc = x_taps<1>(wx, centre, acc);
+                if (ex_of(q) > 0) acc = x_taps<0, kExact>(wx, centre, acc);
+                if (ex_of(q) < 0) acc = x_taps<1, kExact>(wx, centre, acc);
                 if (ey_of(q) != 0) {
                   const int sy = ey_of(q) > 0 ? 0 : 1;
 #pragma unroll
                   for (int k = 0; k < kTaps; ++k)
-                    acc = fma_of(wyr[sy * kTaps + k], rb[k + sy][pq], acc);
+                    acc = fma_of<kExact>(wyr[sy * kTaps + k], rb[k + sy][pq], acc);
                 }
-                sv[q] = q == 0 ? centre : fma_of(ks.A, acc, centre);
+                sv[q] = q == 0 ? centre : fma_of<kExact>(ks.A, acc, centre);
               }
             } else {
 #pragma unroll

@@ -22,12 +22,17 @@ __host__ __device__ constexpr double w_of(int q) {
   return q == 0 ? 4.0 / 9.0 : (q < 5 ? 1.0 / 9.0 : 1.0 / 36.0);
 }
 
-// a b + c.  FP64 with kExact: in one rounding, so that the kernels that take
-// the same step (T2S2-FDLBM1: march, tile, two steps per launch, one block)
-// round a node's values the same way (of a sum of two products the compiler may
-// fuse either).  Otherwise left to the compiler, which fuses FP32 products
-// alike in most kernels of the reduced forms but not in all: see moments_f32
-// and plan_mesh.
+// kExact, here and below: the roundings are spelled out, so that the kernels
+// that take the same step (T2S2-FDLBM1: march, tile, two steps per launch, one
+// block) round a node's values the same way; of a sum of two products the
+// compiler may fuse either, and its choice differs between kernels.  FP64 takes
+// it throughout, FP32 with a force.  FP32 without one is left to the compiler,
+// which fuses alike in those kernels but for what moments_f32 spells out (and
+// the one-block kernel on periodic grids, see plan_mesh).
+template <typename Real, bool kForce>
+constexpr bool kExactOf = sizeof(Real) == 8 || kForce;
+
+// a b + c, kExact in one rounding.
 template <bool kExact = true>
 __device__ inline double fma_of(double a, double b, double c) {
   if constexpr (kExact) return __builtin_fma(a, b, c);
@@ -35,6 +40,7 @@ __device__ inline double fma_of(double a, double b, double c) {
 }
 template <bool kExact = true>
 __device__ inline float fma_of(float a, float b, float c) {
+  if constexpr (kExact) return __builtin_fmaf(a, b, c);
   return a * b + c;
 }
 
@@ -154,10 +160,9 @@ __device__ inline unsigned mix32(unsigned x) {
 // of the nine values' FP32 bits, then a linear congruential sequence
 // (multiplier 1664525, increment 1013904223, on the low 24 bits of the state)
 // whose upper 16 bits serve one value each.  They depend only on the node and
-// the values: the same values round the same way under any tiling (on periodic
-// grids with a force the FP32 values themselves may differ in the last bit
-// between kernels), graph replays give the values of plain launches, and a state
-// that does not change rounds the same way again.  BF16: add 16 random bits to the FP32 bits and cut them;
+// the values: the same values round the same way under any tiling, graph
+// replays give the values of plain launches, and a state that does not change
+// rounds the same way again.  BF16: add 16 random bits to the FP32 bits and cut them;
 // FP16: the same with 13 bits on 2^14 x, then an exact conversion (in the
 // normal FP16 range; below it, 2^14 |x| < 6.1e-5, the conversion rounds to
 // nearest).  Non-finite values keep their class (canonical NaNs, Inf).
@@ -351,9 +356,9 @@ __host__ __device__ constexpr int wclass(int q) { return q == 0 ? 0 : (q < 5 ? 1
 // moment sums.  FP64 arithmetic divides in FP64.  FP32 arithmetic rounds
 // the sums to FP32 and multiplies by the hardware reciprocal of rho refined
 // by one Newton step.
-// (FP64 with kExact: no contraction here and in eq_brackets; x and y enter
-// sums, and whether the compiler fuses their products into those differs
-// between kernels.)
+// (kExact: no contraction here and in eq_brackets; x and y enter sums, and
+// whether the compiler fuses their products into those differs between
+// kernels.)
 template <bool kExact = true>
 __device__ inline void velocity(double s, double jx, double jy, double& r, double& x, double& y) {
   if constexpr (kExact) {
@@ -378,19 +383,37 @@ __device__ inline void velocity(double s, double jx, double jy, float& r, float&
   y = static_cast<float>(jy) * ir;
 }
 
+// The same with the force shift (Fx, Fy) half of eq 3.3.  FP32 with kExact: the
+// shift added in the rounding of the product.
+template <bool kExact = true, typename Real>
+__device__ inline void forced_velocity(double s, double jx, double jy, double half, double Fx,
+                                       double Fy, Real& r, Real& x, Real& y) {
+  if constexpr (kExact && sizeof(Real) == 4) {
+    r = 1.0f + static_cast<float>(s);
+    float ir = __builtin_amdgcn_rcpf(r);
+    ir = __builtin_fmaf(__builtin_fmaf(-r, ir, 1.0f), ir, ir);
+    x = __builtin_fmaf(static_cast<float>(jx), ir, static_cast<float>(half * Fx));
+    y = __builtin_fmaf(static_cast<float>(jy), ir, static_cast<float>(half * Fy));
+  } else {
+    velocity<kExact>(s, jx, jy, r, x, y);
+    x = add_scaled<kExact>(half, Fx, x);
+    y = add_scaled<kExact>(half, Fy, y);
+  }
+}
+
 // Brackets X_q of the equilibrium, f^eq_q - w_q = w_q (drho + rho X_q) with
 // X_q = 3 e_q + 9/2 e_q^2 - 3/2 |u|^2 and e_q = xi_q . u (eq 3.2, c_s^2 =
 // 1/3).  Opposite directions share 9/2 e^2 - 3/2 |u|^2.
 template <bool kExact = true, typename Real>
 __device__ inline void eq_brackets(Real x, Real y, Real X[kQ]) {
-  if constexpr (kExact && sizeof(Real) == 8) {
+  if constexpr (kExact) {
 #pragma clang fp contract(off)
-    const double uu = 1.5 * fma_of(x, x, y * y);
+    const Real uu = Real(1.5) * fma_of(x, x, y * y);
     X[0] = -uu;
-    auto pair = [&](double e, int qp, int qm) {
-      const double T = fma_of(4.5 * e, e, -uu);
-      X[qp] = fma_of(3.0, e, T);
-      X[qm] = fma_of(-3.0, e, T);
+    auto pair = [&](Real e, int qp, int qm) {
+      const Real T = fma_of(Real(4.5) * e, e, -uu);
+      X[qp] = fma_of(Real(3), e, T);
+      X[qm] = fma_of(Real(-3), e, T);
     };
     pair(x, 1, 3);
     pair(y, 2, 4);
@@ -444,9 +467,9 @@ __device__ inline void nee_shift_x(Real rho, const Real (&Xf)[kQ], const Real* X
 // The wall node's R_q of eq 3.10: R_q + f^eq_q(rho, u_b) - f^eq_q(rho, u_f)
 // from the brackets Xf of the fluid node's velocity (eq_brackets) and Xb of
 // the wall's (StepParams::xb), R_q + w_q rho (Xb_q - Xf_q), wr = w_q rho.
-template <typename Real>
+template <bool kExact = true, typename Real>
 __device__ __forceinline__ Real nee_r(Real wr, Real Xf, Real Xb, Real Rf) {
-  return fma_of(wr, Xb - Xf, Rf);
+  return fma_of<kExact>(wr, Xb - Xf, Rf);
 }
 
 // The wall whose node (i + dx, j + dy) is extrapolated from the fluid node

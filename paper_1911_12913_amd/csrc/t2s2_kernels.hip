@@ -97,14 +97,16 @@ template <typename Store, bool kForce, bool kWalls, int kScheme, bool kSaveS = f
 __global__ __launch_bounds__(step_threads(kStorageOf<Store>, kScheme), (kMinWaves<Store, kForce, kWalls, kScheme>)) void step_kernel(
     StepParams p) {
   using Real = typename Cvt<Store>::R;
-  // FP64: scheme 1 is taken by other kernels too, which round alike (see
-  // fma_of), and the family with gradient weights (0, 1, 0) equals it.  What no
-  // other kernel takes leaves its sums to the compiler: in this form it runs 1 to
-  // 3% slower (walled family 16 x 10, BF16, 22.7 us per step, 23.1 so; T1S2 in
-  // FP16 with stochastic rounding 31 x 33, 16.3 and 16.6; channel 1500 x 1400
-  // FP32 61.6, 64.2).
-  constexpr bool kExact = sizeof(Real) == 8 && (kScheme == 1 || kScheme == 3);
-  using Row = std::conditional_t<kExact, LdsPtr<Real>, const Real*>;
+  // Scheme 1 is taken by other kernels too, which round alike (see kExactOf), and
+  // the FP64 family with gradient weights (0, 1, 0) equals it.  What no other
+  // kernel takes leaves its sums to the compiler.  The FP64 forms also read the
+  // rings in another way (kFp64Rows): with both, the others run 1 to 3% slower
+  // (walled family 16 x 10, BF16, 22.7 us per step, 23.1 so; T1S2 in FP16 with
+  // stochastic rounding 31 x 33, 16.3 and 16.6; channel 1500 x 1400 FP32 61.6,
+  // 64.2).
+  constexpr bool kFp64Rows = sizeof(Real) == 8 && (kScheme == 1 || kScheme == 3);
+  constexpr bool kExact = kFp64Rows || (kScheme == 1 && kExactOf<Real, kForce>);
+  using Row = std::conditional_t<kFp64Rows, LdsPtr<Real>, const Real*>;
   // T2S2-FDLBM2, FP64, periodic: f^n of the phase-2 row from a reload.
   constexpr bool kFnRegs = kFnRegsOf<Store, kWalls, kScheme>;
   constexpr int kNP = kPPlanes<kScheme, kFnRegs>;
@@ -243,11 +245,10 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, kScheme), (kMinWave
         double s, jx, jy;
         moment_sums(g, s, jx, jy);
         Real rho, ux, uy;
-        velocity<kExact>(s, jx, jy, rho, ux, uy);
-        if (kForce) {
-          ux = add_scaled<kExact>(p.half_dt, p.Fx, ux);
-          uy = add_scaled<kExact>(p.half_dt, p.Fy, uy);
-        }
+        if constexpr (kForce)
+          forced_velocity<kExact>(s, jx, jy, p.half_dt, p.Fx, p.Fy, rho, ux, uy);
+        else
+          velocity<kExact>(s, jx, jy, rho, ux, uy);
         const Real d = static_cast<Real>(s);
         Real X[kQ];
         eq_brackets<kExact>(ux, uy, X);
@@ -331,11 +332,10 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, kScheme), (kMinWave
             }
             double s, jx, jy;
             moment_sums(S, s, jx, jy);
-            velocity<kExact>(s, jx, jy, rho, ux, uy);
-            if (kForce) {
-              ux = add_scaled<kExact>(hf, p.Fx, ux);
-              uy = add_scaled<kExact>(hf, p.Fy, uy);
-            }
+            if constexpr (kForce)
+              forced_velocity<kExact>(s, jx, jy, hf, p.Fx, p.Fy, rho, ux, uy);
+            else
+              velocity<kExact>(s, jx, jy, rho, ux, uy);
             const Real d = static_cast<Real>(s);
             eq_brackets<kExact>(ux, uy, X);
             R[0] = Real(0);
@@ -421,7 +421,7 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, kScheme), (kMinWave
                   // of the wall's velocity.
                   const Real* Xb = wall_brackets<Real>(p, wall_side_of(dx, dy));
                   Real* slotW = dy == 1 ? topR : ringR + ((r + dy) & (kRing - 1)) * (kQ - 1) * kLanes;
-                  if constexpr (kExact) {
+                  if constexpr (kFp64Rows) {
                     const Real r1 = Real(w_of(1)) * rho, r2 = Real(w_of(5)) * rho;
                     const Real r1b = Real(w_of(1)) * rho2, r2b = Real(w_of(5)) * rho2;
 #pragma unroll
@@ -478,7 +478,7 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, kScheme), (kMinWave
             Real acc = kScheme == 2 ? Real(0) : qold[q];
             if constexpr (gen_bbar) acc += v_now ? vnew[q] : vold[q];
             const int sy = ey_of(q) > 0 ? 0 : 1;
-            if constexpr (kExact) {
+            if constexpr (kFp64Rows) {
               // Each row where it is added, or ahead of the sum for the family
               // without a force (cavity 16 x 10 27.7 us per step, each where it is
               // added 28.7; scheme 1, channel 1100^2 without a force 54.9, ahead
@@ -494,11 +494,12 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, kScheme), (kMinWave
                 acc = full_taps(q, wxr, wyr, centre, acc, [&](int k) { return rows[k]; });
               }
             } else {
-              if (ex_of(q) > 0) acc = x_taps<0, false>(wxr, centre, acc);
-              if (ex_of(q) < 0) acc = x_taps<1, false>(wxr, centre, acc);
+              if (ex_of(q) > 0) acc = x_taps<0, kExact>(wxr, centre, acc);
+              if (ex_of(q) < 0) acc = x_taps<1, kExact>(wxr, centre, acc);
               if (ey_of(q) != 0) {
 #pragma unroll
-                for (int k = 0; k < kTaps; ++k) acc += wyr[sy * kTaps + k] * rb[k + sy][pq];
+                for (int k = 0; k < kTaps; ++k)
+                  acc = fma_of<kExact>(wyr[sy * kTaps + k], rb[k + sy][pq], acc);
               }
             }
             out[q] = kScheme == 2 ? qold[q] + Real(0.5) * acc : acc;
@@ -511,11 +512,10 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, kScheme), (kMinWave
             double s, jx, jy;
             moment_sums(out, s, jx, jy);
             Real rho, ux, uy;
-            velocity<kExact>(s, jx, jy, rho, ux, uy);
-            if (kForce) {
-              ux = add_scaled<kExact>(p.b2dt, p.Fx, ux);
-              uy = add_scaled<kExact>(p.b2dt, p.Fy, uy);
-            }
+            if constexpr (kForce)
+              forced_velocity<kExact>(s, jx, jy, p.b2dt, p.Fx, p.Fy, rho, ux, uy);
+            else
+              velocity<kExact>(s, jx, jy, rho, ux, uy);
             const Real d = static_cast<Real>(s);
             Real X[kQ];
             eq_brackets<kExact>(ux, uy, X);
@@ -548,7 +548,7 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, kScheme), (kMinWave
           p, dst, x0, x1, y0, y1, threadIdx.x % kBlockThreads, kBlockThreads,
           [&](int c2, int r2, int side, double& u, double& v) {
             // (By address, the unforced FP64 forms are 2% faster, the others slower.)
-            if (kExact && !kForce) {
+            if (kFp64Rows && !kForce) {
               u = p.uw[side][0];
               v = p.uw[side][1];
             } else {
@@ -622,6 +622,7 @@ template <typename Store, bool kForce, bool kWalls, bool kSaveS, int kH>
 __global__ __launch_bounds__((tile_waves<Store, kH>() * kLanes)) void tile_step_kernel(
     StepParams p) {
   using Real = typename Cvt<Store>::R;
+  constexpr bool kExact = kExactOf<Real, kForce>;
   constexpr int kWaves = tile_waves<Store, kH>();
   constexpr int kIn = kWaves * kH;   // rows of P
   constexpr int kMid = kIn - 4;      // rows of R
@@ -701,35 +702,34 @@ __global__ __launch_bounds__((tile_waves<Store, kH>() * kLanes)) void tile_step_
       if constexpr (sizeof(Real) == 4 && !kForce) {
         moments_f32<true>(s, jx, jy, rho, X);
       } else {
-        velocity(s, jx, jy, rho, ux, uy);
-        if (kForce) {
-          ux = add_scaled(p.half_dt, p.Fx, ux);
-          uy = add_scaled(p.half_dt, p.Fy, uy);
-        }
-        eq_brackets(ux, uy, X);
+        if constexpr (kForce)
+          forced_velocity<kExact>(s, jx, jy, p.half_dt, p.Fx, p.Fy, rho, ux, uy);
+        else
+          velocity<kExact>(s, jx, jy, rho, ux, uy);
+        eq_brackets<kExact>(ux, uy, X);
       }
       const Real d = static_cast<Real>(s);
       Real E[kQ], Fq[kQ];
 #pragma unroll
       for (int q = 0; q < kQ; ++q) {
-        E[q] = fma_of(rho, X[q], d);
-        Real Pq = fma_of(k.cPg, g[q], k.kP[wclass(q)] * E[q]);
+        E[q] = fma_of<kExact>(rho, X[q], d);
+        Real Pq = fma_of<kExact>(k.cPg, g[q], k.kP[wclass(q)] * E[q]);
         if (kForce) {
-          Fq[q] = force_term(q, p, ux, uy, E[q]);
-          Pq = fma_of(static_cast<Real>(p.cPF), Fq[q], Pq);
+          Fq[q] = force_term<kExact>(q, p, ux, uy, E[q]);
+          Pq = fma_of<kExact>(static_cast<Real>(p.cPF), Fq[q], Pq);
         }
         // Formed here: moved to the later phases, the FP32 products would be
         // fused another way than in step_kernel.
-        if constexpr (sizeof(Real) == 4) asm volatile("" : "+v"(Pq));
+        if constexpr (!kExact) asm volatile("" : "+v"(Pq));
         pr[h][q] = Pq;
         if (ey_of(q) != 0) tP[(j * kYMoving + y_slot(q)) * kLanes + lane] = Pq;
       }
       if (j >= kHalo && j < kIn - kHalo) {
 #pragma unroll
         for (int q = 0; q < kQ; ++q) {
-          qout[h][q] = fma_of(k.cQg, g[q], k.kQ[wclass(q)] * E[q]);
-          if (kForce) qout[h][q] = fma_of(static_cast<Real>(p.cQF), Fq[q], qout[h][q]);
-          if constexpr (sizeof(Real) == 4) asm volatile("" : "+v"(qout[h][q]));
+          qout[h][q] = fma_of<kExact>(k.cQg, g[q], k.kQ[wclass(q)] * E[q]);
+          if (kForce) qout[h][q] = fma_of<kExact>(static_cast<Real>(p.cQF), Fq[q], qout[h][q]);
+          if constexpr (!kExact) asm volatile("" : "+v"(qout[h][q]));
         }
       }
     }
@@ -769,14 +769,14 @@ __global__ __launch_bounds__((tile_waves<Store, kH>() * kLanes)) void tile_step_
       const int pq = y_slot(q) * kLanes;
       const Real centre = ey_of(q) != 0 ? rb[2][pq] : pr[h][q];
       Real acc = Real(0);
-      if (ex_of(q) > 0) acc = x_taps<0>(wxr, centre, acc);
-      if (ex_of(q) < 0) acc = x_taps<1>(wxr, centre, acc);
+      if (ex_of(q) > 0) acc = x_taps<0, kExact>(wxr, centre, acc);
+      if (ex_of(q) < 0) acc = x_taps<1, kExact>(wxr, centre, acc);
       if (ey_of(q) != 0) {
         const int sy = ey_of(q) > 0 ? 0 : 1;
 #pragma unroll
-        for (int k2 = 0; k2 < kTaps; ++k2) acc = fma_of(wyr[sy * kTaps + k2], rb[k2 + sy][pq], acc);
+        for (int k2 = 0; k2 < kTaps; ++k2) acc = fma_of<kExact>(wyr[sy * kTaps + k2], rb[k2 + sy][pq], acc);
       }
-      S[q] = q == 0 ? centre : fma_of(k.A, acc, centre);
+      S[q] = q == 0 ? centre : fma_of<kExact>(k.A, acc, centre);
     }
     if (kSaveS && lane_o && col_interior && out_row(h)) {
       Real* sv = static_cast<Real*>(p.save_s);
@@ -792,19 +792,18 @@ __global__ __launch_bounds__((tile_waves<Store, kH>() * kLanes)) void tile_step_
     if constexpr (sizeof(Real) == 4 && !kForce) {
       moments_f32<kWalls>(s, jx, jy, rho, X);
     } else {
-      velocity(s, jx, jy, rho, ux, uy);
-      if (kForce) {
-        ux = add_scaled(p.half_h, p.Fx, ux);
-        uy = add_scaled(p.half_h, p.Fy, uy);
-      }
-      eq_brackets(ux, uy, X);
+      if constexpr (kForce)
+        forced_velocity<kExact>(s, jx, jy, p.half_h, p.Fx, p.Fy, rho, ux, uy);
+      else
+        velocity<kExact>(s, jx, jy, rho, ux, uy);
+      eq_brackets<kExact>(ux, uy, X);
     }
     const Real d = static_cast<Real>(s);
 #pragma unroll
     for (int q = 1; q < kQ; ++q) {
-      const Real E = fma_of(rho, X[q], d);
-      Real Rq = fma_of(k.cRs, S[q], k.kR[wclass(q)] * E);
-      if (kForce) Rq = fma_of(static_cast<Real>(p.cRF), force_term(q, p, ux, uy, E), Rq);
+      const Real E = fma_of<kExact>(rho, X[q], d);
+      Real Rq = fma_of<kExact>(k.cRs, S[q], k.kR[wclass(q)] * E);
+      if (kForce) Rq = fma_of<kExact>(static_cast<Real>(p.cRF), force_term<kExact>(q, p, ux, uy, E), Rq);
       R[h][q] = Rq;
     }
     if (kWalls) {
@@ -822,14 +821,14 @@ __global__ __launch_bounds__((tile_waves<Store, kH>() * kLanes)) void tile_step_
 #pragma unroll
         for (int q = 1; q < kQ; ++q)
           if (ey_of(q) != 0)
-            wall[y_slot(q) * kLanes] = nee_r(wclass(q) == 1 ? r1 : r2, X[q], Xb[q], R[h][q]);
+            wall[y_slot(q) * kLanes] = nee_r<kExact>(wclass(q) == 1 ? r1 : r2, X[q], Xb[q], R[h][q]);
       }
       if (side) {
 #pragma unroll
         for (int q = 1; q < kQ; ++q) {
           const Real wr = wclass(q) == 1 ? r1 : r2;
-          const Real lo = from_above(nee_r(wr, X[q], tX[q], R[h][q]));
-          const Real hi = from_below(nee_r(wr, X[q], tX[kQ + q], R[h][q]));
+          const Real lo = from_above(nee_r<kExact>(wr, X[q], tX[q], R[h][q]));
+          const Real hi = from_below(nee_r<kExact>(wr, X[q], tX[kQ + q], R[h][q]));
           R[h][q] = col_interior ? R[h][q] : (c == 0 ? lo : (c == nx - 1 ? hi : Real(0)));
         }
       }
@@ -863,7 +862,7 @@ __global__ __launch_bounds__((tile_waves<Store, kH>() * kLanes)) void tile_step_
 #pragma unroll
         for (int k2 = 0; k2 < kTaps; ++k2) rows[k2] = rb[k2 + sy][pq];
       }
-      out[q] = full_taps(q, wxr, wyr, centre, acc, [&](int k) { return rows[k]; });
+      out[q] = full_taps<kExact>(q, wxr, wyr, centre, acc, [&](int k) { return rows[k]; });
     }
     if (lane_o && col_interior) {
       const unsigned boff =
@@ -874,7 +873,7 @@ __global__ __launch_bounds__((tile_waves<Store, kH>() * kLanes)) void tile_step_
   }
   if (kWalls) {
     __syncthreads();  // the tile's stores are visible to the block
-    piece_walls<true, false>(p, dst, x0, x1, y0, y1, threadIdx.x, kWaves * kLanes,
+    piece_walls<kExact, false>(p, dst, x0, x1, y0, y1, threadIdx.x, kWaves * kLanes,
                              [&](int, int, int side, double& u, double& v) {
                                u = tU[side][0];
                                v = tU[side][1];
@@ -999,11 +998,10 @@ __global__ __launch_bounds__(step_threads(kStorageOf<Store>, 0), (kMinWaves<Stor
         double s, jx, jy;
         moment_sums(g, s, jx, jy);
         Real rho, ux, uy;
-        velocity<kExact>(s, jx, jy, rho, ux, uy);
-        if (kForce) {
-          ux = add_scaled<kExact>(p.half_dt, p.Fx, ux);
-          uy = add_scaled<kExact>(p.half_dt, p.Fy, uy);
-        }
+        if constexpr (kForce)
+          forced_velocity<kExact>(s, jx, jy, p.half_dt, p.Fx, p.Fy, rho, ux, uy);
+        else
+          velocity<kExact>(s, jx, jy, rho, ux, uy);
         const Real d = static_cast<Real>(s);
         Real X[kQ];
         eq_brackets<kExact>(ux, uy, X);

@@ -18,18 +18,18 @@ namespace {
 
 // acc + the x taps of x_taps, the neighbours read from LDS: v(o) is the
 // value at offset o along x.
-template <typename Real, typename V>
+template <bool kExact, typename Real, typename V>
 __device__ __forceinline__ Real x_taps_at(int ex, const Real* w, Real centre, Real acc, V v) {
   if (ex > 0) {
-    acc = fma_of(w[0], v(-2), acc);
-    acc = fma_of(w[1], v(-1), acc);
-    acc = fma_of(w[2], centre, acc);
-    acc = fma_of(w[3], v(1), acc);
+    acc = fma_of<kExact>(w[0], v(-2), acc);
+    acc = fma_of<kExact>(w[1], v(-1), acc);
+    acc = fma_of<kExact>(w[2], centre, acc);
+    acc = fma_of<kExact>(w[3], v(1), acc);
   } else if (ex < 0) {
-    acc = fma_of(w[4], v(-1), acc);
-    acc = fma_of(w[5], centre, acc);
-    acc = fma_of(w[6], v(1), acc);
-    acc = fma_of(w[7], v(2), acc);
+    acc = fma_of<kExact>(w[4], v(-1), acc);
+    acc = fma_of<kExact>(w[5], centre, acc);
+    acc = fma_of<kExact>(w[6], v(1), acc);
+    acc = fma_of<kExact>(w[7], v(2), acc);
   }
   return acc;
 }
@@ -40,6 +40,7 @@ __device__ __forceinline__ Real x_taps_at(int ex, const Real* w, Real centre, Re
 template <typename Store, bool kForce, bool kWalls, int kNodes>
 __global__ __launch_bounds__(kNodes) void mesh_steps_kernel(StepParams p, int nsteps) {
   using Real = typename Cvt<Store>::R;
+  constexpr bool kExact = kExactOf<Real, kForce>;
   __shared__ Real tP[kQ * kNodes];  // [q][node]
   __shared__ Real tR[kQ * kNodes];
   const int nx = p.nx, ny = p.ny;
@@ -99,23 +100,22 @@ __global__ __launch_bounds__(kNodes) void mesh_steps_kernel(StepParams p, int ns
       double s, jx, jy;
       moment_sums(g, s, jx, jy);
       Real rho, ux, uy;
-      velocity(s, jx, jy, rho, ux, uy);
-      if (kForce) {
-        ux = add_scaled(p.half_dt, p.Fx, ux);
-        uy = add_scaled(p.half_dt, p.Fy, uy);
-      }
+      if constexpr (kForce)
+        forced_velocity<kExact>(s, jx, jy, p.half_dt, p.Fx, p.Fy, rho, ux, uy);
+      else
+        velocity<kExact>(s, jx, jy, rho, ux, uy);
       const Real d = static_cast<Real>(s);
       Real X[kQ];
-      eq_brackets(ux, uy, X);
+      eq_brackets<kExact>(ux, uy, X);
 #pragma unroll
       for (int q = 0; q < kQ; ++q) {
-        const Real E = fma_of(rho, X[q], d);
-        Real Pq = fma_of(k.cPg, g[q], k.kP[wclass(q)] * E);
-        Real Qq = fma_of(k.cQg, g[q], k.kQ[wclass(q)] * E);
+        const Real E = fma_of<kExact>(rho, X[q], d);
+        Real Pq = fma_of<kExact>(k.cPg, g[q], k.kP[wclass(q)] * E);
+        Real Qq = fma_of<kExact>(k.cQg, g[q], k.kQ[wclass(q)] * E);
         if (kForce) {
-          const Real Fq = force_term(q, p, ux, uy, E);
-          Pq = fma_of(static_cast<Real>(p.cPF), Fq, Pq);
-          Qq = fma_of(static_cast<Real>(p.cQF), Fq, Qq);
+          const Real Fq = force_term<kExact>(q, p, ux, uy, E);
+          Pq = fma_of<kExact>(static_cast<Real>(p.cPF), Fq, Pq);
+          Qq = fma_of<kExact>(static_cast<Real>(p.cQF), Fq, Qq);
         }
         Pown[q] = Pq;
         Q[q] = Qq;
@@ -135,33 +135,32 @@ __global__ __launch_bounds__(kNodes) void mesh_steps_kernel(StepParams p, int ns
       for (int q = 0; q < kQ; ++q) {
         const Real* t = tP + q * kNodes;
         const Real centre = Pown[q];
-        Real acc = x_taps_at(ex_of(q), wx, centre, Real(0), [&](int o) { return t[ix[o + 2]]; });
+        Real acc = x_taps_at<kExact>(ex_of(q), wx, centre, Real(0), [&](int o) { return t[ix[o + 2]]; });
         if (ey_of(q) != 0) {
           const int sy = ey_of(q) > 0 ? 0 : 1;
 #pragma unroll
           for (int k2 = 0; k2 < kTaps; ++k2) {
             const int o = k2 + sy;
-            acc = fma_of(wy[sy * kTaps + k2], o == 2 ? centre : t[iy[o]], acc);
+            acc = fma_of<kExact>(wy[sy * kTaps + k2], o == 2 ? centre : t[iy[o]], acc);
           }
         }
-        S[q] = q == 0 ? centre : fma_of(k.A, acc, centre);
+        S[q] = q == 0 ? centre : fma_of<kExact>(k.A, acc, centre);
       }
       double s, jx, jy;
       moment_sums(S, s, jx, jy);
       Real rho, ux, uy;
-      velocity(s, jx, jy, rho, ux, uy);
-      if (kForce) {
-        ux = add_scaled(p.half_h, p.Fx, ux);
-        uy = add_scaled(p.half_h, p.Fy, uy);
-      }
+      if constexpr (kForce)
+        forced_velocity<kExact>(s, jx, jy, p.half_h, p.Fx, p.Fy, rho, ux, uy);
+      else
+        velocity<kExact>(s, jx, jy, rho, ux, uy);
       const Real d = static_cast<Real>(s);
       Real X[kQ];
-      eq_brackets(ux, uy, X);
+      eq_brackets<kExact>(ux, uy, X);
 #pragma unroll
       for (int q = 1; q < kQ; ++q) {
-        const Real E = fma_of(rho, X[q], d);
-        Real Rq = fma_of(k.cRs, S[q], k.kR[wclass(q)] * E);
-        if (kForce) Rq = fma_of(static_cast<Real>(p.cRF), force_term(q, p, ux, uy, E), Rq);
+        const Real E = fma_of<kExact>(rho, X[q], d);
+        Real Rq = fma_of<kExact>(k.cRs, S[q], k.kR[wclass(q)] * E);
+        if (kForce) Rq = fma_of<kExact>(static_cast<Real>(p.cRF), force_term<kExact>(q, p, ux, uy, E), Rq);
         R[q] = Rq;
         tR[q * kNodes + node] = Rq;
       }
@@ -171,7 +170,7 @@ __global__ __launch_bounds__(kNodes) void mesh_steps_kernel(StepParams p, int ns
           const Real* Xb = wall_brackets<Real>(p, wall_side_of(dx, dy));
 #pragma unroll
           for (int q = 1; q < kQ; ++q)
-            tR[q * kNodes + wall] = nee_r(wclass(q) == 1 ? r1 : r2, X[q], Xb[q], R[q]);
+            tR[q * kNodes + wall] = nee_r<kExact>(wclass(q) == 1 ? r1 : r2, X[q], Xb[q], R[q]);
         });
       }
     }
@@ -198,10 +197,10 @@ __global__ __launch_bounds__(kNodes) void mesh_steps_kernel(StepParams p, int ns
 #pragma unroll
           for (int k2 = 0; k2 < kTaps; ++k2) rows[k2] = k2 + sy == 2 ? R[q] : t[iy[k2 + sy]];
         }
-        out[q] = full_taps_of(
+        out[q] = full_taps_of<kExact>(
             q, wy, Q[q], [&](int k2) { return rows[k2]; },
             [&](Real acc) {
-              return x_taps_at(ex_of(q), wx, R[q], acc, [&](int o) { return x[o + 2]; });
+              return x_taps_at<kExact>(ex_of(q), wx, R[q], acc, [&](int o) { return x[o + 2]; });
             });
       }
       if constexpr (kStochastic<Store>) {
@@ -219,12 +218,12 @@ __global__ __launch_bounds__(kNodes) void mesh_steps_kernel(StepParams p, int ns
         moment_sums(g, s, jx, jy);
         const double rho = 1.0 + s;
         const double ir = recip(rho);
-        const double ux = fma_of(jx, ir, p.half_dt * p.Fx);
-        const double uy = fma_of(jy, ir, p.half_dt * p.Fy);
+        const double ux = fma_of<kExact>(jx, ir, p.half_dt * p.Fx);
+        const double uy = fma_of<kExact>(jy, ir, p.half_dt * p.Fy);
         double ub, vb;
         wall_velocity(p, c + dx, r + dy, ub, vb);
         Real sh[kQ];
-        nee_shift(rho, ux, uy, ub, vb, sh);
+        nee_shift<kExact>(rho, ux, uy, ub, vb, sh);
 #pragma unroll
         for (int q = 0; q < kQ; ++q)
           tP[q * kNodes + wall] = Cvt<Store>::ld(Cvt<Store>::st(g[q] + sh[q]));

@@ -114,7 +114,7 @@ using LdsPtr = const __attribute__((address_space(3))) Real*;
 // terms: the rows above, the row itself (the x taps first), the rows below.
 // FP32 takes the x taps first.
 // x(acc): acc plus the x taps.
-template <typename Real, typename Row, typename X>
+template <bool kExact = true, typename Real, typename Row, typename X>
 __device__ __forceinline__ Real full_taps_of(int q, const Real* wy, Real acc,
                                              Row row, X x) {
   const int sy = ey_of(q) > 0 ? 0 : 1;
@@ -122,7 +122,7 @@ __device__ __forceinline__ Real full_taps_of(int q, const Real* wy, Real acc,
     acc = x(acc);
     if (ey_of(q) != 0) {
 #pragma unroll
-      for (int k = 0; k < kTaps; ++k) acc += wy[sy * kTaps + k] * row(k);
+      for (int k = 0; k < kTaps; ++k) acc = fma_of<kExact>(wy[sy * kTaps + k], row(k), acc);
     }
     return acc;
   }
@@ -141,12 +141,12 @@ __device__ __forceinline__ Real full_taps_of(int q, const Real* wy, Real acc,
   }
   return acc;
 }
-template <typename Real, typename Row>
+template <bool kExact = true, typename Real, typename Row>
 __device__ __forceinline__ Real full_taps(int q, const Real* wx, const Real* wy, Real centre,
                                           Real acc, Row row) {
-  return full_taps_of(q, wy, acc, row, [&](Real a) {
-    if (ex_of(q) > 0) a = x_taps<0>(wx, centre, a);
-    if (ex_of(q) < 0) a = x_taps<1>(wx, centre, a);
+  return full_taps_of<kExact>(q, wy, acc, row, [&](Real a) {
+    if (ex_of(q) > 0) a = x_taps<0, kExact>(wx, centre, a);
+    if (ex_of(q) < 0) a = x_taps<1, kExact>(wx, centre, a);
     return a;
   });
 }

@@ -1187,6 +1187,36 @@ def test_tiles_on_the_smallest_meshes_are_bitwise_the_march(kind, storage, monke
         _compare(case, g, d, u, v, oracle.run(case, phi0, 60))
 
 
+@pytest.mark.parametrize("storage", ["f32", "bf16", "bf16sr", "f16sr"])
+@pytest.mark.parametrize("nx,ny,walls", [(15, 14, "y"), (31, 33, "xy"), (42, 71, "y"), (27, 19, "")])
+def test_forced_reduced_steps_are_bitwise_the_same_by_every_kernel(nx, ny, walls, storage,
+                                                                   monkeypatch):
+    """The reduced forms with a force: the state does not depend on how the
+    steps are divided into calls, nor on the kernel that takes them (one block,
+    the march in two launch shapes, both tile shapes)."""
+    case = _forced_channel(nx, ny, walled_x=walls == "xy")
+    if not walls:
+        case.y, case.period_y, case.periodic_y = np.arange(ny) / ny, 1.0, True
+    phi0 = W.random_state((9, ny, nx), 5e-3, 3)
+
+    def run(calls, **env):
+        for k, v in env.items():
+            monkeypatch.setenv(k, v)
+        ctx = t2s2.context_for_case(case, storage=storage)
+        for k in env:
+            monkeypatch.delenv(k)
+        ctx.init_distributions(torch.from_numpy(phi0))
+        for n in calls:
+            ctx.step(n)
+        return ctx.read_distributions().cpu().numpy()
+
+    whole = run([24])
+    assert np.isfinite(whole).all()
+    assert np.array_equal(run([1] * 24), whole)
+    for env in ({"T2S2_BLOCKS": "8"}, {"T2S2_TILE": "0"}, {"T2S2_TILE": "1"}, {"T2S2_TILE": "2"}):
+        assert np.array_equal(run([24], **env), whole), env
+
+
 @pytest.mark.parametrize("kind,per_graph,kernel", [("mesh", 2, "mesh_steps_kernel"),
                                                    ("mesh", 300, "mesh_steps_kernel"),
                                                    ("pair", 10, "pair_step_kernel"),
