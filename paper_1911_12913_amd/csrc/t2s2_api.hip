@@ -359,9 +359,9 @@ constexpr int64_t kMeshSteps = 256;
 //     force never (channel 31 x 33, 20 steps 288 / 157);
 //   the reduced forms with walls from three steps (1024 nodes, BF16, 2 steps 14.4
 //     / 14.7, 3 steps 19.9 / 22.1, 20 steps 113 / 147).  Not on periodic grids,
-//     where the compiler fuses the FP32 products in another way than in the tile
-//     kernel, and stochastic rounding would turn last-bit differences into whole
-//     units of the 16-bit forms.
+//     where the compiler fuses the FP32 products of a step without a force in
+//     another way than in the tile kernel, and stochastic rounding would turn
+//     last-bit differences into whole units of the 16-bit forms.
 int plan_mesh(const StepParams& sp, int storage) {
   const bool walls = !sp.per_x || !sp.per_y;
   const long long nodes = static_cast<long long>(sp.nx) * sp.ny;

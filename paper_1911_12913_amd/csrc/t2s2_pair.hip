@@ -2,9 +2,10 @@
 // storage, A > 0).
 //
 // Measured (us per step, single steps -> this kernel): Taylor-Green 4096^2
-// 494 -> 345, 2048^2 132 -> 101, cavity 4097^2 541 -> 377, 2049^2 151 -> 117.
-// At 4096^2 it reads 1.15 and writes 1.00 times the state per two steps (3.6
-// TB/s), with the vector units 66% busy: bound by neither alone.
+// 489 -> 348, 2048^2 137 -> 103, cavity 4097^2 532 -> 369, 2049^2 151 -> 117.
+// At 4096^2 it reads 1.16 and writes 1.00 times the state per two steps (3.8
+// TB/s), with the vector units 72% busy (75% of the instructions FP64); the
+// 2049^2 cavity reads 1.53 and writes 1.00, 62% busy: bound by neither alone.
 //
 // A step reads and writes the state once, and at large meshes it runs at the
 // memory's rate; taking two steps per pass halves that traffic.  A block is
