@@ -66,16 +66,18 @@ def kernel_source_hash() -> str:
     return h.hexdigest()[:16]
 
 
-def measured_traffic(storage: str):
+def measured_traffic(storage: str, kernel: str, n: int):
     """HBM bytes per launch from the committed rocprofv3 counter summary, if
-    it was taken on the current kernel sources; else None."""
+    it was taken on the current kernel sources, this kernel and its grid of
+    4096 x 4096; else None."""
     try:
         with open(TRAFFIC_FILE) as f:
             rec = json.load(f)
     except (OSError, ValueError):
         return None
     entry = rec.get(storage)
-    if not entry or rec.get("kernel_hash") != kernel_source_hash():
+    if (not entry or rec.get("kernel_hash") != kernel_source_hash() or n != 4096
+            or entry["kernel"].split("<")[0] != kernel):
         return None
     return entry.get("bytes_per_launch")
 
@@ -442,7 +444,7 @@ def main(argv=None):
               "mesh_steps_kernel": -(-args.steps // 256)}.get(timing["kernel"], args.steps)
     bytes_step = BYTES_PER_NODE[args.storage] * passes / args.steps
     achieved = bytes_step * nodes / (ms_step * 1e-3) / 1e9
-    traffic = measured_traffic(args.storage)
+    traffic = measured_traffic(args.storage, timing["kernel"], n)
 
     # closed-form velocity (eq 3.4) at the final time, for every form's error
     import torch
@@ -463,8 +465,8 @@ def main(argv=None):
                      "rel_l2_velocity_vs_headline": rel_l2_dev(vel_f, vel),
                      "rel_l2_velocity_vs_closed_form": rel_l2_dev(vel_f, exact),
                      "hbm_frac": bl / HBM_PEAK_GBS, "bytes_per_node": BYTES_PER_NODE[st],
-                     "traffic": measured_traffic(st), "nonfinite": diag_f["nonfinite"],
-                     "timing": tim_f}
+                     "traffic": measured_traffic(st, tim_f["kernel"], n),
+                     "nonfinite": diag_f["nonfinite"], "timing": tim_f}
         del vel_f
     del exact
 
